@@ -2,19 +2,36 @@
 // Sec. "Prior-Conditioned Gaussian Parameterization").
 //
 // pgs_knn: exact k nearest neighbours through a uniform grid.  The points'
-// bounding box is cut into cubic cells (at most 128 along its longest side);
+// bounding box is cut into cubic cells (1 to 128 along its longest side, the
+// count chosen from how a sample of the points shares cells, k_grid_choose);
 // points are counted per cell, the counts scanned into cell starts and the
 // points' coordinates and indices gathered in cell order.  One lane per query
 // (queries in cell order, so a wave searches neighbouring cells) visits the
-// cells in shells of growing Chebyshev distance r around its own cell and
-// keeps its k best (squared distance, index) pairs sorted in registers,
-// ordered by distance and then index.  Every point of a cell r + 1 or more
-// cells away is farther than r cell widths, so the search stops after shell
-// r once the k-th distance is at most (r h)^2: no unvisited point can enter
-// or tie.  Squared distances are ((dx*dx) + (dy*dy)) + (dz*dz) in float64
-// with contraction off, which fixes every rounding, so the neighbour sets and
-// their order equal a brute-force search with ties broken by the smaller
-// index, bit for bit, whatever order the cells are visited in.
+// cells within one cell of its own, then shells of growing Chebyshev distance
+// r.  A row of cells along x is one run of points, so the first block is nine
+// runs.  Every point of a cell r + 1 or more cells away is farther than
+// r cell widths (plus the query's distance to its own cell's nearest face),
+// so the search stops once the k-th distance is within that reach: no
+// unvisited point can enter or tie.  Squared distances are
+// ((dx*dx) + (dy*dy)) + (dz*dz) in float64 with contraction off, which fixes
+// every rounding, so the neighbour sets and their order equal a brute-force
+// search with ties broken by the smaller index, bit for bit, whatever order
+// the cells are visited in.
+//
+// The search keeps its candidates as 64-bit keys, the float32 rounding of the
+// distance above the point's position in cell order.  Such a key is ordered
+// like the positive double it spells, so a sorted list takes a new key with
+// one v_max_f64 and one v_min_f64 per slot and no index moves (the lists of
+// (double, index) pairs that this replaces took about ten instructions per
+// slot, and one lane's insertion holds up its wave).  The list holds two keys
+// more than k; its entries' exact distances and indices are then formed again
+// and sorted.  Rounding is monotone, so every point left out has an exact
+// distance above the k-th whenever the k-th's rounding is below the list's
+// last key; where it is not (many points at one distance), the lane searches
+// again with exact comparisons (knn_exact).  On 300k points of a
+// scene's surfaces with k = 16 the search went from 0.93 to 0.20 ms (41M vector
+// instructions, 306 MB of writes scattered to the queries' own order) and the
+// whole call from 1.06 to 0.27 ms; on 2000 points from 7.8 to 0.17 ms.
 //
 // pgs_pca_seed: per point, in float64: covariance of the 16 neighbours about
 // their centroid, cyclic Jacobi eigen-decomposition of the 3x3 matrix,
@@ -40,11 +57,13 @@ __device__ __forceinline__ double sqdist(double qx, double qy, double qz, double
 // dims[3] cells per axis (at most kGridMax).
 constexpr int kGridMax = 128;
 constexpr int kBoxBlocks = 256;
+constexpr uint32_t kGridCells = (uint32_t)kGridMax * kGridMax * kGridMax;
 
 struct GridDesc {
     double lo[3];
     double h;
     int dims[3];
+    uint32_t cells;  // dims[0] dims[1] dims[2]
 };
 
 __device__ __forceinline__ int cell_axis(double v, double lo, double h, int dim) {
@@ -53,8 +72,12 @@ __device__ __forceinline__ int cell_axis(double v, double lo, double h, int dim)
 }
 
 // Per-block partial bounding boxes: part[b][0..2] minima, [3..5] maxima.
-__global__ __launch_bounds__(256) void k_box_partial(const float* __restrict__ pts, int m, float* __restrict__ part) {
+// Also clears the cell counts.
+__global__ __launch_bounds__(256) void k_box_partial(const float* __restrict__ pts, int m, float* __restrict__ part,
+                                                     uint32_t* __restrict__ counts) {
     __shared__ float red[6][256];
+    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < kGridCells / 4; i += gridDim.x * 256)
+        reinterpret_cast<uint4*>(counts)[i] = make_uint4(0u, 0u, 0u, 0u);
     float mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < m; i += gridDim.x * blockDim.x)
         for (int a = 0; a < 3; ++a) {
@@ -78,117 +101,211 @@ __global__ __launch_bounds__(256) void k_box_partial(const float* __restrict__ p
     if (threadIdx.x < 6) part[blockIdx.x * 6 + threadIdx.x] = red[threadIdx.x][0];
 }
 
-// The grid from the partial boxes (every thread computes the same value).
-__device__ GridDesc grid_of(const float* __restrict__ part) {
-    float mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (int b = 0; b < kBoxBlocks; ++b)
-        for (int a = 0; a < 3; ++a) {
-            mn[a] = fminf(mn[a], part[b * 6 + a]);
-            mx[a] = fmaxf(mx[a], part[b * 6 + 3 + a]);
-        }
+// A grid of `cells` cells along the longest side of the box [mn, mx].
+__device__ __forceinline__ GridDesc make_grid(const float* mn, const float* mx, double cells) {
     GridDesc g;
     double ext = 0.0;
     for (int a = 0; a < 3; ++a) ext = fmax(ext, (double)mx[a] - (double)mn[a]);
-    g.h = ext > 0.0 ? ext / kGridMax : 1.0;
+    g.h = ext > 0.0 ? ext / cells : 1.0;
     for (int a = 0; a < 3; ++a) {
         g.lo[a] = mn[a];
         const int d = (int)floor(((double)mx[a] - (double)mn[a]) / g.h) + 1;
         g.dims[a] = d < 1 ? 1 : (d > kGridMax ? kGridMax : d);
     }
+    g.cells = (uint32_t)g.dims[0] * g.dims[1] * g.dims[2];
     return g;
 }
 
-__global__ __launch_bounds__(256) void k_cell_count(const float* __restrict__ pts, int m,
-                                                    const float* __restrict__ part, uint32_t* __restrict__ counts,
-                                                    uint32_t* __restrict__ cell_of) {
-    __shared__ GridDesc sg;
-    if (threadIdx.x == 0) sg = grid_of(part);
+// The grid (one workgroup).  The search costs what the points of the 27
+// cells around a query cost as long as k neighbours lie within one cell
+// width, and far more when shells of empty cells have to be walked: with 128
+// cells a side whatever the cloud, 2000 points took 9 ms where 300k took
+// 0.9 ms.  So the cells are sized for `want` other points in the cell of a
+// point, which on a surface puts about pi want within one cell width; the
+// caller's max(4, 0.7 k) measured best or close to it for each k (surface
+// clouds of 20k and 300k points, wanted shares 5 to 20).
+// A sample of the points is dropped into grids of 64, 32, 16, 8 and 4 cells a
+// side (each the halved coordinates of the one before); the pairs that share
+// a cell, scaled from the sample to m points, are each grid's share, and the
+// wanted share lies between two of them (or beyond the finest) with the
+// dimension that the two show.  Only the cost of the search depends on the
+// choice, never its result.  One point per thread and the three coarse grids
+// in LDS: with four points and every grid counted by atomics in memory the
+// kernel took 150 us of queueing on the coarse grids' few cells, 18 us now.
+constexpr int kChooseThreads = 1024;
+constexpr int kLevels = 5;              // 64 >> level cells a side
+constexpr int kLdsCells = 17 * 17 * 17 + 9 * 9 * 9 + 5 * 5 * 5;
+
+__global__ __launch_bounds__(kChooseThreads) void k_grid_choose(const float* __restrict__ pts, int m,
+                                                                const float* __restrict__ part,
+                                                                uint32_t* __restrict__ counts, float want,
+                                                                GridDesc* __restrict__ desc) {
+    __shared__ float box[6];
+    __shared__ uint32_t pairs[kLevels];
+    __shared__ uint32_t coarse[kLdsCells];
+    const int t = threadIdx.x;
+    const int s = min(m, kChooseThreads);
+    float p[3] = {0.f, 0.f, 0.f};
+    if (t < s) {
+        const int i = (int)((long long)t * m / s);
+        for (int a = 0; a < 3; ++a) p[a] = pts[(size_t)a * m + i];
+    }
+    if (t < 6 * 64) {  // one wave per box bound
+        const int a = t >> 6, l = t & 63;
+        float v = part[l * 6 + a];
+        for (int b = l + 64; b < kBoxBlocks; b += 64) {
+            const float u = part[b * 6 + a];
+            v = a < 3 ? fminf(v, u) : fmaxf(v, u);
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            const float u = __shfl_xor(v, o);
+            v = a < 3 ? fminf(v, u) : fmaxf(v, u);
+        }
+        if (l == 0) box[a] = v;
+    }
+    if (t < kLevels) pairs[t] = 0u;
+    for (int e = t; e < kLdsCells; e += kChooseThreads) coarse[e] = 0u;
     __syncthreads();
-    const GridDesc g = sg;
+    uint32_t at[2] = {0u, 0u};
+    if (t < s) {
+        const GridDesc g = make_grid(box, box + 3, 64.0);
+        int c[3], d[3];
+        for (int a = 0; a < 3; ++a) {
+            c[a] = cell_axis(p[a], g.lo[a], g.h, g.dims[a]);
+            d[a] = g.dims[a];  // at most 65
+        }
+        uint32_t old[kLevels], base = 0;
+        for (int l = 0; l < kLevels; ++l) {
+            const uint32_t cell = base + ((uint32_t)c[2] * d[1] + c[1]) * d[0] + c[0];
+            if (l < 2) {
+                at[l] = cell;
+                old[l] = atomicAdd(&counts[cell], 1u);
+            } else {
+                old[l] = atomicAdd(&coarse[cell], 1u);
+            }
+            base = l == 1 ? 0u : base + (uint32_t)d[0] * d[1] * d[2];
+            for (int a = 0; a < 3; ++a) {
+                c[a] >>= 1;
+                d[a] = (d[a] + 1) >> 1;
+            }
+        }
+        for (int l = 0; l < kLevels; ++l)
+            if (old[l]) atomicAdd(&pairs[l], old[l]);
+    }
+    __syncthreads();  // every count has returned
+    if (t < s) {
+        counts[at[0]] = 0u;
+        counts[at[1]] = 0u;
+    }
+    if (t == 0) {
+        // mean number of other points in a point's cell, at m points
+        float share[kLevels];
+        const float up = 2.0f / (float)s * ((float)(m - 1) / (float)max(s - 1, 1));
+        for (int l = 0; l < kLevels; ++l) share[l] = fmaxf((float)pairs[l] * up, 0.1f);
+        // the finest grid that holds the wanted share, or the coarsest
+        int l = 0;
+        while (l + 1 < kLevels && share[l] < want) ++l;
+        // share ~ side^-dimension between this grid and its finer (or, from
+        // the finest, coarser) neighbour, the dimension kept between 1 and 3
+        const int n = l > 0 ? l : 1;
+        const float dim = fminf(3.0f, fmaxf(1.0f, log2f(share[n] / share[n - 1])));
+        const float side = (float)(64 >> l) * exp2f(log2f(share[l] / want) / dim);
+        *desc = make_grid(box, box + 3, (double)fminf((float)kGridMax, fmaxf(1.0f, floorf(side))));
+    }
+}
+
+// Cell of every point and its rank among the cell's points.
+__global__ __launch_bounds__(256) void k_cell_count(const float* __restrict__ pts, int m,
+                                                    const GridDesc* __restrict__ desc, uint32_t* __restrict__ counts,
+                                                    uint32_t* __restrict__ cell_of, uint32_t* __restrict__ rank_of) {
+    const GridDesc g = *desc;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < m; i += gridDim.x * blockDim.x) {
         const int cx = cell_axis(pts[i], g.lo[0], g.h, g.dims[0]);
         const int cy = cell_axis(pts[(size_t)m + i], g.lo[1], g.h, g.dims[1]);
         const int cz = cell_axis(pts[2 * (size_t)m + i], g.lo[2], g.h, g.dims[2]);
         const uint32_t c = ((uint32_t)cz * g.dims[1] + cy) * g.dims[0] + cx;
         cell_of[i] = c;
-        atomicAdd(&counts[c], 1u);
+        rank_of[i] = atomicAdd(&counts[c], 1u);
     }
 }
 
-// Exclusive scan of the cell counts into starts (one chunk of 4096 per
-// workgroup; the chunk totals are added up by each workgroup itself).
+// Exclusive scan of the cell counts into starts, starts[cells] = m (one chunk
+// of 4096 per workgroup, chunks past the last cell empty; the chunk totals
+// are added up by each workgroup itself).
 constexpr int kCellScanItems = 4096;
 
-__global__ __launch_bounds__(256) void k_cell_total(const uint32_t* __restrict__ counts, uint32_t n,
+__device__ __forceinline__ uint32_t block_sum_256(uint32_t v, uint32_t* red) {
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return red[0] + red[1] + red[2] + red[3];
+}
+
+__global__ __launch_bounds__(256) void k_cell_total(const uint32_t* __restrict__ counts,
+                                                    const GridDesc* __restrict__ desc,
                                                     uint32_t* __restrict__ totals) {
-    __shared__ uint32_t red[256];
+    __shared__ uint32_t red[4];
+    const uint32_t n = desc->cells;
+    if (blockIdx.x * kCellScanItems >= n) return;
+    // counts past the last cell are zero, and the array holds whole chunks
+    const uint4* c = reinterpret_cast<const uint4*>(counts + (size_t)blockIdx.x * kCellScanItems);
     uint32_t s = 0;
-    for (uint32_t i = blockIdx.x * kCellScanItems + threadIdx.x; i < min(n, (blockIdx.x + 1) * kCellScanItems);
-         i += 256)
-        s += counts[i];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if (threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-        __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kCellScanItems / 1024; ++k) {
+        const uint4 v = c[k * 256 + threadIdx.x];
+        s += v.x + v.y + v.z + v.w;
     }
-    if (threadIdx.x == 0) totals[blockIdx.x] = red[0];
+    s = block_sum_256(s, red);
+    if (threadIdx.x == 0) totals[blockIdx.x] = s;
 }
 
-__global__ __launch_bounds__(256) void k_cell_starts(const uint32_t* __restrict__ counts, uint32_t n,
+__global__ __launch_bounds__(256) void k_cell_starts(const uint32_t* __restrict__ counts, int m,
+                                                     const GridDesc* __restrict__ desc,
                                                      const uint32_t* __restrict__ totals,
-                                                     uint32_t* __restrict__ starts, uint32_t* __restrict__ cursor) {
-    __shared__ uint32_t sc[256];
-    __shared__ uint32_t s_before;
-    uint32_t b = 0;
-    for (uint32_t k = threadIdx.x; k < blockIdx.x; k += 256) b += totals[k];
-    sc[threadIdx.x] = b;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t t = 0;
-        for (int k = 0; k < 256; ++k) t += sc[k];
-        s_before = t;
-    }
-    __syncthreads();
-    // 16 consecutive cells per thread
-    const uint32_t base = blockIdx.x * kCellScanItems + threadIdx.x * 16;
-    uint32_t loc[16], sum = 0;
-    for (int k = 0; k < 16; ++k) {
-        loc[k] = base + k < n ? counts[base + k] : 0u;
-        sum += loc[k];
-    }
-    sc[threadIdx.x] = sum;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        const uint32_t add = threadIdx.x >= (unsigned)off ? sc[threadIdx.x - off] : 0u;
-        __syncthreads();
-        sc[threadIdx.x] += add;
-        __syncthreads();
-    }
-    uint32_t run = s_before + sc[threadIdx.x] - sum;
-    for (int k = 0; k < 16; ++k) {
-        if (base + k < n) {
-            starts[base + k] = run;
-            cursor[base + k] = run;
+                                                     uint32_t* __restrict__ starts) {
+    __shared__ uint32_t red[4], wsum[4];
+    const uint32_t n = desc->cells, base = blockIdx.x * kCellScanItems;
+    if (base >= n) return;
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    uint32_t run = 0;
+    for (uint32_t k = t; k < blockIdx.x; k += 256) run += totals[k];
+    run = block_sum_256(run, red);
+    // four cells per thread and round
+    for (int k = 0; k < kCellScanItems / 1024; ++k) {
+        const uint32_t at = base + k * 1024 + t * 4;
+        const uint4 v = *reinterpret_cast<const uint4*>(counts + at);
+        const uint32_t own = v.x + v.y + v.z + v.w;
+        uint32_t inc = own;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t u = __shfl_up(inc, o);
+            if (lane >= o) inc += u;
         }
-        run += loc[k];
+        if (lane == 63) wsum[wv] = inc;
+        __syncthreads();
+        uint32_t before = run;
+        for (int w = 0; w < 4; ++w) {
+            if (w < wv) before += wsum[w];
+            run += wsum[w];
+        }
+        const uint32_t e = before + inc - own;
+        *reinterpret_cast<uint4*>(starts + at) = make_uint4(e, e + v.x, e + v.x + v.y, e + v.x + v.y + v.z);
+        __syncthreads();
     }
-}
-
-__global__ __launch_bounds__(256) void k_cell_end(const uint32_t* __restrict__ counts, uint32_t n,
-                                                  uint32_t* __restrict__ starts) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) starts[n] = starts[n - 1] + counts[n - 1];
+    // a chunk that ends on the last cell leaves its end to be written
+    if (t == 0 && base + kCellScanItems >= n) starts[n] = (uint32_t)m;
 }
 
 // Points in cell order (order inside a cell is arbitrary: the search's
 // tie rule does not depend on it).
 __global__ __launch_bounds__(256) void k_cell_scatter(const float* __restrict__ pts, int m,
                                                       const uint32_t* __restrict__ cell_of,
-                                                      uint32_t* __restrict__ cursor, float4* __restrict__ sorted) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < m; i += gridDim.x * blockDim.x) {
-        const uint32_t at = atomicAdd(&cursor[cell_of[i]], 1u);
-        sorted[at] = make_float4(pts[i], pts[(size_t)m + i], pts[2 * (size_t)m + i], __int_as_float(i));
-    }
+                                                      const uint32_t* __restrict__ rank_of,
+                                                      const uint32_t* __restrict__ starts,
+                                                      float4* __restrict__ sorted) {
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < m; i += gridDim.x * blockDim.x)
+        sorted[starts[cell_of[i]] + rank_of[i]] =
+            make_float4(pts[i], pts[(size_t)m + i], pts[2 * (size_t)m + i], __int_as_float(i));
 }
 
 template <int K>
@@ -212,18 +329,13 @@ __device__ __forceinline__ void knn_insert(double d, int idx, double (&bd)[K], i
     }
 }
 
+// Search of one query with exact comparisons throughout (the general path:
+// many points at one distance, distances past float32, coordinates that are
+// not finite).
 template <int K>
-__global__ __launch_bounds__(kKnnThreads) void k_knn_grid(const float4* __restrict__ sorted, int m,
-                                                          const float* __restrict__ part,
-                                                          const uint32_t* __restrict__ starts,
-                                                          int* __restrict__ nbr, double* __restrict__ d2out) {
-    __shared__ GridDesc sg;
-    if (threadIdx.x == 0) sg = grid_of(part);
-    __syncthreads();
-    const GridDesc g = sg;
-    const int j = blockIdx.x * kKnnThreads + threadIdx.x;
-    if (j >= m) return;
-    const float4 qp = sorted[j];
+__device__ __noinline__ void knn_exact(const float4* __restrict__ sorted, int m, const GridDesc& g,
+                                       const uint32_t* __restrict__ starts, float4 qp, int* __restrict__ nbr,
+                                       double* __restrict__ d2out) {
     const int q = __float_as_int(qp.w);
     const double qx = qp.x, qy = qp.y, qz = qp.z;
     const int cx = cell_axis(qx, g.lo[0], g.h, g.dims[0]);
@@ -271,19 +383,155 @@ __global__ __launch_bounds__(kKnnThreads) void k_knn_grid(const float4* __restri
     }
 }
 
+// Key of a candidate: the float32 rounding of its squared distance above its
+// position, as a double.  The patterns up to float32's infinity spell positive
+// finite doubles, ordered like the pairs (rounded distance, position); those
+// of NaN (sign cleared) lie above them or spell NaN and are never taken.
+constexpr uint32_t kInfBits = 0x7f800000u;
+__device__ __forceinline__ double knn_key(uint32_t hi, uint32_t lo) { return __hiloint2double((int)hi, (int)lo); }
+
+// The smaller and the larger of two keys, one instruction each (the compiler's
+// fmin and fmax first quiet each operand, which doubles the list's cost).
+__device__ __forceinline__ double key_min(double a, double b) {
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ double key_max(double a, double b) {
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// Bound by vector issue: about 15 instructions per candidate and, whenever
+// one of the wave's lanes takes it, two per slot of the list.
+template <int K>
+__global__ __launch_bounds__(kKnnThreads) void k_knn_grid(const float4* __restrict__ sorted, int m,
+                                                          const GridDesc* __restrict__ desc,
+                                                          const uint32_t* __restrict__ starts,
+                                                          int* __restrict__ nbr, double* __restrict__ d2out) {
+    constexpr int KE = K + 2;
+    const GridDesc& g = *desc;
+    const int j = blockIdx.x * kKnnThreads + threadIdx.x;
+    if (j >= m) return;
+    const float4 qp = sorted[j];
+    const double qx = qp.x, qy = qp.y, qz = qp.z;
+    const int nx = g.dims[0], ny = g.dims[1], nz = g.dims[2];
+    const double h = g.h;
+    const int cx = cell_axis(qx, g.lo[0], h, nx);
+    const int cy = cell_axis(qy, g.lo[1], h, ny);
+    const int cz = cell_axis(qz, g.lo[2], h, nz);
+    // distance from the query to its own cell's nearest face, in cells, less
+    // a margin for the rounding of the cell decisions
+    auto face_gap = [&](double v, double lo, int c) {
+        const double f = (v - lo) / h - c;
+        return fmin(f, 1.0 - f);
+    };
+    double gap = fmin(face_gap(qx, g.lo[0], cx), fmin(face_gap(qy, g.lo[1], cy), face_gap(qz, g.lo[2], cz)));
+    gap = fmax(gap, 0.0) - 1e-9;
+    double a[KE];
+#pragma unroll
+    for (int k = 0; k < KE; ++k) a[k] = knn_key(kInfBits, 0xffffffffu);
+    auto take = [&](uint32_t s, uint32_t e) {
+        for (uint32_t t0 = s; t0 < e; t0 += 4) {
+            float4 p[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) p[u] = sorted[min(t0 + u, e - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t t = t0 + u;
+                const float d = (float)sqdist(qx, qy, qz, p[u].x, p[u].y, p[u].z);
+                const double x = knn_key(__float_as_uint(d) & 0x7fffffffu, t);
+                if (t < e && t != (uint32_t)j && x < a[KE - 1]) {
+#pragma unroll
+                    for (int k = KE - 1; k > 0; --k) a[k] = key_min(a[k], key_max(a[k - 1], x));
+                    a[0] = key_min(a[0], x);
+                }
+            }
+        }
+    };
+    auto run_of = [&](int y, int z, int x0, int x1) {
+        if (y < 0 || y >= ny || z < 0 || z >= nz) return;
+        x0 = max(x0, 0);
+        x1 = min(x1, nx - 1);
+        if (x0 > x1) return;
+        const uint32_t c = ((uint32_t)z * ny + y) * nx;
+        take(starts[c + x0], starts[c + x1 + 1]);
+    };
+    // the 3 x 3 x 3 block, the query's own row first
+    run_of(cy, cz, cx - 1, cx + 1);
+    for (int i = 0; i < 9; ++i)
+        if (i != 4) run_of(cy + i % 3 - 1, cz + i / 3 - 1, cx - 1, cx + 1);
+    const int rmax = max(nx, max(ny, nz));
+    for (int r = 2;; ++r) {
+        // visited: every cell within r - 1; the k-th distance is at most its
+        // rounded key's value and a unit of rounding more
+        const double reach = ((double)(r - 1) + gap) * h;
+        const uint32_t kth = (uint32_t)__double2hiint(a[K - 1]);
+        if (r > rmax ||
+            (kth < kInfBits && (double)__uint_as_float(kth) * (1.0 + 1e-6) <= reach * reach * (1.0 - 1e-12)))
+            break;
+        for (int dz = -r; dz <= r; ++dz)
+            for (int dy = -r; dy <= r; ++dy) {
+                if (dz == -r || dz == r || dy == -r || dy == r) {
+                    run_of(cy + dy, cz + dz, cx - r, cx + r);
+                } else {
+                    run_of(cy + dy, cz + dz, cx - r, cx - r);
+                    run_of(cy + dy, cz + dz, cx + r, cx + r);
+                }
+            }
+    }
+    // exact distances and indices of the list, sorted (they are in the order
+    // of their roundings already, so usually nothing moves)
+    double bd[KE];
+    int bi[KE];
+#pragma unroll
+    for (int k = 0; k < KE; ++k) {
+        const uint32_t t = (uint32_t)__double2loint(a[k]);
+        const bool has = t != 0xffffffffu;
+        const float4 p = sorted[has ? t : (uint32_t)j];
+        bd[k] = has ? sqdist(qx, qy, qz, p.x, p.y, p.z) : INFINITY;
+        bi[k] = has ? __float_as_int(p.w) : 0x7fffffff;
+    }
+    for (bool moved = true; moved;) {
+        moved = false;
+#pragma unroll
+        for (int k = 0; k + 1 < KE; ++k) {
+            const bool sw = bd[k + 1] < bd[k] || (bd[k + 1] == bd[k] && bi[k + 1] < bi[k]);
+            const double d0 = bd[k], d1 = bd[k + 1];
+            const int i0 = bi[k], i1 = bi[k + 1];
+            bd[k] = sw ? d1 : d0;
+            bd[k + 1] = sw ? d0 : d1;
+            bi[k] = sw ? i1 : i0;
+            bi[k + 1] = sw ? i0 : i1;
+            moved |= sw;
+        }
+    }
+    // every point left out rounds to the last key's distance or more
+    if (!(__float_as_uint((float)bd[K - 1]) < (uint32_t)__double2hiint(a[KE - 1]))) {
+        knn_exact<K>(sorted, m, g, starts, qp, nbr, d2out);
+        return;
+    }
+    const int q = __float_as_int(qp.w);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        nbr[(size_t)k * m + q] = bi[k];
+        d2out[(size_t)k * m + q] = bd[k];
+    }
+}
+
 // Workspace of pgs_knn for m points.
 struct KnnWs {
     float* part;
+    GridDesc* desc;
     uint32_t* counts;
     uint32_t* starts;
-    uint32_t* cursor;
     uint32_t* totals;
     uint32_t* cell_of;
+    uint32_t* rank_of;
     float4* sorted;
     size_t bytes;
 };
-
-constexpr uint32_t kGridCells = (uint32_t)kGridMax * kGridMax * kGridMax;
 
 KnnWs knn_layout(void* base, int m) {
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
@@ -291,18 +539,15 @@ KnnWs knn_layout(void* base, int m) {
     char* p = static_cast<char*>(base);
     size_t off = 0;
     w.part = reinterpret_cast<float*>(p + off); off += up((size_t)kBoxBlocks * 6 * 4);
+    w.desc = reinterpret_cast<GridDesc*>(p + off); off += up(sizeof(GridDesc));
     w.counts = reinterpret_cast<uint32_t*>(p + off); off += up((size_t)kGridCells * 4);
     w.starts = reinterpret_cast<uint32_t*>(p + off); off += up(((size_t)kGridCells + 1) * 4);
-    w.cursor = reinterpret_cast<uint32_t*>(p + off); off += up((size_t)kGridCells * 4);
     w.totals = reinterpret_cast<uint32_t*>(p + off); off += up((size_t)(kGridCells / kCellScanItems + 1) * 4);
     w.cell_of = reinterpret_cast<uint32_t*>(p + off); off += up((size_t)m * 4);
+    w.rank_of = reinterpret_cast<uint32_t*>(p + off); off += up((size_t)m * 4);
     w.sorted = reinterpret_cast<float4*>(p + off); off += up((size_t)m * 16);
     w.bytes = off;
     return w;
-}
-
-__global__ void k_clear_cells(uint32_t* __restrict__ p, uint32_t n) {
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0u;
 }
 
 // Eigen-decomposition of a symmetric 3x3 matrix by cyclic Jacobi rotations.
@@ -605,20 +850,19 @@ extern "C" pgs_status pgs_knn(const float* points_dev, int32_t m, int32_t k, int
     PGS_REQUIRE(workspace_bytes >= w.bytes, "pgs_knn: workspace %zu < %zu", workspace_bytes, w.bytes);
     hipStream_t s = pgs::as_stream(stream);
     const int gm = (m + 255) / 256 < 4096 ? (m + 255) / 256 : 4096;
-    k_box_partial<<<kBoxBlocks, 256, 0, s>>>(points_dev, m, w.part);
-    k_clear_cells<<<1024, 256, 0, s>>>(w.counts, kGridCells);
-    k_cell_count<<<gm, 256, 0, s>>>(points_dev, m, w.part, w.counts, w.cell_of);
-    const uint32_t chunks = (kGridCells + kCellScanItems - 1) / kCellScanItems;
-    k_cell_total<<<chunks, 256, 0, s>>>(w.counts, kGridCells, w.totals);
-    k_cell_starts<<<chunks, 256, 0, s>>>(w.counts, kGridCells, w.totals, w.starts, w.cursor);
-    k_cell_end<<<1, 64, 0, s>>>(w.counts, kGridCells, w.starts);
-    k_cell_scatter<<<gm, 256, 0, s>>>(points_dev, m, w.cell_of, w.cursor, w.sorted);
+    k_box_partial<<<kBoxBlocks, 256, 0, s>>>(points_dev, m, w.part, w.counts);
+    k_grid_choose<<<1, kChooseThreads, 0, s>>>(points_dev, m, w.part, w.counts, fmaxf(4.0f, 0.7f * (float)k), w.desc);
+    k_cell_count<<<gm, 256, 0, s>>>(points_dev, m, w.desc, w.counts, w.cell_of, w.rank_of);
+    const uint32_t chunks = kGridCells / kCellScanItems;
+    k_cell_total<<<chunks, 256, 0, s>>>(w.counts, w.desc, w.totals);
+    k_cell_starts<<<chunks, 256, 0, s>>>(w.counts, m, w.desc, w.totals, w.starts);
+    k_cell_scatter<<<gm, 256, 0, s>>>(points_dev, m, w.cell_of, w.rank_of, w.starts, w.sorted);
     const dim3 grid((m + kKnnThreads - 1) / kKnnThreads), block(kKnnThreads);
     switch (k) {
-        case 4: k_knn_grid<4><<<grid, block, 0, s>>>(w.sorted, m, w.part, w.starts, nbr_dev, d2_dev); break;
-        case 8: k_knn_grid<8><<<grid, block, 0, s>>>(w.sorted, m, w.part, w.starts, nbr_dev, d2_dev); break;
-        case 16: k_knn_grid<16><<<grid, block, 0, s>>>(w.sorted, m, w.part, w.starts, nbr_dev, d2_dev); break;
-        default: k_knn_grid<kMaxK><<<grid, block, 0, s>>>(w.sorted, m, w.part, w.starts, nbr_dev, d2_dev); break;
+        case 4: k_knn_grid<4><<<grid, block, 0, s>>>(w.sorted, m, w.desc, w.starts, nbr_dev, d2_dev); break;
+        case 8: k_knn_grid<8><<<grid, block, 0, s>>>(w.sorted, m, w.desc, w.starts, nbr_dev, d2_dev); break;
+        case 16: k_knn_grid<16><<<grid, block, 0, s>>>(w.sorted, m, w.desc, w.starts, nbr_dev, d2_dev); break;
+        default: k_knn_grid<kMaxK><<<grid, block, 0, s>>>(w.sorted, m, w.desc, w.starts, nbr_dev, d2_dev); break;
     }
     PGS_CHECK_LAUNCH("pgs_knn");
     return PGS_OK;

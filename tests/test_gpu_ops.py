@@ -406,3 +406,32 @@ def test_knn_grid_search_cases(case):
     ids, dd = o_seed.knn(pts, q, k)
     np.testing.assert_array_equal(nbr.cpu().numpy()[:, q].T, ids)
     np.testing.assert_array_equal(d2.cpu().numpy()[:, q].T, dd)
+
+
+@pytest.mark.parametrize("k", [4, 8, 16, 32])
+@pytest.mark.parametrize("case", ["fewest", "lattice", "volume", "skewed", "copies", "huge"])
+def test_knn_lists_and_grid_sizes(case, k):
+    # the search's candidate lists against brute force at every list length:
+    # the fewest points, distances tied beyond the list's end (lattice, many
+    # copies of a point), a filled volume (small cells), a dense cluster in a
+    # wide sparse cloud (cell size from the sample), and distances past float32
+    rng = np.random.default_rng(17)
+    if case == "fewest":
+        pts = rng.normal(size=(k + 1, 3)).astype(np.float32)
+    elif case == "lattice":
+        g = np.arange(9, dtype=np.float32) * 0.25
+        pts = np.stack(np.meshgrid(g, g, g, indexing="ij"), -1).reshape(-1, 3)
+    elif case == "volume":
+        pts = rng.uniform(size=(5000, 3)).astype(np.float32)
+    elif case == "skewed":
+        pts = np.r_[rng.normal(size=(3000, 3)) * 0.02, rng.uniform(-3, 3, (500, 3))].astype(np.float32)
+    elif case == "copies":
+        pts = np.repeat(rng.uniform(size=(60, 3)).astype(np.float32), 40, axis=0)
+    else:
+        pts = (rng.normal(size=(300, 3)) * 1e25).astype(np.float32)
+    _, nbr, d2 = _knn_gpu(pts, k)
+    torch.cuda.synchronize()
+    q = list(range(0, len(pts), max(1, len(pts) // 60)))
+    ids, dd = o_seed.knn(pts, q, k)
+    np.testing.assert_array_equal(nbr.cpu().numpy()[:, q].T, ids)
+    np.testing.assert_array_equal(d2.cpu().numpy()[:, q].T, dd)
