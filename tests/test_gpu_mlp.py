@@ -95,6 +95,22 @@ def test_mlp_forward_full_size_sampled_rows():
     _compare_net(got[rows], want, "y sampled", outputs=True)
 
 
+@pytest.mark.parametrize("m", [15, 16, 17, 49, 32769])
+def test_mlp_row_tiles_and_wide_activations(m):
+    # the forward's 16-row tiles at their edges and past one round of its
+    # blocks; weights large enough that the pre-activations reach both
+    # saturated ends of GELU, in the forward and in the weight gradients
+    w = synth.random_normal(36, mlp.N_WEIGHTS, 0.5)
+    X = synth.random_normal(37 + m, (m, 64))
+    rows = np.unique(np.r_[np.arange(min(m, 64)), m - 1])
+    want, _ = mlp.forward(w, X[rows], emulate=True)
+    _compare_net(_gpu_forward(w, X)[rows], want, f"y m={m}")
+    if m <= 64:
+        dY = synth.random_normal(38 + m, (m, 8))
+        _, cache = mlp.forward(w, X, emulate=True)
+        assert_block_close(_gpu_backward(w, X, dY), mlp.backward(w, cache, dY, emulate=True), MLP_TOL, what="dw")
+
+
 def _split(g):
     out, off = [], 0
     for s in mlp.SHAPES:
