@@ -240,3 +240,18 @@ def test_full_size_pipeline():
         np.testing.assert_array_equal(depth[i] > 0, d > 0)
         np.testing.assert_allclose(depth[i], d, rtol=1e-6, atol=0)
         say(f"[mvs full] target {t}: kept {(d > 0).mean():.3f}")
+
+
+@pytest.mark.parametrize("W,H,D,other", [(65, 41, 64, 30), (50, 33, 192, 30), (43, 40, 128, 15), (33, 29, 256, 15)])
+def test_cost_with_planes_behind_the_reference(W, H, D, other):
+    # the reference looks back at the target (or across its view), so the far
+    # planes lie behind it, some within a hair of its centre's plane: cells
+    # in front take the shared-reciprocal quotients, their wave's others the
+    # true divisions; ragged sizes leave the last workgroup part full
+    _, cams, g, _, _ = _views(W, H, [0, other])
+    cams = [cams[0], cams[other]]
+    lo, hi = 1.0, 14.0
+    cost, _, _, _ = _gpu_depth(cams, g, [0], [1, 0], np.array([[lo, hi], [0.0, 0.0]]), _params(D), want_agg=False)
+    C, marg = omvs.cost_volume(omvs.census(g[0]), omvs.census(g[1]), cams[0], cams[1], lo, hi, D, with_margin=True)
+    _assert_cost_close(cost[0], C, marg, f"reference {other}")
+    assert (C == omvs.COST_OUT).any() and (C != omvs.COST_OUT).any()
