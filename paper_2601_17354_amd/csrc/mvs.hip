@@ -17,15 +17,14 @@
 //       reference view from float32 arithmetic in a fixed order without
 //       contraction (the nearest-pixel decision is reproducible), Hamming
 //       distance of the Census strings; cost volume [y][x][plane] bytes;
-//   k_sgm<KPL, COLS>  one wave per image line sweeps it forward (path costs
-//       stored as bytes) and back: lane l holds the KPL consecutive planes
-//       KPL l .. (one load per step of each operand, prefetched 8 steps
-//       ahead); per step the previous costs' minimum is a DPP wave reduction
-//       and the neighbouring planes come from DPP wave shifts.  The row
-//       kernel writes the two row paths' sum; the column kernel adds both
-//       column paths to it, stages the totals of 32 steps in an LDS ring and
-//       lets two lanes per pixel take the winner, the confidence test and the refined
-//       depth of one of those pixels, without storing the total;
+//   k_sgm_*<D>    semi-global aggregation, four image lines per wave: 16 lanes
+//       hold a line's D planes two to a register (packed 16-bit arithmetic),
+//       the least path cost is four rotations of the 16 lanes.  k_sgm_rows
+//       sums both row directions, k_sgm_cols adds both column directions and
+//       takes winner, confidence test and refined depth; path costs are
+//       recomputed from checkpoints instead of stored.  k_sgm_paths stores
+//       three directions side by side where few lines would leave the chip
+//       idle;
 //   k_fuse_*      per-row counts, one scan over rows and the back-projection
 //       of the kept pixels in row-major order.
 
@@ -437,36 +436,13 @@ void launch_cost(dim3 grid, hipStream_t s, const pgs_camera* cams, int W, int H,
 
 // ---------------------------------------------------------------- SGM
 
-constexpr int kIntMax = 0x7fffffff;
-
-// Minimum over the wave, returned to every lane: an inclusive min-scan
-// inside each row of 16 lanes (DPP row shifts), folded across rows with
-// row broadcasts (lane 63 ends with the total), then read from lane 63.
-__device__ __forceinline__ int wave_min_all(int v) {
-    v = min(v, __builtin_amdgcn_update_dpp(kIntMax, v, 0x111, 0xf, 0xf, false));
-    v = min(v, __builtin_amdgcn_update_dpp(kIntMax, v, 0x112, 0xf, 0xf, false));
-    v = min(v, __builtin_amdgcn_update_dpp(kIntMax, v, 0x114, 0xf, 0xf, false));
-    v = min(v, __builtin_amdgcn_update_dpp(kIntMax, v, 0x118, 0xf, 0xf, false));
-    v = min(v, __builtin_amdgcn_update_dpp(kIntMax, v, 0x142, 0xa, 0xf, false));
-    v = min(v, __builtin_amdgcn_update_dpp(kIntMax, v, 0x143, 0xc, 0xf, false));
-    return __builtin_amdgcn_readlane(v, 63);
-}
-
-// Value of lane l - 1 (wave shift right by one), `edge` in lane 0.
-__device__ __forceinline__ int from_lower_lane(int v, int edge) {
-    return __builtin_amdgcn_update_dpp(edge, v, 0x138, 0xf, 0xf, false);
-}
-
-// Value of lane l + 1 (wave shift left by one), `edge` in lane 63.
-__device__ __forceinline__ int from_upper_lane(int v, int edge) {
-    return __builtin_amdgcn_update_dpp(edge, v, 0x130, 0xf, 0xf, false);
-}
-
 struct SgmArgs {
     const uint8_t* cost;
-    uint8_t* lbuf;       // forward path costs of the line being swept [T][H][W][D]
-    uint16_t* agg;       // path-cost sum [T][H][W][D]
-    bool agg_total;      // the last pass also stores the full sum
+    // workspace, e = T H W D bytes each: [0] checkpoints (sweeps of whole lines)
+    // or left-to-right path costs, [1] row sums or right-to-left, [2]
+    // top-to-bottom
+    uint8_t* buf[3];
+    uint16_t* agg_out;   // the full sums, if wanted
     const int32_t* targets;
     const double* range;
     float* depth;        // [T][H][W]
@@ -475,164 +451,377 @@ struct SgmArgs {
     double keep_ratio;   // 1 - confidence threshold
 };
 
-// Lane l holds planes KPL l .. KPL l + KPL - 1 of a pixel: its costs are KPL
-// consecutive bytes and its sums KPL consecutive uint16, loaded as one word
-// where KPL allows and kept packed until used.
-template <int KPL> struct SumWord { typedef uint64_t type; };
-template <> struct SumWord<1> { typedef uint32_t type; };
-template <> struct SumWord<2> { typedef uint32_t type; };
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
-template <int KPL>
-struct LanePack {
-    typedef typename SumWord<KPL>::type G;
-    __device__ static void load(const uint8_t* c, const uint16_t* g, bool with_g, uint32_t& cw, G& gw) {
-        if (KPL == 2) {
-            cw = *reinterpret_cast<const uint16_t*>(c);
-            gw = with_g ? *reinterpret_cast<const uint32_t*>(g) : 0u;
-        } else if (KPL == 4) {
-            cw = *reinterpret_cast<const uint32_t*>(c);
-            gw = with_g ? (G)*reinterpret_cast<const uint64_t*>(g) : (G)0;
+template <bool V>
+struct Const {
+    constexpr operator bool() const { return V; }
+};
+
+__device__ __forceinline__ u16x2 pair_of(uint32_t v) { return __builtin_bit_cast(u16x2, v); }
+__device__ __forceinline__ uint32_t word_of(u16x2 v) { return __builtin_bit_cast(uint32_t, v); }
+__device__ __forceinline__ u16x2 splat(uint32_t v) { return pair_of(v | (v << 16)); }
+
+// A wave sweeps four image lines at once, one per row of 16 lanes: lane i of
+// a row holds the PL = D / 16 consecutive planes PL i .. of its line's pixel
+// as NR registers of two 16-bit values (packed 16-bit arithmetic: two planes
+// an instruction; the row minimum is four rotations inside the 16 lanes).
+// A pixel's costs and path costs are NB words of bytes per lane.  kSeg
+// steps are held in registers at a time.
+template <int D>
+struct Sweep {
+    static constexpr int PL = D / 16, NR = PL / 2, NB = PL / 4;
+    static constexpr int kSeg = D <= 128 ? 16 : 8;
+    struct Bytes {
+        uint32_t w[NB];
+    };
+    // no alignment beyond a byte's is asked of the cost volume
+    typedef uint32_t Any __attribute__((ext_vector_type(NB == 1 ? 2 : NB), aligned(1)));
+
+    __device__ static __forceinline__ Bytes load(const uint8_t* p) {
+        Bytes b;
+        if constexpr (NB == 1) {
+            typedef uint32_t One __attribute__((aligned(1)));
+            b.w[0] = *reinterpret_cast<const One*>(p);
         } else {
-            cw = 0;
-            gw = 0;
+            const Any v = *reinterpret_cast<const Any*>(p);
 #pragma unroll
-            for (int j = 0; j < KPL; ++j) {
-                cw |= (uint32_t)c[j] << (8 * j);
-                if (with_g) gw |= (G)g[j] << (16 * j);
-            }
+            for (int k = 0; k < NB; ++k) b.w[k] = v[k];
+        }
+        return b;
+    }
+    __device__ static __forceinline__ void store(uint8_t* p, const Bytes& b) {
+        if constexpr (NB == 1) {
+            typedef uint32_t One __attribute__((aligned(1)));
+            *reinterpret_cast<One*>(p) = b.w[0];
+        } else {
+            Any v;
+#pragma unroll
+            for (int k = 0; k < NB; ++k) v[k] = b.w[k];
+            *reinterpret_cast<Any*>(p) = v;
         }
     }
-    __device__ static uint32_t load_bytes(const uint8_t* c) {
-        if (KPL == 2) return *reinterpret_cast<const uint16_t*>(c);
-        if (KPL == 4) return *reinterpret_cast<const uint32_t*>(c);
-        uint32_t w = 0;
-#pragma unroll
-        for (int j = 0; j < KPL; ++j) w |= (uint32_t)c[j] << (8 * j);
-        return w;
+    // planes 2 i and 2 i + 1 of packed bytes, as a pair
+    __device__ static __forceinline__ u16x2 pair(const Bytes& b, int i) {
+        return pair_of(__builtin_amdgcn_perm(0u, b.w[i >> 1], (i & 1) ? 0x0c030c02u : 0x0c010c00u));
     }
-    __device__ static void store_bytes(uint8_t* c, const int (&v)[KPL]) {
-        if (KPL == 2) {
-            *reinterpret_cast<uint16_t*>(c) = (uint16_t)((uint32_t)v[0] | ((uint32_t)v[1] << 8));
-        } else if (KPL == 4) {
-            *reinterpret_cast<uint32_t*>(c) =
-                (uint32_t)v[0] | ((uint32_t)v[1] << 8) | ((uint32_t)v[2] << 16) | ((uint32_t)v[3] << 24);
-        } else {
+    __device__ static __forceinline__ Bytes bytes(const u16x2 (&v)[NR]) {
+        Bytes b;
 #pragma unroll
-            for (int j = 0; j < KPL; ++j) c[j] = (uint8_t)v[j];
-        }
-    }
-    __device__ static G load_sums(const uint16_t* g) {
-        if (KPL == 2) return *reinterpret_cast<const uint32_t*>(g);
-        if (KPL == 4) return (G)*reinterpret_cast<const uint64_t*>(g);
-        G w = 0;
-#pragma unroll
-        for (int j = 0; j < KPL; ++j) w |= (G)g[j] << (16 * j);
-        return w;
-    }
-    __device__ static int cost(uint32_t cw, int j) { return (int)((cw >> (8 * j)) & 255u); }
-    __device__ static int sum(G gw, int j) { return (int)((gw >> (16 * j)) & 0xffffu); }
-    __device__ static void store(uint16_t* g, const int (&v)[KPL]) {
-        if (KPL == 2) {
-            *reinterpret_cast<uint32_t*>(g) = (uint32_t)v[0] | ((uint32_t)v[1] << 16);
-        } else if (KPL == 4) {
-            *reinterpret_cast<uint64_t*>(g) = (uint64_t)(uint32_t)v[0] | ((uint64_t)(uint32_t)v[1] << 16) |
-                                              ((uint64_t)(uint32_t)v[2] << 32) | ((uint64_t)(uint32_t)v[3] << 48);
-        } else {
-#pragma unroll
-            for (int j = 0; j < KPL; ++j) g[j] = (uint16_t)v[j];
-        }
+        for (int k = 0; k < NB; ++k) b.w[k] = __builtin_amdgcn_perm(word_of(v[2 * k + 1]), word_of(v[2 * k]), 0x06040200u);
+        return b;
     }
 };
 
-// One sweep of a wave along its line.  kForward: path costs to lbuf (bytes,
-// every value <= 48 + p2 <= 255 is checked on the host); kRowsBack: the
-// opposite direction, the two rows' path costs summed into agg; kColsBack:
-// the opposite column direction added to the row sum and lbuf's forward
-// column costs, then per pixel the winner and the confidence-test sums
-// (recorded in lane step mod 64 and turned into refined depths 64 pixels
-// at a time).
-enum SweepMode { kForward = 0, kRowsBack = 1, kColsBack = 2 };
-constexpr int kSgmRing = 32;  // column steps staged in LDS per wave
+// Minimum over a row's 16 lanes of both halves of v, in both halves of every
+// lane.
+__device__ __forceinline__ u16x2 row_min(u16x2 v) {
+    v = __builtin_elementwise_min(v, __builtin_shufflevector(v, v, 1, 0));
+    uint32_t w = word_of(v);  // equal halves: the words order like them
+    w = min(w, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x128, 0xf, 0xf, true));
+    w = min(w, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x124, 0xf, 0xf, true));
+    w = min(w, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x122, 0xf, 0xf, true));
+    w = min(w, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x121, 0xf, 0xf, true));
+    return pair_of(w);
+}
 
-template <int KPL, int MODE>
-__device__ __forceinline__ void sgm_sweep(const SgmArgs& a, int line, int ti, bool rows, bool rev,
-                                          uint16_t* ring) {
-#pragma clang fp contract(off)
-    constexpr int D = 64 * KPL;
-    constexpr int kBig = 1 << 28;
-    constexpr int PF = 8;
-    typedef LanePack<KPL> LP;
-    typedef typename LP::G G;
-    const int lane = threadIdx.x & 63;
-    const int n = rows ? a.W : a.H;
-    const size_t npix = (size_t)a.W * a.H;
-    const long long p0 = rows ? (long long)line * a.W + (rev ? a.W - 1 : 0)
-                              : (long long)(rev ? a.H - 1 : 0) * a.W + line;
-    const long long dp = rows ? (rev ? -1 : 1) : (rev ? -(long long)a.W : (long long)a.W);
-    const size_t off = (size_t)ti * npix * D + KPL * lane;
-    const uint8_t* cbase = a.cost + off;
-    uint8_t* lbase = a.lbuf + off;
-    uint16_t* abase = a.agg + off;
-    double inv_far = 0.0, h = 0.0;
-    if (MODE == kColsBack) {
-        const int tv = a.targets[ti];
-        const double d_min = a.range[2 * tv], d_max = a.range[2 * tv + 1];
-        inv_far = 1.0 / d_max;
-        h = (1.0 / d_min - inv_far) / (double)(D - 1);
+template <int NR>
+__device__ __forceinline__ u16x2 least(const u16x2 (&v)[NR]) {
+    u16x2 m = v[0];
+#pragma unroll
+    for (int i = 1; i < NR; ++i) m = __builtin_elementwise_min(m, v[i]);
+    return row_min(m);
+}
+
+// One step of a path: L(k) = C(k) + min(L(k), L(k +- 1) + P1, m + P2) - m with
+// m the least L, over the previous pixel's L; as every L is at least m, the
+// minimum less m is min(min(L(k), L(k +- 1) + P1) - m, P2).  A path starts from
+// L = 0, which gives its first pixel's costs.
+template <int D>
+__device__ __forceinline__ void path_step(u16x2 (&L)[Sweep<D>::NR], const typename Sweep<D>::Bytes& c, u16x2 p1,
+                                          u16x2 p2) {
+    constexpr int NR = Sweep<D>::NR;
+    constexpr int kNone = 0x7fff7fff;  // beyond the first and the last plane
+    const u16x2 m = least<NR>(L);
+    const uint32_t below = (uint32_t)__builtin_amdgcn_update_dpp(kNone, (int)word_of(L[NR - 1]), 0x111, 0xf, 0xf, false);
+    const uint32_t above = (uint32_t)__builtin_amdgcn_update_dpp(kNone, (int)word_of(L[0]), 0x101, 0xf, 0xf, false);
+    // s[i] = (plane 2 i - 1, plane 2 i): the planes below those of register i,
+    // and above those of register i - 1
+    u16x2 s[NR + 1];
+    s[0] = pair_of(__builtin_amdgcn_alignbit(word_of(L[0]), below, 16));
+#pragma unroll
+    for (int i = 1; i < NR; ++i) s[i] = pair_of(__builtin_amdgcn_alignbit(word_of(L[i]), word_of(L[i - 1]), 16));
+    s[NR] = pair_of(__builtin_amdgcn_alignbit(above, word_of(L[NR - 1]), 16));
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        const u16x2 side = __builtin_elementwise_min(s[i], s[i + 1]) + p1;
+        const u16x2 best = __builtin_elementwise_min(__builtin_elementwise_min(L[i], side) - m, p2);
+        L[i] = Sweep<D>::pair(c, i) + best;
     }
-    int L[KPL];
-    uint32_t cc[PF], cn[PF], fc[PF], fn[PF];
-    G ac[PF], an[PF];
-    auto load = [&](int s, uint32_t& c, uint32_t& f, G& g) {
-        if (s < n) {
-            const size_t e = (size_t)(p0 + dp * s) * D;
-            c = LP::load_bytes(cbase + e);
-            if (MODE != kForward) f = LP::load_bytes(lbase + e);
-            if (MODE == kColsBack) g = LP::load_sums(abase + e);
+}
+
+// Where a wave's lines lie: line l of a target starts at pixel l (columns) or
+// l W (rows) and steps by W or 1.  Lines past the last repeat it: they store
+// the same bytes again, so no store is masked and the sweeps' loops know how
+// many are in flight when they wait for their loads.
+struct Lines {
+    size_t first;    // byte of this lane's planes at step 0
+    size_t step;     // bytes from a step to the next
+    int n, line;     // steps, this lane's line
+    bool live;
+    __device__ __forceinline__ size_t at(int s) const { return first + (size_t)s * step; }
+};
+
+template <int D>
+__device__ __forceinline__ Lines lines_of(const SgmArgs& a, bool rows, int wave, int ti) {
+    const int lane = threadIdx.x & 63, count = rows ? a.H : a.W;
+    Lines q;
+    q.n = rows ? a.W : a.H;
+    q.line = 4 * wave + (lane >> 4);
+    q.live = q.line < count;
+    q.line = min(q.line, count - 1);
+    const size_t pix = (size_t)ti * a.W * a.H + (rows ? (size_t)q.line * a.W : (size_t)q.line);
+    q.first = pix * D + (lane & 15) * Sweep<D>::PL;
+    q.step = rows ? (size_t)D : (size_t)a.W * D;
+    return q;
+}
+
+template <int D>
+__device__ __forceinline__ void load_seg(const uint8_t* base, const Lines& q, int seg,
+                                         typename Sweep<D>::Bytes (&v)[Sweep<D>::kSeg]) {
+    constexpr int S = Sweep<D>::kSeg;
+#pragma unroll
+    for (int s = 0; s < S; ++s) v[s] = Sweep<D>::load(base + q.at(min(max(seg, 0) * S + s, q.n - 1)));
+}
+
+// Forward sweep of whole segments 0 .. nseg - 2 that keeps only the state
+// before each segment from 1 on (checkpoints, one per kSeg steps).
+template <int D>
+__device__ __forceinline__ void checkpoint_sweep(const uint8_t* cost, uint8_t* ck, const Lines& q, u16x2 p1, u16x2 p2) {
+    typedef Sweep<D> SW;
+    constexpr int S = SW::kSeg, NR = SW::NR;
+    const int nseg = (q.n + S - 1) / S;
+    u16x2 L[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) L[i] = splat(0u);
+    typename SW::Bytes c[S], cn[S];
+    load_seg<D>(cost, q, 0, c);
+    for (int seg = 0; seg + 1 < nseg; ++seg) {
+        load_seg<D>(cost, q, seg + 1, cn);
+#pragma unroll
+        for (int s = 0; s < S; ++s) path_step<D>(L, c[s], p1, p2);
+        SW::store(ck + q.at((seg + 1) * S), SW::bytes(L));
+#pragma unroll
+        for (int s = 0; s < S; ++s) c[s] = cn[s];
+    }
+}
+
+// A segment's forward path costs again, from its checkpoint.
+template <int D>
+__device__ __forceinline__ void recompute(const typename Sweep<D>::Bytes& ck, bool first,
+                                          const typename Sweep<D>::Bytes (&c)[Sweep<D>::kSeg],
+                                          typename Sweep<D>::Bytes (&f)[Sweep<D>::kSeg], u16x2 p1, u16x2 p2) {
+    typedef Sweep<D> SW;
+    u16x2 L[SW::NR];
+#pragma unroll
+    for (int i = 0; i < SW::NR; ++i) L[i] = first ? splat(0u) : SW::pair(ck, i);
+#pragma unroll
+    for (int s = 0; s < SW::kSeg; ++s) {
+        path_step<D>(L, c[s], p1, p2);
+        f[s] = SW::bytes(L);
+    }
+}
+
+// Both row directions of four rows.  The forward path costs are not stored:
+// the forward sweep leaves a checkpoint per segment, and the backward sweep
+// recomputes a segment's forward path before walking it back, both from the
+// segment's costs in registers.  Per cell the costs are read twice and one
+// byte of sum is written (2 (48 + P2) <= 255), where storing the path costs
+// and 16-bit sums moved six bytes.
+template <int D>
+__global__ __launch_bounds__(64) void k_sgm_rows(SgmArgs a) {
+    typedef Sweep<D> SW;
+    constexpr int S = SW::kSeg, NR = SW::NR, NB = SW::NB;
+    const Lines q = lines_of<D>(a, true, blockIdx.x, blockIdx.y);
+    const u16x2 p1 = splat((uint32_t)a.p1), p2 = splat((uint32_t)a.p2);
+    checkpoint_sweep<D>(a.cost, a.buf[0], q, p1, p2);
+    u16x2 L[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) L[i] = splat(0u);
+    const int nseg = (q.n + S - 1) / S;
+    typename SW::Bytes c[S], cn[S], f[S], ck, ckn;
+    load_seg<D>(a.cost, q, nseg - 1, c);
+    ck = SW::load(a.buf[0] + q.at((nseg - 1) * S));
+    auto back = [&](int seg, auto whole) {
+        load_seg<D>(a.cost, q, seg - 1, cn);
+        ckn = SW::load(a.buf[0] + q.at(max(seg - 1, 0) * S));
+        recompute<D>(ck, seg == 0, c, f, p1, p2);
+#pragma unroll
+        for (int s = S - 1; s >= 0; --s) {
+            const int x = seg * S + s;
+            if (whole || x < q.n) {
+                path_step<D>(L, c[s], p1, p2);
+                typename SW::Bytes b = SW::bytes(L);
+#pragma unroll
+                for (int k = 0; k < NB; ++k) b.w[k] += f[s].w[k];  // four sums of bytes, none past 255
+                SW::store(a.buf[1] + q.at(x), b);
+            }
         }
+#pragma unroll
+        for (int s = 0; s < S; ++s) c[s] = cn[s];
+        ck = ckn;
     };
-    // column back sweep: the full sums of kSgmRing consecutive steps sit in
-    // this wave's LDS ring (row = step mod kSgmRing, D + 2 uint16 per row so
-    // that the lanes' rows fall in different banks); lanes p and p + 32 then
-    // take the winner, the second minimum two planes away and the winner's
-    // neighbours of step p over one half of the planes each, combined by a
-    // lane swap, and lane p writes that pixel's depth and confidence
-    constexpr int RS = D + 2;
-    constexpr int RING = kSgmRing;
-    auto flush = [&](int s_first, int count) {
+    // only the last segment may be short
+    if (q.n % S) back(nseg - 1, Const<false>());
+    for (int seg = q.n / S - 1; seg >= 0; --seg) back(seg, Const<true>());
+}
+
+// One direction of four lines, its path costs stored: blocks of the grid take
+// left to right, right to left and top to bottom side by side.
+template <int D>
+__global__ __launch_bounds__(64) void k_sgm_paths(SgmArgs a, int row_waves) {
+    typedef Sweep<D> SW;
+    constexpr int S = SW::kSeg, NR = SW::NR;
+    const int dir = (int)blockIdx.x < row_waves ? 0 : (int)blockIdx.x < 2 * row_waves ? 1 : 2;
+    const Lines q = lines_of<D>(a, dir < 2, (int)blockIdx.x - dir * row_waves, blockIdx.y);
+    const u16x2 p1 = splat((uint32_t)a.p1), p2 = splat((uint32_t)a.p2);
+    uint8_t* out = a.buf[dir];
+    // step s of a backward path is pixel n - 1 - s
+    Lines w = q;
+    if (dir == 1) {
+        w.first = q.at(q.n - 1);
+        w.step = (size_t)0 - q.step;
+    }
+    u16x2 L[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) L[i] = splat(0u);
+    typename SW::Bytes c[S], cn[S];
+    load_seg<D>(a.cost, w, 0, c);
+    auto ahead = [&](int seg, auto whole) {
+        load_seg<D>(a.cost, w, seg + 1, cn);
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const int x = seg * S + s;
+            if (whole || x < q.n) {
+                path_step<D>(L, c[s], p1, p2);
+                SW::store(out + w.at(x), SW::bytes(L));
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < S; ++s) c[s] = cn[s];
+    };
+    for (int seg = 0; seg < q.n / S; ++seg) ahead(seg, Const<true>());
+    if (q.n % S) ahead(q.n / S, Const<false>());
+}
+
+// Bottom to top over four columns, added to the other three paths, and each
+// pixel's winner.  STAGED: the three are read (buf 0, 1, 2); else the row
+// sums are read (buf 1) and top to bottom is swept here first, recomputed by
+// segment as in k_sgm_rows.  Per step and row of lanes: the least sum and the
+// smallest plane that has it (FUSED, where sum and plane fit 16 bits: one
+// minimum of D sum + plane; else one of the sums and one of
+// 256 [sum > least] + plane), then the least sum two or more planes away
+// (excluded planes raised past every sum); lane s of the row keeps step s,
+// and at the segment's end every lane finishes one pixel, taking the winner's
+// two neighbours from the segment's sums in LDS.  AGG also stores the sums.
+template <int D, bool STAGED, bool FUSED, bool AGG>
+__global__ __launch_bounds__(64) void k_sgm_cols(SgmArgs a) {
+#pragma clang fp contract(off)
+    typedef Sweep<D> SW;
+    constexpr int S = SW::kSeg, NR = SW::NR;
+    __shared__ __align__(16) uint32_t sums[S][4][D / 2];
+    const int lane = threadIdx.x & 63, li = lane & 15, row = lane >> 4, ti = blockIdx.y;
+    const Lines q = lines_of<D>(a, false, blockIdx.x, ti);
+    const u16x2 p1 = splat((uint32_t)a.p1), p2 = splat((uint32_t)a.p2);
+    if (!STAGED) checkpoint_sweep<D>(a.cost, a.buf[0], q, p1, p2);
+    const int tv = a.targets[ti];
+    const double d_min = a.range[2 * tv], d_max = a.range[2 * tv + 1];
+    const double inv_far = 1.0 / d_max, h = (1.0 / d_min - inv_far) / (double)(D - 1);
+    u16x2 L[NR], plane[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        L[i] = splat(0u);
+        const uint32_t k = (uint32_t)(li * SW::PL + 2 * i);
+        plane[i] = pair_of(k | ((k + 1u) << 16));
+    }
+    const int nseg = (q.n + S - 1) / S;
+    typename SW::Bytes c[S], cn[S], r[S], rn[S], f[S], fn[S], ck, ckn;
+    typename SW::Bytes r2[STAGED ? S : 1], r2n[STAGED ? S : 1];
+    auto fetch = [&](int seg, typename SW::Bytes (&cc)[S], typename SW::Bytes (&rr)[S]) {
+        load_seg<D>(a.cost, q, seg, cc);
+        load_seg<D>(a.buf[1], q, seg, rr);
+    };
+    fetch(nseg - 1, c, r);
+    if constexpr (STAGED) {
+        load_seg<D>(a.buf[2], q, nseg - 1, f);
+        load_seg<D>(a.buf[0], q, nseg - 1, r2);
+    } else {
+        ck = SW::load(a.buf[0] + q.at((nseg - 1) * S));
+    }
+    auto back = [&](int seg, auto whole) {
+        fetch(seg - 1, cn, rn);
+        if constexpr (STAGED) {
+            load_seg<D>(a.buf[2], q, seg - 1, fn);
+            load_seg<D>(a.buf[0], q, seg - 1, r2n);
+        } else {
+            ckn = SW::load(a.buf[0] + q.at(max(seg - 1, 0) * S));
+            recompute<D>(ck, seg == 0, c, f, p1, p2);
+        }
+        uint32_t my_sums = 0, my_plane = 0;  // (second << 16 | least), winner of step li
+#pragma unroll
+        for (int s = S - 1; s >= 0; --s) {
+            const int y = seg * S + s;
+            if (whole || y < q.n) {
+                path_step<D>(L, c[s], p1, p2);
+                u16x2 T[NR];
+#pragma unroll
+                for (int i = 0; i < NR; ++i) {
+                    T[i] = L[i] + SW::pair(f[s], i) + SW::pair(r[s], i);
+                    if constexpr (STAGED) T[i] += SW::pair(r2[s], i);
+                }
+                if constexpr (AGG) {
+                    typedef uint32_t Half __attribute__((aligned(2)));
+                    Half* o = reinterpret_cast<Half*>(a.agg_out + q.at(y));
+#pragma unroll
+                    for (int i = 0; i < NR; ++i) o[i] = word_of(T[i]);
+                }
+#pragma unroll
+                for (int i = 0; i < NR; ++i) sums[s][row][li * NR + i] = word_of(T[i]);
+                u16x2 v[NR], s1, kw;
+                if constexpr (FUSED) {
+#pragma unroll
+                    for (int i = 0; i < NR; ++i) v[i] = T[i] * splat(D) + plane[i];
+                    const u16x2 key = least<NR>(v);
+                    s1 = key / splat(D);
+                    kw = key & splat(D - 1);
+                } else {
+                    s1 = least<NR>(T);
+#pragma unroll
+                    for (int i = 0; i < NR; ++i)  // 256 less where the sum is the least
+                        v[i] = __builtin_elementwise_sub_sat(splat(1u), T[i] - s1) * splat(0xff00u) +
+                               (plane[i] + splat(256u));
+                    kw = least<NR>(v);
+                }
+#pragma unroll
+                for (int i = 0; i < NR; ++i) {
+                    // 0, 1, 2 for the planes next to and at the winner
+                    const u16x2 e = plane[i] + splat(1u) - kw;
+                    v[i] = __builtin_elementwise_sub_sat(splat(3u), e) * splat(0x4000u) + T[i];
+                }
+                const u16x2 s2 = least<NR>(v);
+                const uint32_t both = __builtin_amdgcn_perm(word_of(s2), word_of(s1), 0x05040100u);
+                my_sums = li == s ? both : my_sums;
+                my_plane = li == s ? word_of(kw) & 0xffffu : my_plane;
+            }
+        }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        // lanes p and p + 32 take step p, each over half of the planes
-        const int px = lane & 31, half = lane >> 5;
-        const bool act = px < count;
-        const uint32_t* r = reinterpret_cast<const uint32_t*>(ring + px * RS) + half * (D / 4);
-        const int k0 = half * (D / 2);
-        int key = kBig;  // (sum << 8) | plane, smallest first
-        if (act) {
-#pragma unroll 4
-            for (int c = 0; c < D / 4; ++c) {
-                const uint32_t w = r[c];
-                key = min(key, (int)((w & 0xffffu) << 8) | (k0 + 2 * c));
-                key = min(key, (int)((w >> 16) << 8) | (k0 + 2 * c + 1));
-            }
-        }
-        key = min(key, __shfl_xor(key, 32));
-        const int s1 = key >> 8, kw = key & 255;
-        int s2 = kBig;
-        if (act) {
-#pragma unroll 4
-            for (int c = 0; c < D / 4; ++c) {
-                const uint32_t w = r[c];
-                const int ka = k0 + 2 * c, kb = ka + 1;
-                if (ka - kw >= 2 || kw - ka >= 2) s2 = min(s2, (int)(w & 0xffffu));
-                if (kb - kw >= 2 || kw - kb >= 2) s2 = min(s2, (int)(w >> 16));
-            }
-        }
-        s2 = min(s2, __shfl_xor(s2, 32));
-        if (act && half == 0) {
-            const uint16_t* rh = ring + px * RS;
-            const int vm = rh[kw > 0 ? kw - 1 : 0], vq = rh[kw < D - 1 ? kw + 1 : D - 1];
+        const int y = seg * S + li;
+        if (li < S && y < q.n && q.live) {
+            const int s1 = (int)(my_sums & 0xffffu), s2 = (int)(my_sums >> 16), kw = (int)my_plane;
+            const uint16_t* t = reinterpret_cast<const uint16_t*>(sums[li][row]);
+            const int vm = t[kw > 0 ? kw - 1 : 0], vq = t[kw < D - 1 ? kw + 1 : D - 1];
             const bool keep = kw > 0 && kw < D - 1 && s2 > 0 && (double)s1 <= a.keep_ratio * (double)s2;
             float dout = 0.0f;
             if (keep) {
@@ -640,95 +829,28 @@ __device__ __forceinline__ void sgm_sweep(const SgmArgs& a, int line, int ti, bo
                 const double delta = den > 0 ? (double)(vm - vq) / (2.0 * (double)den) : 0.0;
                 dout = (float)(1.0 / (inv_far + ((double)kw + delta) * h));
             }
-            const size_t o = (size_t)ti * npix + (size_t)(p0 + dp * (s_first + px));
+            const size_t o = ((size_t)ti * a.H + y) * a.W + q.line;
             a.depth[o] = dout;
             a.conf[o] = s2 > 0 ? (float)(1.0 - (double)s1 / (double)s2) : 0.0f;
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            c[s] = cn[s];
+            r[s] = rn[s];
+            if constexpr (STAGED) {
+                f[s] = fn[s];
+                r2[s] = r2n[s];
+            }
+        }
+        ck = ckn;
     };
-#pragma unroll
-    for (int q = 0; q < PF; ++q) load(q, cc[q], fc[q], ac[q]);
-    for (int s0 = 0; s0 < n; s0 += PF) {
-#pragma unroll
-        for (int q = 0; q < PF; ++q) load(s0 + PF + q, cn[q], fn[q], an[q]);
-#pragma unroll
-        for (int q = 0; q < PF; ++q) {
-            const int s = s0 + q;
-            if (s >= n) break;
-            if (s == 0) {
-#pragma unroll
-                for (int j = 0; j < KPL; ++j) L[j] = LP::cost(cc[q], j);
-            } else {
-                int m = L[0];
-#pragma unroll
-                for (int j = 1; j < KPL; ++j) m = min(m, L[j]);
-                m = wave_min_all(m);
-                // plane k - 1 of the lane's first plane is the previous
-                // lane's last; k + 1 of its last is the next lane's first
-                const int below = from_lower_lane(L[KPL - 1], kBig);
-                const int above = from_upper_lane(L[0], kBig);
-                int Ln[KPL];
-#pragma unroll
-                for (int j = 0; j < KPL; ++j) {
-                    const int km1 = j > 0 ? L[j - 1] : below;
-                    const int kp1 = j + 1 < KPL ? L[j + 1] : above;
-                    const int best = min(min(L[j], km1 + a.p1), min(kp1 + a.p1, m + a.p2));
-                    Ln[j] = LP::cost(cc[q], j) + best - m;
-                }
-#pragma unroll
-                for (int j = 0; j < KPL; ++j) L[j] = Ln[j];
-            }
-            const size_t e = (size_t)(p0 + dp * s) * D;
-            if (MODE == kForward) {
-                LP::store_bytes(lbase + e, L);
-            } else if (MODE == kRowsBack) {
-                int S[KPL];
-#pragma unroll
-                for (int j = 0; j < KPL; ++j) S[j] = LP::cost(fc[q], j) + L[j];
-                LP::store(abase + e, S);
-            } else {
-                int S[KPL];
-#pragma unroll
-                for (int j = 0; j < KPL; ++j) S[j] = LP::sum(ac[q], j) + LP::cost(fc[q], j) + L[j];
-                if (a.agg_total) LP::store(abase + e, S);
-                uint16_t* rw = ring + (s & (RING - 1)) * RS + KPL * lane;
-                if (KPL == 2) {
-                    *reinterpret_cast<uint32_t*>(rw) = (uint32_t)S[0] | ((uint32_t)S[1] << 16);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < KPL; ++j) rw[j] = (uint16_t)S[j];
-                }
-                if ((s & (RING - 1)) == RING - 1 || s == n - 1) flush(s & ~(RING - 1), (s & (RING - 1)) + 1);
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < PF; ++q) {
-            cc[q] = cn[q];
-            fc[q] = fn[q];
-            ac[q] = an[q];
-        }
-    }
+    // only the last segment may be short
+    if (q.n % S) back(nseg - 1, Const<false>());
+    for (int seg = q.n / S - 1; seg >= 0; --seg) back(seg, Const<true>());
 }
-
-// Rows (COLS = false): left to right into lbuf, then right to left summed
-// with it into agg.  Columns (COLS = true): top to bottom into lbuf, then
-// bottom to top with the winner.  One wave per line, four lines per
-// workgroup; the second sweep reads what the same wave stored.
-template <int KPL, bool COLS>
-__global__ __launch_bounds__(256) void k_sgm(SgmArgs a) {
-    extern __shared__ uint16_t sgm_ring[];  // columns: [4 waves][kSgmRing steps][64 KPL + 2]
-    const int line = blockIdx.x * 4 + (threadIdx.x >> 6), ti = blockIdx.y;
-    if (line >= (COLS ? a.W : a.H)) return;
-    uint16_t* ring = sgm_ring + (threadIdx.x >> 6) * kSgmRing * (64 * KPL + 2);
-    sgm_sweep<KPL, kForward>(a, line, ti, !COLS, false, ring);
-    if (COLS) sgm_sweep<KPL, kColsBack>(a, line, ti, false, true, ring);
-    else sgm_sweep<KPL, kRowsBack>(a, line, ti, true, true, ring);
-}
-
-template <int KPL>
-constexpr size_t sgm_ring_bytes() { return (size_t)4 * kSgmRing * (64 * KPL + 2) * sizeof(uint16_t); }
 
 // ---------------------------------------------------------------- fusion
 
@@ -829,14 +951,45 @@ pgs_status check_params(const pgs_mvs_params* p, const char* who) {
     return PGS_OK;
 }
 
-template <int KPL>
-pgs_status launch_sgm(SgmArgs a, int n_targets, hipStream_t s) {
-    static const bool lds_ok = hipFuncSetAttribute(reinterpret_cast<const void*>(k_sgm<KPL, true>),
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                   (int)sgm_ring_bytes<KPL>()) == hipSuccess;
-    PGS_REQUIRE(lds_ok, "pgs_mvs_sgm: cannot reserve %zu bytes of LDS", sgm_ring_bytes<KPL>());
-    k_sgm<KPL, false><<<dim3((a.H + 3) / 4, n_targets), 256, 0, s>>>(a);
-    k_sgm<KPL, true><<<dim3((a.W + 3) / 4, n_targets), 256, sgm_ring_bytes<KPL>(), s>>>(a);
+// Large batches sweep whole lines twice (rows, then columns; six bytes moved
+// per cell, three forward steps for two).  Small ones, whose few lines leave
+// the chip waiting for each step's chain, run three of the four directions
+// side by side with their path costs stored (ten bytes per cell), which
+// halves the steps that follow one another.  The line lies where the two
+// measured even, by waves of four rows (whole lines / side by side): 640x480
+// of 64 planes 402 / 372 us at 960 waves; 960x720 of 128 658 / 366 us at 180,
+// 680 / 552 at 540, 701 / 725 at 720; 640x480 of 256 818 / 673 at 480,
+// 1177 / 1501 at 960.  Sums of two rows that pass a byte, and calls that want
+// the sums, run side by side too.  Before, one line per wave with 32-bit
+// planes, path costs stored as bytes and row sums in 16 bits: twelve bytes per
+// cell and about 50 vector instructions a pixel-step against 11; eight
+// 960x720 targets of 128 planes 2.12 -> 1.18 ms, one 0.70 -> 0.37 ms.
+template <int D>
+constexpr long long kSgmWaves = D == 64 ? 1024 : 640;
+
+template <int D>
+pgs_status launch_sgm(const SgmArgs& a, int n_targets, hipStream_t s) {
+    const int rows = (a.H + 3) / 4, cols = (a.W + 3) / 4;
+    const bool wide = 2 * (kCostOut + a.p2) > 255;
+    if ((long long)rows * n_targets <= kSgmWaves<D> || wide || a.agg_out) {
+        // sums up to 4 (48 + P2) and log2 D bits of plane in 16
+        constexpr bool kFits = D == 64;
+        const bool fused = kFits || (D == 128 && 4 * (kCostOut + a.p2) < 512);
+        const dim3 grid(cols, n_targets);
+        k_sgm_paths<D><<<dim3(2 * rows + cols, n_targets), 64, 0, s>>>(a, rows);
+        if (fused) {
+            if constexpr (D <= 128) {
+                if (a.agg_out) k_sgm_cols<D, true, true, true><<<grid, 64, 0, s>>>(a);
+                else k_sgm_cols<D, true, true, false><<<grid, 64, 0, s>>>(a);
+            }
+        } else if constexpr (!kFits) {
+            if (a.agg_out) k_sgm_cols<D, true, false, true><<<grid, 64, 0, s>>>(a);
+            else k_sgm_cols<D, true, false, false><<<grid, 64, 0, s>>>(a);
+        }
+    } else {
+        k_sgm_rows<D><<<dim3(rows, n_targets), 64, 0, s>>>(a);
+        k_sgm_cols<D, false, (D <= 128), false><<<dim3(cols, n_targets), 64, 0, s>>>(a);
+    }
     PGS_CHECK_LAUNCH("pgs_mvs_sgm");
     return PGS_OK;
 }
@@ -939,9 +1092,11 @@ extern "C" pgs_status pgs_mvs_sgm(const uint8_t* cost_dev, int32_t width, int32_
     const size_t e = (size_t)n_targets * width * height * params->n_planes;
     SgmArgs a{};
     a.cost = cost_dev;
-    a.lbuf = static_cast<uint8_t*>(workspace_dev);
-    a.agg = agg_out_dev ? agg_out_dev : reinterpret_cast<uint16_t*>(static_cast<char*>(workspace_dev) + al256(e));
-    a.agg_total = agg_out_dev != nullptr;
+    char* ws = static_cast<char*>(workspace_dev);
+    a.buf[0] = reinterpret_cast<uint8_t*>(ws);
+    a.buf[1] = reinterpret_cast<uint8_t*>(ws + al256(e));
+    a.buf[2] = a.buf[1] + e;
+    a.agg_out = agg_out_dev;
     a.targets = targets_dev;
     a.range = range_dev;
     a.depth = depth_dev;
@@ -953,10 +1108,10 @@ extern "C" pgs_status pgs_mvs_sgm(const uint8_t* cost_dev, int32_t width, int32_
     a.keep_ratio = 1.0 - params->conf_min;
     hipStream_t s = pgs::as_stream(stream);
     switch (params->n_planes) {
-        case 64: return launch_sgm<1>(a, n_targets, s);
-        case 128: return launch_sgm<2>(a, n_targets, s);
-        case 192: return launch_sgm<3>(a, n_targets, s);
-        default: return launch_sgm<4>(a, n_targets, s);
+        case 64: return launch_sgm<64>(a, n_targets, s);
+        case 128: return launch_sgm<128>(a, n_targets, s);
+        case 192: return launch_sgm<192>(a, n_targets, s);
+        default: return launch_sgm<256>(a, n_targets, s);
     }
 }
 

@@ -255,3 +255,38 @@ def test_cost_with_planes_behind_the_reference(W, H, D, other):
     C, marg = omvs.cost_volume(omvs.census(g[0]), omvs.census(g[1]), cams[0], cams[1], lo, hi, D, with_margin=True)
     _assert_cost_close(cost[0], C, marg, f"reference {other}")
     assert (C == omvs.COST_OUT).any() and (C != omvs.COST_OUT).any()
+
+
+@pytest.mark.parametrize("T,W,H,D,p2,agg", [
+    (1, 5, 3, 64, 32, False), (1, 16, 48, 128, 79, False), (2, 33, 17, 128, 80, False), (1, 49, 31, 64, 207, False),
+    (1, 23, 21, 128, 207, True), (1, 37, 26, 192, 79, False), (1, 18, 40, 256, 207, True),
+    # enough rows for the sweeps of whole lines
+    (2, 13, 1290, 128, 32, False), (2, 19, 1284, 192, 79, False), (1, 40, 2565, 256, 32, False),
+    (2, 9, 2052, 64, 79, False), (2, 13, 1290, 128, 80, False)])
+def test_sgm_line_sweeps(T, W, H, D, p2, agg):
+    # both ways of sweeping the lines against the oracle on random volumes:
+    # lines shorter than a segment, of whole segments and with a remainder,
+    # line counts that do not fill a wave, penalties on both sides of the byte
+    # sums and of the joined sum-and-plane keys, plane counts of each kernel;
+    # smooth ramps make ties between planes and between neighbours
+    from paper_2601_17354_amd import mvs
+    rng = np.random.default_rng(W * H + D + p2)
+    cost = rng.integers(0, 49, (T, H, W, D)).astype(np.uint8)
+    cost[:, : H // 3] = (np.arange(D) // 3 % 49).astype(np.uint8)
+    pr = _params(D, p1=7, p2=p2)
+    ranges = np.array([[1.0, 6.0]] * T)
+    depth = torch.empty((T, H, W), dtype=torch.float32, device="cuda")
+    conf = torch.empty_like(depth)
+    out = torch.empty((T, H, W, D), dtype=torch.int16, device="cuda") if agg else None
+    mvs.pgs_mvs_sgm(torch.as_tensor(cost, device="cuda"), torch.arange(T, dtype=torch.int32, device="cuda"),
+                    torch.as_tensor(ranges, device="cuda"), pr, depth, conf, agg_out=out)
+    torch.cuda.synchronize()
+    for t in range(T):
+        S = omvs.sgm(cost[t], pr.p1, pr.p2)
+        if agg:
+            np.testing.assert_array_equal(out[t].cpu().numpy().view(np.uint16).astype(np.int64), S)
+        d, c, _ = omvs.winner(S, 1.0, 6.0, pr.conf_min)
+        got = depth[t].cpu().numpy()
+        np.testing.assert_array_equal(got > 0, d > 0)
+        np.testing.assert_allclose(got, d, rtol=1e-6, atol=0)
+        np.testing.assert_allclose(conf[t].cpu().numpy(), c, rtol=1e-6, atol=1e-7)
