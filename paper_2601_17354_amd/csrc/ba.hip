@@ -6,26 +6,25 @@
 // Everything is float64.  One Levenberg-Marquardt step (pgs_ba_step):
 //   k_ba_points   one thread per point, over its observations: residual,
 //                 Huber weight, Jacobians; the point block H_pp + lambda
-//                 diag(H_pp) inverted in place (3x3, adjugate), v = H_pp^-1 b_p,
-//                 and per observation the pose-point block H_tp (6x3) and the
-//                 observation's pose block and gradient (21 + 6 values);
+//                 diag(H_pp) inverted in place (3x3, adjugate), v = H_pp^-1 b_p.
+//                 The observations' own blocks are not stored: every kernel
+//                 that needs one linearises the observation again (about 150
+//                 instructions; its 45 stored values made 360 bytes per
+//                 observation out and several times back);
 //   k_ba_cameras  16 workgroups per camera, each over a slice of its
-//                 observations: partial row blocks of the reduced system
+//                 observations: the camera's pose block and gradient, and
+//                 partial row blocks of the reduced system
 //                 S = H_tt - H_tp H_pp^-1 H_pt (its blocks (i, k), k <= i:
-//                 the solve reads the lower triangle) and g = b_t - H_tp v
+//                 the solve reads the lower triangle) and g = b_t - H_tp v,
 //                 accumulated in LDS over every pair of observations that
-//                 share a point (float64 LDS atomics); the first slice adds
-//                 the camera's damped pose block and gradient, summed over
-//                 its observations in a fixed order; k_ba_rows sums the
-//                 slices in order;
-//   k_ba_solve /  the gauge-free rows and columns of S (camera 0's six
-//   k_ba_syrk     parameters and camera 1's centre coordinate along the gauge
-//                 axis removed), a panel-blocked Cholesky (each panel
-//                 factored by one workgroup in LDS, the right-hand side
-//                 carried as an extra row so the forward substitution comes
-//                 with the factor; the trailing update over many
-//                 workgroups), and the blocked back substitution -> the
-//                 pose step;
+//                 share a point (float64 LDS atomics); k_ba_rows sums the
+//                 slices in order, damps, and writes the gauge-free lower
+//                 triangle (camera 0's six parameters and camera 1's centre
+//                 coordinate along the gauge axis left out);
+//   k_ba_first /  a Cholesky in 32-column panels, one launch per panel, the
+//   k_ba_panel    right-hand side carried as an extra row so the forward
+//                 substitution comes with the factor, and k_ba_back, the
+//                 back substitution -> the pose step;
 //   k_ba_backsub  one thread per point: dP = v - H_pp^-1 sum H_tp^T dt.
 // The cost (sum of Huber terms) is reduced per block in a fixed order.
 #include <math.h>
@@ -35,15 +34,15 @@
 namespace {
 
 constexpr int kCamThreads = 256;
-constexpr int kSolveThreads = 1024;
 constexpr int kCostThreads = 256;
+constexpr int kPointThreads = 64;
 
-// Per-observation record in the workspace: H_tp (6x3 row-major), then the
-// observation's pose block (upper triangle of 6x6, row-major, 21 values)
-// and its gradient contribution (6).
-constexpr int kObsRec = 18 + 21 + 6;
 // Per-point record: damped H_pp^-1 (3x3 row-major) and v (3).
 constexpr int kPtRec = 12;
+
+// A camera in LDS: rotation (9, row-major) and centre (3), padded so that
+// different cameras' words fall in different banks.
+constexpr int kCamRec = 13;
 
 struct Obs {
     double r[2];        // residual
@@ -52,19 +51,26 @@ struct Obs {
     double Jp[2][3];    // d r / dP
 };
 
-__device__ __forceinline__ void observe(const pgs_ba_problem& pb, const double* __restrict__ rot,
-                                        const double* __restrict__ centre, const double* __restrict__ pts,
-                                        int o, int j, Obs& ob) {
-    const int i = (int)pb.obs_cam_dev[o];
-    const double* R = rot + 9 * (size_t)i;
-    const double d0 = pts[3 * (size_t)j] - centre[3 * i], d1 = pts[3 * (size_t)j + 1] - centre[3 * i + 1],
-                 d2 = pts[3 * (size_t)j + 2] - centre[3 * i + 2];
+__device__ __forceinline__ void load_cams(const pgs_ba_problem& pb, const double* __restrict__ rot,
+                                          const double* __restrict__ centre, double* cam) {
+    for (int e = threadIdx.x; e < pb.n_cams * 12; e += blockDim.x) {
+        const int i = e / 12, k = e - i * 12;
+        cam[i * kCamRec + k] = k < 9 ? rot[9 * (size_t)i + k] : centre[3 * (size_t)i + k - 9];
+    }
+}
+
+// The observation (u, v) of point P by the camera record cam.
+__device__ __forceinline__ void observe(const pgs_ba_problem& pb, const double* cam, const double (&P)[3], double u,
+                                        double v, Obs& ob) {
+    double R[9];
+    for (int k = 0; k < 9; ++k) R[k] = cam[k];
+    const double d0 = P[0] - cam[9], d1 = P[1] - cam[10], d2 = P[2] - cam[11];
     const double x0 = R[0] * d0 + R[1] * d1 + R[2] * d2;
     const double x1 = R[3] * d0 + R[4] * d1 + R[5] * d2;
     const double x2 = R[6] * d0 + R[7] * d1 + R[8] * d2;
     const double iz = 1.0 / x2;
-    ob.r[0] = pb.fx * x0 * iz + pb.cx - pb.obs_uv_dev[2 * (size_t)o];
-    ob.r[1] = pb.fy * x1 * iz + pb.cy - pb.obs_uv_dev[2 * (size_t)o + 1];
+    ob.r[0] = pb.fx * x0 * iz + pb.cx - u;
+    ob.r[1] = pb.fy * x1 * iz + pb.cy - v;
     const double s = ob.r[0] * ob.r[0] + ob.r[1] * ob.r[1];
     const double nrm = sqrt(s);
     ob.w = nrm <= pb.huber_delta ? 1.0 : pb.huber_delta / nrm;
@@ -92,33 +98,34 @@ __device__ __forceinline__ void observe(const pgs_ba_problem& pb, const double* 
     }
 }
 
+__device__ __forceinline__ void load_point(const double* __restrict__ pts, size_t j, double (&P)[3]) {
+    for (int a = 0; a < 3; ++a) P[a] = pts[3 * j + a];
+}
+
 __device__ __forceinline__ int tri6(int a, int b) {  // index of (a, b), a <= b, in the 6x6 upper triangle
     return a * 6 - a * (a - 1) / 2 + (b - a);
 }
 
-__global__ __launch_bounds__(256) void k_ba_points(pgs_ba_problem pb, const double* __restrict__ rot,
-                                                   const double* __restrict__ centre,
-                                                   const double* __restrict__ pts, double lam,
-                                                   double* __restrict__ obs_rec, double* __restrict__ pt_rec) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(kPointThreads) void k_ba_points(pgs_ba_problem pb, const double* __restrict__ rot,
+                                                             const double* __restrict__ centre,
+                                                             const double* __restrict__ pts, double lam,
+                                                             double* __restrict__ pt_rec) {
+    extern __shared__ double cam[];
+    load_cams(pb, rot, centre, cam);
+    __syncthreads();
+    const int j = blockIdx.x * kPointThreads + threadIdx.x;
     if (j >= pb.n_points) return;
+    double P[3];
+    load_point(pts, j, P);
     double Hp[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}}, bp[3] = {0, 0, 0};
     const uint32_t o0 = pb.point_start_dev[j], o1 = pb.point_start_dev[j + 1];
     for (uint32_t o = o0; o < o1; ++o) {
         Obs ob;
-        observe(pb, rot, centre, pts, (int)o, j, ob);
-        double* rec = obs_rec + (size_t)o * kObsRec;
+        observe(pb, cam + pb.obs_cam_dev[o] * kCamRec, P, pb.obs_uv_dev[2 * (size_t)o],
+                pb.obs_uv_dev[2 * (size_t)o + 1], ob);
         for (int a = 0; a < 3; ++a) {
             for (int b = 0; b < 3; ++b) Hp[a][b] += ob.w * (ob.Jp[0][a] * ob.Jp[0][b] + ob.Jp[1][a] * ob.Jp[1][b]);
             bp[a] -= ob.w * (ob.Jp[0][a] * ob.r[0] + ob.Jp[1][a] * ob.r[1]);
-        }
-        for (int a = 0; a < 6; ++a)
-            for (int b = 0; b < 3; ++b)
-                rec[3 * a + b] = ob.w * (ob.Jt[0][a] * ob.Jp[0][b] + ob.Jt[1][a] * ob.Jp[1][b]);
-        for (int a = 0; a < 6; ++a) {
-            for (int b = a; b < 6; ++b)
-                rec[18 + tri6(a, b)] = ob.w * (ob.Jt[0][a] * ob.Jt[0][b] + ob.Jt[1][a] * ob.Jt[1][b]);
-            rec[39 + a] = -ob.w * (ob.Jt[0][a] * ob.r[0] + ob.Jt[1][a] * ob.r[1]);
         }
     }
     // damped point block and its inverse (adjugate / determinant)
@@ -154,105 +161,158 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
     return v;
 }
 
-// Workgroup (i, s): split s of camera i's observations.  Partial row block
-// i of the reduced system over those observations (pair products of
-// observations that share a point, float64 LDS atomics); split 0 also adds
-// the camera's damped pose block and gradient, summed over all its
-// observations in a fixed order.  Partials go to part[i][s][6 n6 + 6].
-constexpr int kCamSplit = 16;
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
-__global__ __launch_bounds__(kCamThreads) void k_ba_cameras(pgs_ba_problem pb, double lam,
-                                                            const double* __restrict__ obs_rec,
+// Workgroup (i, s): slice s of camera i's observations, 64 to a wave.  First
+// each lane linearises one observation of camera i: its pose block and
+// gradient, its share of - H_tp v, and T = H_tp H_pp^-1 with the point's
+// coordinates into the wave's LDS slots.  Then the pairs (observation, member
+// k <= i of its point's track) are listed, eight members of every track at a
+// time, and taken one per lane whichever observation they belong to: the
+// lane linearises the member and adds - T H_tp(k)^T, 36 float64 LDS atomics.
+// The lane's own track in lockstep (half of its members past i) and each
+// member's block read from memory took 0.55 ms for 60 cameras and 786k
+// observations, 0.21 ms now, of which the LDS is busy 0.09 ms with the adds
+// (two workgroups per CU is what its size allows).  Blocks of 37 values
+// put different cameras' terms in different banks.
+// An observation's pair with itself, which would put as many adds on one
+// block as the wave has tracks, is taken off the pose block in registers (its
+// product is symmetric too).
+// Partials go to part[i][s][36 n_cams + 33]: row blocks k <= i, then pose
+// block less own pairs (21), the pose block's diagonal (6, for the damping)
+// and gradient less H_tp v (6).
+constexpr int kCamSplit = 16;
+constexpr int kBlk = 37;               // 36 values of a row block, padded
+constexpr int kSlot = 21;              // T (18) and the point (3)
+constexpr int kMembers = 8;            // members of a track listed at a time
+constexpr int kPose = 33;
+
+constexpr size_t cameras_lds(int n_cams) {
+    return (size_t)(kCamRec + kBlk) * n_cams * 8 + (kCamThreads / 64) * (64 * kSlot * 8 + 64 * kMembers * 4 + 64 * 4);
+}
+
+__global__ __launch_bounds__(kCamThreads) void k_ba_cameras(pgs_ba_problem pb, const double* __restrict__ rot,
+                                                            const double* __restrict__ centre,
+                                                            const double* __restrict__ pts,
                                                             const double* __restrict__ pt_rec,
                                                             double* __restrict__ part) {
     extern __shared__ double lds[];
     constexpr int NW = kCamThreads / 64;
-    const int i = blockIdx.x, split = blockIdx.y, t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    const int n6 = 6 * pb.n_cams;
-    double* row = lds;                 // [6][n6]
-    double* wsum = row + 6 * n6;       // [NW][27] per-wave pose block sums
-    double* gi = wsum + NW * 27;       // [6]
-    const uint32_t c0 = pb.cam_start_dev[i], c1 = pb.cam_start_dev[i + 1];
-    for (int e = t; e < 6 * n6; e += kCamThreads) row[e] = 0.0;
-    if (t < 6) gi[t] = 0.0;
-    if (split == 0) {
-        // pose block and gradient of camera i: per-lane sums over its
-        // observations, then wave sums and the waves' totals in a fixed order
-        double acc[27];
-        for (int k = 0; k < 27; ++k) acc[k] = 0.0;
-        for (uint32_t q = c0 + t; q < c1; q += kCamThreads) {
-            const double* rec = obs_rec + (size_t)pb.cam_obs_dev[q] * kObsRec + 18;
-            for (int k = 0; k < 27; ++k) acc[k] += rec[k];
-        }
-        for (int k = 0; k < 27; ++k) {
-            const double v = wave_sum_f64(acc[k]);
-            if (lane == 0) wsum[wv * 27 + k] = v;
-        }
-        __syncthreads();
-        if (t < 36) {
-            const int a = t / 6, b = t % 6, k = a <= b ? tri6(a, b) : tri6(b, a);
-            double h = 0.0;
-            for (int w = 0; w < NW; ++w) h += wsum[w * 27 + k];
-            if (a == b) h += lam * h;
-            row[a * n6 + 6 * i + b] = h;
-        }
-        if (t < 6) {
-            double h = 0.0;
-            for (int w = 0; w < NW; ++w) h += wsum[w * 27 + 21 + t];
-            gi[t] = h;
-        }
-    }
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6, C = pb.n_cams, split = blockIdx.y;
+    const int i = C - 1 - (int)blockIdx.x;  // the last cameras have the most pairs and go first
+    double* cam = lds;                            // [C][kCamRec]
+    double* acc = cam + (size_t)C * kCamRec;      // [C][kBlk]
+    double* slots = acc + (size_t)C * kBlk + (size_t)wv * 64 * kSlot;
+    uint32_t* lists = reinterpret_cast<uint32_t*>(acc + (size_t)C * kBlk + (size_t)NW * 64 * kSlot);
+    uint32_t* list = lists + wv * 64 * (kMembers + 1);
+    uint32_t* starts = list + 64 * kMembers;      // first observation of each slot's track
+    load_cams(pb, rot, centre, cam);
+    for (int e = t; e < (i + 1) * kBlk; e += kCamThreads) acc[e] = 0.0;
     __syncthreads();
-    // - H_tp H_pp^-1 H_pt and - H_tp v over this split of camera i's observations
+    const uint32_t c0 = pb.cam_start_dev[i], c1 = pb.cam_start_dev[i + 1];
     const uint32_t chunk = (c1 - c0 + kCamSplit - 1) / kCamSplit;
     const uint32_t q0 = c0 + split * chunk, q1 = min(c1, q0 + chunk);
-    double gl[6] = {0, 0, 0, 0, 0, 0};  // this lane's share of - H_tp v
-    for (uint32_t q = q0 + t; q < q1; q += kCamThreads) {
-        const uint32_t o = pb.cam_obs_dev[q];
-        const uint32_t j = pb.obs_pt_dev[o];
-        const double* Htp = obs_rec + (size_t)o * kObsRec;
-        const double* pr = pt_rec + (size_t)j * kPtRec;
-        double T[6][3];  // H_tp(i, j) H_pp(j)^-1
-        for (int a = 0; a < 6; ++a)
-            for (int b = 0; b < 3; ++b)
-                T[a][b] = Htp[3 * a] * pr[b] + Htp[3 * a + 1] * pr[3 + b] + Htp[3 * a + 2] * pr[6 + b];
-        for (int a = 0; a < 6; ++a) gl[a] -= Htp[3 * a] * pr[9] + Htp[3 * a + 1] * pr[10] + Htp[3 * a + 2] * pr[11];
-        // the track is walked from a lane-dependent start so that the lanes
-        // of a wave add into different camera blocks at the same time
-        const uint32_t s0 = pb.point_start_dev[j], nt = pb.point_start_dev[j + 1] - s0;
-        for (uint32_t r = 0; r < nt; ++r) {
-            uint32_t o2 = s0 + r + (uint32_t)lane % nt;
-            if (o2 >= s0 + nt) o2 -= nt;
-            const int k = (int)pb.obs_cam_dev[o2];
-            if (k > i) continue;  // the solve reads the lower triangle only
-            const double* H2 = obs_rec + (size_t)o2 * kObsRec;
-            for (int a = 0; a < 6; ++a)
-                for (int b = 0; b < 6; ++b)
-                    atomicAdd(&row[a * n6 + 6 * k + b],
-                              -(T[a][0] * H2[3 * b] + T[a][1] * H2[3 * b + 1] + T[a][2] * H2[3 * b + 2]));
+    double pose[kPose];
+#pragma unroll
+    for (int k = 0; k < kPose; ++k) pose[k] = 0.0;
+    for (uint32_t qb = q0 + wv * 64; qb < q1; qb += kCamThreads) {
+        const bool has = qb + lane < q1;
+        uint32_t s0 = 0, n = 0, own = 0;
+        if (has) {
+            const uint32_t o = pb.cam_obs_dev[qb + lane], j = pb.obs_pt_dev[o];
+            own = o;
+            s0 = pb.point_start_dev[j];
+            n = pb.point_start_dev[j + 1] - s0;
+            double P[3];
+            load_point(pts, j, P);
+            Obs ob;
+            observe(pb, cam + i * kCamRec, P, pb.obs_uv_dev[2 * (size_t)o], pb.obs_uv_dev[2 * (size_t)o + 1], ob);
+            const double* pr = pt_rec + (size_t)j * kPtRec;
+            double h0[3], h1[3];  // w Jp H_pp^-1
+            double v0 = 0.0, v1 = 0.0;
+            for (int b = 0; b < 3; ++b) {
+                h0[b] = ob.w * (ob.Jp[0][0] * pr[b] + ob.Jp[0][1] * pr[3 + b] + ob.Jp[0][2] * pr[6 + b]);
+                h1[b] = ob.w * (ob.Jp[1][0] * pr[b] + ob.Jp[1][1] * pr[3 + b] + ob.Jp[1][2] * pr[6 + b]);
+                v0 += ob.w * ob.Jp[0][b] * pr[9 + b];
+                v1 += ob.w * ob.Jp[1][b] * pr[9 + b];
+            }
+            double* slot = slots + lane * kSlot;
+            // H_tp H_pp^-1 H_pt of the observation itself: Jt^T G Jt
+            double g00 = 0.0, g01 = 0.0, g11 = 0.0;
+            for (int b = 0; b < 3; ++b) {
+                g00 += ob.w * h0[b] * ob.Jp[0][b];
+                g01 += ob.w * h0[b] * ob.Jp[1][b];
+                g11 += ob.w * h1[b] * ob.Jp[1][b];
+            }
+#pragma unroll
+            for (int a = 0; a < 6; ++a) {
+                const double w0 = ob.w * ob.Jt[0][a], w1 = ob.w * ob.Jt[1][a];
+                const double u0 = w0 - (g00 * ob.Jt[0][a] + g01 * ob.Jt[1][a]);
+                const double u1 = w1 - (g01 * ob.Jt[0][a] + g11 * ob.Jt[1][a]);
+#pragma unroll
+                for (int b = a; b < 6; ++b) pose[tri6(a, b)] += u0 * ob.Jt[0][b] + u1 * ob.Jt[1][b];
+                pose[21 + a] += w0 * ob.Jt[0][a] + w1 * ob.Jt[1][a];
+                pose[27 + a] -= ob.Jt[0][a] * (ob.w * ob.r[0] + v0) + ob.Jt[1][a] * (ob.w * ob.r[1] + v1);
+                for (int b = 0; b < 3; ++b) slot[3 * a + b] = ob.Jt[0][a] * h0[b] + ob.Jt[1][a] * h1[b];
+            }
+            for (int a = 0; a < 3; ++a) slot[18 + a] = P[a];
+            starts[lane] = s0;
+        }
+        for (uint32_t m = 0; __any(m < n); m += kMembers) {
+            uint32_t mine = 0;
+#pragma unroll
+            for (int u = 0; u < kMembers; ++u)
+                if (m + u < n && s0 + m + u != own && (int)pb.obs_cam_dev[s0 + m + u] <= i) mine |= 1u << u;
+            const int cnt = __popc(mine);
+            int inc = cnt;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int up = __shfl_up(inc, o);
+                if (lane >= o) inc += up;
+            }
+            const int total = __shfl(inc, 63);
+            int at = inc - cnt;
+            for (uint32_t w = mine; w; w &= w - 1) list[at++] = ((uint32_t)lane << 3) | (uint32_t)(__ffs(w) - 1);
+            wave_sync();
+            for (int f = lane; f < total; f += 64) {
+                const uint32_t en = list[f], sl = en >> 3, o2 = starts[sl] + m + (en & 7u);
+                const int k = (int)pb.obs_cam_dev[o2];
+                const double* slot = slots + sl * kSlot;
+                double P[3];
+                for (int a = 0; a < 3; ++a) P[a] = slot[18 + a];
+                Obs ob;
+                observe(pb, cam + k * kCamRec, P, pb.obs_uv_dev[2 * (size_t)o2], pb.obs_uv_dev[2 * (size_t)o2 + 1],
+                        ob);
+                double* out = acc + (size_t)k * kBlk;
+                for (int a = 0; a < 6; ++a) {
+                    const double t0 = slot[3 * a], t1 = slot[3 * a + 1], t2 = slot[3 * a + 2];
+                    const double u0 = -ob.w * (t0 * ob.Jp[0][0] + t1 * ob.Jp[0][1] + t2 * ob.Jp[0][2]);
+                    const double u1 = -ob.w * (t0 * ob.Jp[1][0] + t1 * ob.Jp[1][1] + t2 * ob.Jp[1][2]);
+                    for (int b = 0; b < 6; ++b) atomicAdd(&out[6 * a + b], u0 * ob.Jt[0][b] + u1 * ob.Jt[1][b]);
+                }
+            }
+            wave_sync();  // the list is read before it is written again
         }
     }
-    for (int a = 0; a < 6; ++a) {
-        const double v = wave_sum_f64(gl[a]);
-        if (lane == 0) atomicAdd(&gi[a], v);
+    __syncthreads();
+    double* out = part + ((size_t)i * kCamSplit + split) * (36 * (size_t)C + kPose);
+    for (int e = t; e < (i + 1) * 36; e += kCamThreads) out[e] = acc[(e / 36) * kBlk + e % 36];
+    // the waves' pose sums, added in order (the slots are free again)
+    double* wsum = acc + (size_t)C * kBlk;  // [NW][kPose]
+#pragma unroll
+    for (int k = 0; k < kPose; ++k) {
+        const double v = wave_sum_f64(pose[k]);
+        if (lane == 0) wsum[wv * kPose + k] = v;
     }
     __syncthreads();
-    double* out = part + ((size_t)i * kCamSplit + split) * (6 * n6 + 6);
-    for (int e = t; e < 6 * n6; e += kCamThreads) out[e] = row[e];
-    if (t < 6) out[6 * n6 + t] = gi[t];
-}
-
-// Row blocks of S and g: the camera splits' partials summed in split order.
-__global__ __launch_bounds__(256) void k_ba_rows(int n_cams, const double* __restrict__ part,
-                                                 double* __restrict__ S, double* __restrict__ g) {
-    const int n6 = 6 * n_cams, per = 6 * n6 + 6;
-    const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (size_t)n_cams * per) return;
-    const int i = (int)(e / per), k = (int)(e - (size_t)i * per);
-    double acc = 0.0;
-    for (int sp = 0; sp < kCamSplit; ++sp) acc += part[((size_t)i * kCamSplit + sp) * per + k];
-    if (k < 6 * n6) S[(size_t)(6 * i) * n6 + k] = acc;
-    else g[6 * i + (k - 6 * n6)] = acc;
+    if (t < kPose) {
+        double h = 0.0;
+        for (int w = 0; w < NW; ++w) h += wsum[w * kPose + t];
+        out[36 * (size_t)C + t] = h;
+    }
 }
 
 // Free (moving) pose parameter k of nf: skips camera 0's six and camera 1's
@@ -261,232 +321,299 @@ __device__ __forceinline__ int free_param(int k, int gauge_axis) {
     const int p = k + 6;                        // past camera 0
     return p >= 9 + gauge_axis ? p + 1 : p;     // past camera 1's fixed centre coordinate
 }
+// Its inverse: the free parameter's number, or -1.
+__device__ __forceinline__ int free_index(int p, int gauge_axis) {
+    if (p < 6 || p == 9 + gauge_axis) return -1;
+    return p - 6 - (p > 9 + gauge_axis ? 1 : 0);
+}
 
-// Broadcast of a double from lane `src` of the wave.
-__device__ __forceinline__ double lane_bcast(double v, int src) {
+// The gauge-free reduced system from the camera slices' partials, summed in
+// slice order: thread (i, k, a, b) of the lower triangle's row blocks, the
+// damped pose block added at k = i; the right-hand side becomes row nf of A.
+__global__ __launch_bounds__(256) void k_ba_rows(int n_cams, int gauge_axis, double lam,
+                                                 const double* __restrict__ part, double* __restrict__ A) {
+    const int nf = 6 * n_cams - 7, per = 36 * n_cams + kPose;
+    const int i = blockIdx.y, e = blockIdx.x * 256 + threadIdx.x;
+    if (e >= 36 * (i + 1) + 6) return;
+    const double* p = part + (size_t)i * kCamSplit * per;
+    auto slices = [&](int at) {
+        double acc = 0.0;
+        for (int sp = 0; sp < kCamSplit; ++sp) acc += p[(size_t)sp * per + at];
+        return acc;
+    };
+    if (e >= 36 * (i + 1)) {
+        const int a = e - 36 * (i + 1), r = free_index(6 * i + a, gauge_axis);
+        if (r >= 0) A[(size_t)nf * nf + r] = slices(36 * n_cams + 27 + a);
+        return;
+    }
+    const int k = e / 36, ab = e - 36 * k, a = ab / 6, b = ab - 6 * a;
+    const int r = free_index(6 * i + a, gauge_axis), c = free_index(6 * k + b, gauge_axis);
+    if (r < 0 || c < 0 || c > r) return;
+    double v = slices(e);
+    if (k == i) {
+        v += slices(36 * n_cams + (a <= b ? tri6(a, b) : tri6(b, a)));
+        if (a == b) v += lam * slices(36 * n_cams + 21 + a);
+    }
+    A[(size_t)r * nf + c] = v;
+}
+
+// ---------------------------------------------------------------- solve
+//
+// A holds nf + 1 rows of nf: the lower triangle of the system, then the
+// right-hand side as an extra row, so that the Cholesky factorisation
+// A = L L^T of the rows computes the forward substitution L y = g as that
+// row's entries of L.  Right-looking, in panels of 32 columns with one launch
+// each (k_ba_panel): a workgroup per 32 x 32 tile of the trailing triangle
+// turns its own two row blocks of the panel into L (A L11^-T, one product with
+// the inverse of the panel's diagonal block, which the launch before left)
+// and subtracts their product; the workgroup of the next panel's diagonal
+// block then factors and inverts it.  Nothing but that block's chain is
+// serial.  One workgroup factoring a panel, another launch updating the
+// trailing triangle and a triangular solve per row of the panel took 505 + 74
+// us at 60 cameras (nf = 353), 12 launches of 12.3 us and 30 + 11 us for the
+// back substitution and the first block now: each launch's fixed 4 us and the
+// 5 us of its 32 pivots are what is left.
+constexpr int kPW = 32;
+constexpr int kPS = kPW + 1;
+constexpr int kSolveThreads = 1024;
+
+__device__ __forceinline__ double read_lane_f64(double v, int src) {
     const long long b = __double_as_longlong(v);
-    const int lo = __shfl((int)(b & 0xffffffffll), src), hi = __shfl((int)(b >> 32), src);
+    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), src);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), src);
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// One workgroup solves the gauge-free reduced camera system.  A holds nf + 1
-// rows of nf: the system's rows, then the right-hand side as an extra row,
-// so that the Cholesky factorisation A = L L^T of the rows computes the
-// forward substitution L y = g as that row's entries of L.  Right-looking,
-// in panels of PW columns: the panel's rows (from the panel's diagonal down,
-// right-hand side included) are staged in LDS; the PW x PW diagonal block is
-// factored with one thread per entry; the rows below are the triangular
-// solves x L11^T = a, one thread per row; the trailing lower triangle is
-// updated in 4 x 4 register blocks from the panel in LDS.  Back substitution
-// L^T x = y then runs panel by panel from the last: the products with the
-// solved entries below a panel are summed over 1024 / PW row slices in a
-// fixed order, and one wave solves the PW x PW triangle with lane broadcasts.
-// The step is scattered to the free pose entries; the fixed ones are 0.
-// `flags` and [k_begin, k_end) select the part one launch does (gather,
-// panels, in-kernel trailing updates, back substitution).
-constexpr int kSolveGather = 1, kSolveTrailing = 2, kSolveBack = 4;
-
-template <int PW>
-__global__ __launch_bounds__(kSolveThreads) void k_ba_solve(int n_cams, int gauge_axis,
-                                                            const double* __restrict__ S,
-                                                            const double* __restrict__ g, double* __restrict__ A,
-                                                            double* __restrict__ dpose, int k_begin, int k_end,
-                                                            int flags) {
-    extern __shared__ double lds[];
-    constexpr int T = kSolveThreads, PS = PW + 1, NS = T / PW;
-    const int n6 = 6 * n_cams, nf = n6 - 7, t = threadIdx.x;
-    double* col = lds;                  // [PW] the column being eliminated
-    double* inv = col + PW;             // [PW] 1 / L_pp of the panel
-    double* dd = inv + PW;              // [1]  the pivot
-    double* P = dd + 2;                 // panel [nf + 1][PS]; later red [NS][PW], L11 [PW][PS], x [nf]
-    if (flags & kSolveGather) {
-        for (int e = t; e < nf * nf; e += T) {
-            const int r = e / nf, c = e - r * nf;
-            if (c <= r) A[e] = S[(size_t)free_param(r, gauge_axis) * n6 + free_param(c, gauge_axis)];
-        }
-        for (int c = t; c < nf; c += T) A[(size_t)nf * nf + c] = g[free_param(c, gauge_axis)];
-        __syncthreads();
-    }
-    for (int k0 = k_begin; k0 < nf && k0 < k_end; k0 += PW) {
-        const int nb = min(PW, nf - k0), m = nf + 1 - k0;  // panel rows, the right-hand side last
-        for (int e = t; e < m * nb; e += T) {
-            const int r = e / nb, c = e - r * nb;
-            P[r * PS + c] = (r >= nb || c <= r) ? A[(size_t)(k0 + r) * nf + k0 + c] : 0.0;
-        }
-        __syncthreads();
-        // diagonal block: thread (r, c), c <= r < nb, keeps its entry in a register
-        const int dr = t / PW, dc = t % PW;
-        const bool own = t < PW * PW && dr < nb && dc <= dr;
-        double a = own ? P[dr * PS + dc] : 0.0;
-        for (int p = 0; p < nb; ++p) {
-            if (own && dr == p && dc == p) dd[0] = a;
-            __syncthreads();
-            if (own && dc == p) {
-                const double d = sqrt(dd[0]);
-                a = dr == p ? d : a / d;
-                col[dr] = a;
-                if (dr == p) inv[p] = 1.0 / d;
-            }
-            __syncthreads();
-            if (own && dc > p) a -= col[dr] * col[dc];
-        }
-        if (own) P[dr * PS + dc] = a;
-        __syncthreads();
-        // rows below the block: x L11^T = a, x_p = (a_p - sum_{q<p} x_q L_pq) / L_pp
-        for (int r = nb + t; r < m; r += T) {
-            double x[PW];
-#pragma unroll
-            for (int p = 0; p < PW; ++p) x[p] = p < nb ? P[r * PS + p] : 0.0;
-#pragma unroll
-            for (int p = 0; p < PW; ++p) {
-                if (p < nb) {
-                    double v = x[p];
-#pragma unroll
-                    for (int q = 0; q < p; ++q) v -= x[q] * P[p * PS + q];
-                    x[p] = v * inv[p];
-                }
-            }
-#pragma unroll
-            for (int p = 0; p < PW; ++p)
-                if (p < nb) P[r * PS + p] = x[p];
-        }
-        __syncthreads();
-        for (int e = t; e < m * nb; e += T) {
-            const int r = e / nb, c = e - r * nb;
-            if (r >= nb || c <= r) A[(size_t)(k0 + r) * nf + k0 + c] = P[r * PS + c];
-        }
-        // trailing update of rows nb..m-1 (right-hand side last), columns
-        // nb..nf-k0-1, lower triangle: A_ij -= sum_p L_ip L_jp (here, or by
-        // k_ba_syrk over many workgroups)
-        const int mt = m - nb, mc = mt - 1, bi_n = (mt + 3) >> 2, bj_n = (mc + 3) >> 2;
-        for (int e = t; e < ((flags & kSolveTrailing) ? bi_n * bj_n : 0); e += T) {
-            const int bi = e / bj_n, bj = e - bi * bj_n;
-            if (bj > bi) continue;
-            double acc[4][4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[u][v] = 0.0;
-            int ri[4], rj[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                ri[u] = nb + min(4 * bi + u, mt - 1);
-                rj[u] = nb + min(4 * bj + u, mc - 1);
-            }
-            for (int p = 0; p < nb; ++p) {
-                double li[4], lj[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    li[u] = P[ri[u] * PS + p];
-                    lj[u] = P[rj[u] * PS + p];
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) acc[u][v] = fma(li[u], lj[v], acc[u][v]);
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int ii = 4 * bi + u;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int jj = 4 * bj + v;
-                    if (ii < mt && jj < mc && jj <= ii) A[(size_t)(k0 + nb + ii) * nf + k0 + nb + jj] -= acc[u][v];
-                }
-            }
-        }
-        __syncthreads();
-    }
-    if (!(flags & kSolveBack)) return;
-    // back substitution L^T x = y, y = row nf of A
-    double* red = P;                    // [NS][PW]
-    double* L11 = red + NS * PW;        // [PW][PS]
-    double* xs = L11 + PW * PS;         // [nf]
-    const int lane = t & 63;
-    for (int k0 = ((nf - 1) / PW) * PW; k0 >= 0; k0 -= PW) {
-        const int nb = min(PW, nf - k0), cc = t % PW, sl = t / PW;
-        double v = 0.0;
-        if (cc < nb)
-            for (int r = k0 + nb + sl; r < nf; r += NS) v += A[(size_t)r * nf + k0 + cc] * xs[r];
-        red[sl * PW + cc] = v;
-        for (int e = t; e < nb * nb; e += T) {
-            const int r = e / nb, c = e - r * nb;
-            if (c <= r) L11[r * PS + c] = A[(size_t)(k0 + r) * nf + k0 + c];
-        }
-        __syncthreads();
-        if (t < 64) {
-            double w = 0.0;
-            if (lane < nb) {
-                w = A[(size_t)nf * nf + k0 + lane];
-                for (int q = 0; q < NS; ++q) w -= red[q * PW + lane];
-            }
-            for (int q = nb - 1; q >= 0; --q) {
-                const double xq = lane_bcast(w / L11[q * PS + q], q);
-                if (lane == q) w = xq;
-                else if (lane < q) w -= L11[q * PS + lane] * xq;
-            }
-            if (lane < nb) xs[k0 + lane] = w;
-        }
-        __syncthreads();
-    }
-    for (int e = t; e < n6; e += T) dpose[e] = 0.0;
-    __syncthreads();
-    for (int r = t; r < nf; r += T) dpose[free_param(r, gauge_axis)] = xs[r];
+// 1 / sqrt(d) to the last place or two: the hardware's estimate and one
+// third-order correction.
+__device__ __forceinline__ double inv_sqrt(double d) {
+    const double y = __builtin_amdgcn_rsq(d);
+    const double e = fma(-(d * y), y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
-// Trailing update after panel k0 over many workgroups: one 32 x 32 tile of
-// the lower triangle of rows k0 + nb .. nf (the right-hand side row last)
-// and columns k0 + nb .. nf - 1 per workgroup, A_ij -= sum_p L_ip L_jp with
-// the panel's columns of both row ranges staged in LDS; each thread a 2 x 2
-// block, the sum over p in order.
-constexpr int kSyrkTile = 32;
+// Inverse of the Cholesky factor of the 32 x 32 block D (lower triangle,
+// row stride kPS, in LDS), by one wave in registers: lane r < 32 eliminates row
+// r, lane 32 + c carries column c of the identity through the same steps, and
+// both multiply by the same column of L.  The next pivot's entry goes from
+// lane to lane through scalar registers, so that the chain of pivots is a
+// reciprocal root and three products a step; the rest of the column is read
+// back from LDS (col, 32 x 32) in its shadow.  Row-major to inv.
+__device__ __forceinline__ void invert_factor(const double* D, double* col, double* __restrict__ inv, int lane) {
+    double v[kPW];
+    const int r = lane & 31;
+    const bool low = lane < 32;
+#pragma unroll
+    for (int c = 0; c < kPW; ++c) v[c] = low ? D[r * kPS + c] : (c == r ? 1.0 : 0.0);
+    double pivot = read_lane_f64(v[0], 0);
+#pragma unroll
+    for (int p = 0; p < kPW; ++p) {
+        const double m = v[p] * inv_sqrt(pivot);
+        v[p] = m;
+        if (p + 1 < kPW) {
+            v[p + 1] = fma(-m, read_lane_f64(m, p + 1), v[p + 1]);
+            pivot = read_lane_f64(v[p + 1], p + 1);
+        }
+        if (p + 2 < kPW) {
+            if (low) col[p * kPW + r] = m;
+            wave_sync();
+#pragma unroll
+            for (int c = p + 2; c < kPW; ++c) v[c] = fma(-m, col[p * kPW + c], v[c]);
+        }
+    }
+    if (!low) {
+#pragma unroll
+        for (int c = 0; c < kPW; ++c) inv[c * kPW + r] = v[c];
+    }
+}
 
-template <int PW>
-__global__ __launch_bounds__(256) void k_ba_syrk(int nf, int k0, double* __restrict__ A) {
-    __shared__ double Li[kSyrkTile][PW + 1], Lj[kSyrkTile][PW + 1];
-    const int t = threadIdx.x, nb = min(PW, nf - k0), r0 = k0 + nb;
-    const int mt = nf + 1 - r0, mc = nf - r0;
-    const int e = (int)blockIdx.x;
+// The first panel's diagonal block (identity past nf).
+__global__ __launch_bounds__(64) void k_ba_first(int nf, const double* __restrict__ A, double* __restrict__ inv) {
+    __shared__ __align__(16) double D[kPW * kPS], col[kPW * kPW];
+    for (int e = threadIdx.x; e < kPW * kPW; e += 64) {
+        const int r = e / kPW, c = e % kPW;
+        D[r * kPS + c] = r < nf && c <= r ? A[(size_t)r * nf + c] : (r == c ? 1.0 : 0.0);
+    }
+    __syncthreads();
+    invert_factor(D, col, inv, threadIdx.x);
+}
+
+// Thread (ty, tx) of a 16 x 16 grid: rows 2 ty, 2 ty + 1 of X times rows
+// 2 tx, 2 tx + 1 of Y (32 columns each).
+__device__ __forceinline__ void tile_product(const double* X, const double* Y, int ty, int tx, double (&o)[2][2]) {
+    o[0][0] = o[0][1] = o[1][0] = o[1][1] = 0.0;
+#pragma unroll 8
+    for (int p = 0; p < kPW; ++p) {
+        const double a0 = X[2 * ty * kPS + p], a1 = X[(2 * ty + 1) * kPS + p];
+        const double b0 = Y[2 * tx * kPS + p], b1 = Y[(2 * tx + 1) * kPS + p];
+        o[0][0] = fma(a0, b0, o[0][0]);
+        o[0][1] = fma(a0, b1, o[0][1]);
+        o[1][0] = fma(a1, b0, o[1][0]);
+        o[1][1] = fma(a1, b1, o[1][1]);
+    }
+}
+
+// Panel k0: tile e of the lower triangle of rows k0 + 32 .. nf (the
+// right-hand side last).  L gets the panel's rows below its diagonal block.
+__global__ __launch_bounds__(256) void k_ba_panel(int nf, int k0, double* __restrict__ A, double* __restrict__ L,
+                                                  double* __restrict__ invs) {
+    __shared__ __align__(16) double I[kPW * kPS], X[kPW * kPS], Y[kPW * kPS];
+    const int t = threadIdx.x, nb = min(kPW, nf - k0), r0 = k0 + nb;
+    const int mt = nf + 1 - r0, mc = nf - r0;  // rows and columns left
     int ti = 0;
-    while ((ti + 1) * (ti + 2) / 2 <= e) ++ti;
-    const int tj = e - ti * (ti + 1) / 2, i0 = ti * kSyrkTile, j0 = tj * kSyrkTile;
-    if (j0 >= mc) return;
-    for (int q = t; q < kSyrkTile * nb; q += 256) {
-        const int r = q / nb, p = q - r * nb;
-        Li[r][p] = i0 + r < mt ? A[(size_t)(r0 + i0 + r) * nf + k0 + p] : 0.0;
-        Lj[r][p] = j0 + r < mc ? A[(size_t)(r0 + j0 + r) * nf + k0 + p] : 0.0;
+    while ((ti + 1) * (ti + 2) / 2 <= (int)blockIdx.x) ++ti;
+    const int tj = (int)blockIdx.x - ti * (ti + 1) / 2, i0 = ti * kPW, j0 = tj * kPW;
+    if (tj > 0 && j0 >= mc) return;
+    const double* inv = invs + (size_t)(k0 / kPW) * kPW * kPW;
+    for (int q = t; q < kPW * kPW; q += 256) {
+        const int r = q / kPW, p = q % kPW;
+        I[r * kPS + p] = inv[q];
+        X[r * kPS + p] = i0 + r < mt && p < nb ? A[(size_t)(r0 + i0 + r) * nf + k0 + p] : 0.0;
+        Y[r * kPS + p] = j0 + r < mc && p < nb ? A[(size_t)(r0 + j0 + r) * nf + k0 + p] : 0.0;
     }
     __syncthreads();
     const int ty = t >> 4, tx = t & 15;
-    double acc[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
-    for (int p = 0; p < nb; ++p) {
-        const double a0 = Li[2 * ty][p], a1 = Li[2 * ty + 1][p], b0 = Lj[2 * tx][p], b1 = Lj[2 * tx + 1][p];
-        acc[0][0] = fma(a0, b0, acc[0][0]);
-        acc[0][1] = fma(a0, b1, acc[0][1]);
-        acc[1][0] = fma(a1, b0, acc[1][0]);
-        acc[1][1] = fma(a1, b1, acc[1][1]);
-    }
+    double li[2][2], lj[2][2];
+    tile_product(X, I, ty, tx, li);
+    tile_product(Y, I, ty, tx, lj);
+    __syncthreads();
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
         for (int v = 0; v < 2; ++v) {
-            const int ii = i0 + 2 * ty + u, jj = j0 + 2 * tx + v;
-            if (ii < mt && jj < mc && jj <= ii) A[(size_t)(r0 + ii) * nf + r0 + jj] -= acc[u][v];
+            const int r = 2 * ty + u, c = 2 * tx + v;
+            X[r * kPS + c] = li[u][v];
+            Y[r * kPS + c] = lj[u][v];
+            if (tj == 0 && i0 + r < mt && c < nb) L[(size_t)(r0 + i0 + r) * nf + k0 + c] = li[u][v];
         }
+    if (mc == 0) return;  // the last panel: only the right-hand side's row is left
+    __syncthreads();
+    double o[2][2];
+    tile_product(X, Y, ty, tx, o);
+    const bool next = blockIdx.x == 0;  // the next panel's diagonal block
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+            const int r = 2 * ty + u, c = 2 * tx + v, ii = i0 + r, jj = j0 + c;
+            double w = 0.0;
+            if (ii < mt && jj < mc && jj <= ii) {
+                double* at = A + (size_t)(r0 + ii) * nf + r0 + jj;
+                w = *at - o[u][v];
+                *at = w;
+            }
+            if (next) I[r * kPS + c] = ii < mc && jj <= ii ? w : (r == c ? 1.0 : 0.0);
+        }
+    if (!next) return;
+    __syncthreads();
+    if (t < 64) invert_factor(I, X, invs + (size_t)(k0 / kPW + 1) * kPW * kPW, t);
 }
 
-__global__ __launch_bounds__(256) void k_ba_backsub(pgs_ba_problem pb, const double* __restrict__ obs_rec,
-                                                    const double* __restrict__ pt_rec,
-                                                    const double* __restrict__ dpose,
-                                                    double* __restrict__ dpoint) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+// Sum over each half of the wave, in every lane of the half.
+template <int CTRL>
+__device__ __forceinline__ double dpp_add_f64(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return v + __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ double half_sum(double v) {
+    v = dpp_add_f64<0x128>(v);  // rotations inside a row of 16 lanes
+    v = dpp_add_f64<0x124>(v);
+    v = dpp_add_f64<0x122>(v);
+    v = dpp_add_f64<0x121>(v);
+    const long long b = __double_as_longlong(v);
+    const uint32_t lo = (uint32_t)(b & 0xffffffffll), hi = (uint32_t)(b >> 32);
+    // rows 0 and 1, and 2 and 3, meet
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __longlong_as_double(((long long)h[0] << 32) | l[0]) + __longlong_as_double(((long long)h[1] << 32) | l[1]);
+}
+
+// Back substitution L^T x = y, y = row nf of L, by one workgroup, panels last
+// to first: x_p = L11^-T (y_p - sum over the rows below of L^T x).  Thread
+// (slice, column) sums the column's products with the solved entries over
+// every 32nd row below the panel, whose factors are loaded a panel ahead (they
+// do not depend on x); the slices meet through LDS, each half wave adding one
+// column's, and the same halves form the product with the inverse.  The step
+// is scattered to the free pose entries; the fixed ones are 0.
+constexpr int kBackRows = (6 * PGS_BA_MAX_CAMS + kPW - 1) / kPW;  // rows per slice at most
+
+__global__ __launch_bounds__(kSolveThreads) void k_ba_back(int n_cams, int gauge_axis, const double* __restrict__ L,
+                                                           const double* __restrict__ invs,
+                                                           double* __restrict__ dpose) {
+    __shared__ double red[kPW][kPS], xs[6 * PGS_BA_MAX_CAMS], z[kPW];
+    const int n6 = 6 * n_cams, nf = n6 - 7, t = threadIdx.x, cc = t % kPW, sl = t / kPW;
+    const int last = (nf - 1) / kPW, rows = (nf + kPW - 1) / kPW;
+    double f[kBackRows], iv, y;
+    auto fetch = [&](int pn) {
+        const int k0 = pn * kPW, nb = min(kPW, nf - k0), r0 = k0 + nb;
+        iv = y = 0.0;
+        if (pn < 0) return;  // uniform
+#pragma unroll
+        for (int q = 0; q < kBackRows; ++q)
+            if (q < rows) {
+                const int r = r0 + sl + q * kPW;
+                f[q] = cc < nb && r < nf ? L[(size_t)r * nf + k0 + cc] : 0.0;
+            }
+        // row cc, column sl of the inverse; the right-hand side's entry sl
+        iv = invs[(size_t)pn * kPW * kPW + cc * kPW + sl];
+        y = sl < nb ? L[(size_t)nf * nf + k0 + sl] : 0.0;
+    };
+    for (int e = t; e < 6 * PGS_BA_MAX_CAMS; e += kSolveThreads) xs[e] = 0.0;
+    fetch(last);
+    __syncthreads();
+    for (int pn = last; pn >= 0; --pn) {
+        const int k0 = pn * kPW, r0 = min(k0 + kPW, nf);
+        double v = 0.0;
+#pragma unroll
+        for (int q = 0; q < kBackRows; ++q)
+            if (q < rows) {
+                const int r = r0 + sl + q * kPW;
+                if (r < nf) v = fma(f[q], xs[r], v);
+            }
+        red[sl][cc] = v;
+        const double iw = iv, yy = y;
+        fetch(pn - 1);
+        __syncthreads();
+        // column sl: its slices' sums, one per lane of the half
+        const double w = yy - half_sum(red[cc][sl]);
+        if (cc == 0) z[sl] = w;
+        __syncthreads();
+        const double x = half_sum(iw * z[cc]);  // (L11^-T z)_sl = sum over q of inv[q][sl] z[q]
+        if (cc == 0 && k0 + sl < nf) xs[k0 + sl] = x;
+        __syncthreads();
+    }
+    for (int e = t; e < n6; e += kSolveThreads) {
+        const int r = free_index(e, gauge_axis);
+        dpose[e] = r >= 0 ? xs[r] : 0.0;
+    }
+}
+
+__global__ __launch_bounds__(kPointThreads) void k_ba_backsub(pgs_ba_problem pb, const double* __restrict__ rot,
+                                                              const double* __restrict__ centre,
+                                                              const double* __restrict__ pts,
+                                                              const double* __restrict__ pt_rec,
+                                                              const double* __restrict__ dpose,
+                                                              double* __restrict__ dpoint) {
+    extern __shared__ double cam[];
+    load_cams(pb, rot, centre, cam);
+    __syncthreads();
+    const int j = blockIdx.x * kPointThreads + threadIdx.x;
     if (j >= pb.n_points) return;
-    double s[3] = {0, 0, 0};
+    double P[3], s[3] = {0, 0, 0};
+    load_point(pts, j, P);
     for (uint32_t o = pb.point_start_dev[j]; o < pb.point_start_dev[j + 1]; ++o) {
-        const double* Htp = obs_rec + (size_t)o * kObsRec;
-        const double* dt = dpose + 6 * (size_t)pb.obs_cam_dev[o];
-        for (int b = 0; b < 3; ++b)
-            for (int a = 0; a < 6; ++a) s[b] += Htp[3 * a + b] * dt[a];
+        const uint32_t i = pb.obs_cam_dev[o];
+        Obs ob;
+        observe(pb, cam + i * kCamRec, P, pb.obs_uv_dev[2 * (size_t)o], pb.obs_uv_dev[2 * (size_t)o + 1], ob);
+        const double* dt = dpose + 6 * (size_t)i;
+        double d0 = 0.0, d1 = 0.0;  // Jt dt
+        for (int a = 0; a < 6; ++a) {
+            d0 += ob.Jt[0][a] * dt[a];
+            d1 += ob.Jt[1][a] * dt[a];
+        }
+        for (int b = 0; b < 3; ++b) s[b] += ob.w * (ob.Jp[0][b] * d0 + ob.Jp[1][b] * d1);
     }
     const double* pr = pt_rec + (size_t)j * kPtRec;
     for (int a = 0; a < 3; ++a)
@@ -499,11 +626,17 @@ __global__ __launch_bounds__(kCostThreads) void k_ba_cost(pgs_ba_problem pb, con
                                                           const double* __restrict__ pts,
                                                           double* __restrict__ part) {
     __shared__ double s[kCostThreads];
+    extern __shared__ double cam[];
+    load_cams(pb, rot, centre, cam);
+    __syncthreads();
     double acc = 0.0;
     for (int j = blockIdx.x * kCostThreads + threadIdx.x; j < pb.n_points; j += gridDim.x * kCostThreads) {
+        double P[3];
+        load_point(pts, j, P);
         for (uint32_t o = pb.point_start_dev[j]; o < pb.point_start_dev[j + 1]; ++o) {
             Obs ob;
-            observe(pb, rot, centre, pts, (int)o, j, ob);
+            observe(pb, cam + pb.obs_cam_dev[o] * kCamRec, P, pb.obs_uv_dev[2 * (size_t)o],
+                    pb.obs_uv_dev[2 * (size_t)o + 1], ob);
             const double q = ob.r[0] * ob.r[0] + ob.r[1] * ob.r[1];
             const double n = sqrt(q);
             acc += n <= pb.huber_delta ? q : 2.0 * pb.huber_delta * n - pb.huber_delta * pb.huber_delta;
@@ -518,12 +651,20 @@ __global__ __launch_bounds__(kCostThreads) void k_ba_cost(pgs_ba_problem pb, con
     if (threadIdx.x == 0) part[blockIdx.x] = s[0];
 }
 
-__global__ void k_ba_cost_final(const double* __restrict__ part, int n, double* __restrict__ out) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        double acc = 0.0;
-        for (int k = 0; k < n; ++k) acc += part[k];
-        *out = acc;
+// The blocks' sums, added in a fixed order (one thread alone took 20 us over
+// 386 of them).
+__global__ __launch_bounds__(kCostThreads) void k_ba_cost_final(const double* __restrict__ part, int n,
+                                                                double* __restrict__ out) {
+    __shared__ double s[kCostThreads];
+    double acc = 0.0;
+    for (int k = threadIdx.x; k < n; k += kCostThreads) acc += part[k];
+    s[threadIdx.x] = acc;
+    __syncthreads();
+    for (int k = kCostThreads / 2; k > 0; k >>= 1) {
+        if (threadIdx.x < k) s[threadIdx.x] += s[threadIdx.x + k];
+        __syncthreads();
     }
+    if (threadIdx.x == 0) *out = s[0];
 }
 
 __global__ __launch_bounds__(256) void k_ba_apply(int n_cams, int n_points, const double* __restrict__ rot,
@@ -766,7 +907,7 @@ __global__ __launch_bounds__(256) void k_compact_obs(pgs_ba_problem pb, const ui
 
 // Workspace layout of one problem size.
 struct BaWs {
-    double *obs_rec, *pt_rec, *cam_part, *S, *g, *A, *part;
+    double *pt_rec, *cam_part, *A, *L, *invs, *part;
     size_t bytes;
 };
 
@@ -774,57 +915,40 @@ inline size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 constexpr int kCostBlocks = 1024;
 
 BaWs ba_layout(void* base, int C, int M, int O) {
+    (void)O;
     BaWs w{};
     char* p = static_cast<char*>(base);
     size_t off = 0;
     const size_t n6 = 6 * (size_t)C, nf = n6 > 7 ? n6 - 7 : 0;
     auto take = [&](size_t n) { double* q = reinterpret_cast<double*>(p + off); off += al(n * 8); return q; };
-    w.obs_rec = take((size_t)O * kObsRec);
     w.pt_rec = take((size_t)M * kPtRec);
-    w.cam_part = take((size_t)C * kCamSplit * (6 * n6 + 6));
-    w.S = take(n6 * n6);
-    w.g = take(n6);
+    w.cam_part = take((size_t)C * kCamSplit * (36 * (size_t)C + kPose));
     w.A = take((nf + 1) * nf);
+    w.L = take((nf + 1) * nf);
+    w.invs = take(((nf + kPW - 1) / kPW) * kPW * kPW);
     w.part = take(kCostBlocks);
     w.bytes = off;
     return w;
 }
 
-// Panel width of the solve and its LDS: the panel's nf + 1 rows padded to
-// PW + 1 doubles (32 columns up to nf = 400: at most 106 KB; 16 beyond, up
-// to nf = 6 PGS_BA_MAX_CAMS - 7: about 104 KB).
-constexpr int kSolveWide = 400;
-template <int PW>
-inline size_t solve_lds(int nf) {
-    const size_t panel = (size_t)(nf + 1) * (PW + 1), back = (size_t)kSolveThreads + PW * (PW + 1) + nf;
-    return (2 * PW + 2 + (panel > back ? panel : back)) * sizeof(double);
-}
-template <int PW>
-bool solve_lds_reserved(int nf) {
-    static const bool ok = hipFuncSetAttribute(reinterpret_cast<const void*>(k_ba_solve<PW>),
+inline size_t cams_lds(int C) { return (size_t)C * kCamRec * sizeof(double); }
+
+bool cameras_lds_reserved() {
+    static const bool ok = hipFuncSetAttribute(reinterpret_cast<const void*>(k_ba_cameras),
                                                hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               (int)solve_lds<PW>(PW == 32 ? kSolveWide : 6 * PGS_BA_MAX_CAMS - 7)) ==
-                           hipSuccess;
-    return ok && solve_lds<PW>(nf) <= solve_lds<PW>(PW == 32 ? kSolveWide : 6 * PGS_BA_MAX_CAMS - 7);
+                                               (int)cameras_lds(PGS_BA_MAX_CAMS)) == hipSuccess;
+    return ok;
 }
 
-// The solve as a chain of launches: the gather and the first panel, then
-// per panel the trailing update over many workgroups and the next panel's
-// factorisation (one workgroup), then the back substitution.
-template <int PW>
+// The solve as a chain of launches, one per panel.
 void solve_panels(int C, int gauge_axis, const BaWs& w, double* dpose, hipStream_t s) {
     const int nf = 6 * C - 7;
-    const size_t lds = solve_lds<PW>(nf);
-    for (int k0 = 0; k0 < nf; k0 += PW) {
-        k_ba_solve<PW><<<1, kSolveThreads, lds, s>>>(C, gauge_axis, w.S, w.g, w.A, dpose, k0, k0 + PW,
-                                                     k0 == 0 ? kSolveGather : 0);
-        const int nb = min(PW, nf - k0), mt = nf + 1 - k0 - nb;
-        if (nf - k0 - nb > 0) {
-            const int tiles = (mt + kSyrkTile - 1) / kSyrkTile;
-            k_ba_syrk<PW><<<tiles * (tiles + 1) / 2, 256, 0, s>>>(nf, k0, w.A);
-        }
+    k_ba_first<<<1, 64, 0, s>>>(nf, w.A, w.invs);
+    for (int k0 = 0; k0 < nf; k0 += kPW) {
+        const int mt = nf + 1 - min(k0 + kPW, nf), tiles = (mt + kPW - 1) / kPW;
+        k_ba_panel<<<tiles * (tiles + 1) / 2, 256, 0, s>>>(nf, k0, w.A, w.L, w.invs);
     }
-    k_ba_solve<PW><<<1, kSolveThreads, lds, s>>>(C, gauge_axis, w.S, w.g, w.A, dpose, nf, nf, kSolveBack);
+    k_ba_back<<<1, kSolveThreads, 0, s>>>(C, gauge_axis, w.L, w.invs, dpose);
 }
 
 pgs_status check_problem(const pgs_ba_problem* pb, const char* who) {
@@ -855,8 +979,9 @@ extern "C" pgs_status pgs_ba_cost(const pgs_ba_problem* problem, const double* r
     PGS_REQUIRE(workspace_bytes >= w.bytes, "pgs_ba_cost: workspace %zu < %zu", workspace_bytes, w.bytes);
     hipStream_t s = pgs::as_stream(stream);
     const int blocks = min(kCostBlocks, (problem->n_points + kCostThreads - 1) / kCostThreads);
-    k_ba_cost<<<blocks, kCostThreads, 0, s>>>(*problem, rot_dev, centre_dev, points_dev, w.part);
-    k_ba_cost_final<<<1, 64, 0, s>>>(w.part, blocks, cost_dev);
+    k_ba_cost<<<blocks, kCostThreads, cams_lds(problem->n_cams), s>>>(*problem, rot_dev, centre_dev, points_dev,
+                                                                     w.part);
+    k_ba_cost_final<<<1, kCostThreads, 0, s>>>(w.part, blocks, cost_dev);
     PGS_CHECK_LAUNCH("pgs_ba_cost");
     return PGS_OK;
 }
@@ -872,21 +997,16 @@ extern "C" pgs_status pgs_ba_step(const pgs_ba_problem* problem, const double* r
     const BaWs w = ba_layout(workspace_dev, C, M, problem->n_obs);
     PGS_REQUIRE(workspace_bytes >= w.bytes, "pgs_ba_step: workspace %zu < %zu", workspace_bytes, w.bytes);
     hipStream_t s = pgs::as_stream(stream);
-    k_ba_points<<<(M + 255) / 256, 256, 0, s>>>(*problem, rot_dev, centre_dev, points_dev, lambda, w.obs_rec,
-                                                w.pt_rec);
-    const size_t lds = (size_t)(6 * 6 * C + (kCamThreads / 64) * 27 + 6) * sizeof(double);
-    k_ba_cameras<<<dim3(C, kCamSplit), kCamThreads, lds, s>>>(*problem, lambda, w.obs_rec, w.pt_rec, w.cam_part);
-    const size_t rows = (size_t)C * (36 * C + 6);
-    k_ba_rows<<<(unsigned)((rows + 255) / 256), 256, 0, s>>>(C, w.cam_part, w.S, w.g);
-    const int nf = 6 * C - 7;
-    if (nf <= kSolveWide) {
-        PGS_REQUIRE(solve_lds_reserved<32>(nf), "pgs_ba_step: cannot reserve LDS for the solve");
-        solve_panels<32>(C, problem->gauge_axis, w, dpose_dev, s);
-    } else {
-        PGS_REQUIRE(solve_lds_reserved<16>(nf), "pgs_ba_step: cannot reserve LDS for the solve");
-        solve_panels<16>(C, problem->gauge_axis, w, dpose_dev, s);
-    }
-    k_ba_backsub<<<(M + 255) / 256, 256, 0, s>>>(*problem, w.obs_rec, w.pt_rec, dpose_dev, dpoint_dev);
+    PGS_REQUIRE(cameras_lds_reserved(), "pgs_ba_step: cannot reserve LDS for the camera rows");
+    const int pblocks = (M + kPointThreads - 1) / kPointThreads;
+    k_ba_points<<<pblocks, kPointThreads, cams_lds(C), s>>>(*problem, rot_dev, centre_dev, points_dev, lambda,
+                                                            w.pt_rec);
+    k_ba_cameras<<<dim3(C, kCamSplit), kCamThreads, cameras_lds(C), s>>>(*problem, rot_dev, centre_dev, points_dev,
+                                                                         w.pt_rec, w.cam_part);
+    k_ba_rows<<<dim3((36 * C + 6 + 255) / 256, C), 256, 0, s>>>(C, problem->gauge_axis, lambda, w.cam_part, w.A);
+    solve_panels(C, problem->gauge_axis, w, dpose_dev, s);
+    k_ba_backsub<<<pblocks, kPointThreads, cams_lds(C), s>>>(*problem, rot_dev, centre_dev, points_dev, w.pt_rec,
+                                                             dpose_dev, dpoint_dev);
     PGS_CHECK_LAUNCH("pgs_ba_step");
     return PGS_OK;
 }

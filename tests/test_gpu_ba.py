@@ -195,3 +195,35 @@ def test_refine_loop_removes_outliers_and_converges():
     assert np.sqrt((r * r).sum(1)).max() < 4.0 * 3
     rot_err = np.degrees(np.arccos(np.clip((np.einsum("cij,cij->c", R, tr["R_true"]) - 1) / 2, -1, 1)))
     assert np.median(rot_err) < 0.01
+
+
+@pytest.mark.parametrize("n_cams,n_points,max_views,twice", [
+    (2, 40, 8, False), (3, 50, 8, False), (7, 60, 8, True), (12, 90, 12, False), (17, 90, 17, True), (40, 60, 40, True)])
+def test_ba_step_panel_and_track_sizes(n_cams, n_points, max_views, twice):
+    # the solve's panels (5 to 233 free parameters: one panel and several, the
+    # last one to 31 columns wide), tracks shorter and longer than the
+    # members listed at a time, and points seen twice by one camera: the step
+    # against the oracle's dense solve and in its normal equations
+    ba, tr, _, _ = _setup(11, n_cams=n_cams, n_points=n_points, max_views=max_views)
+    if twice:
+        # every third observation again, half a pixel away
+        reps = 1 + (np.arange(tr["obs_cam"].size) % 3 == 0)
+        uv = np.repeat(tr["obs_uv"], reps, axis=0)
+        again = np.r_[False, np.repeat(np.arange(reps.size), reps)[1:] == np.repeat(np.arange(reps.size), reps)[:-1]]
+        uv[again] += 0.5
+        tr = dict(tr, obs_cam=np.repeat(tr["obs_cam"], reps), obs_pt=np.repeat(tr["obs_pt"], reps), obs_uv=uv)
+    pb = ba.BAProblem.from_tracks(tr, huber_delta=DELTA)
+    st = ba.state(tr["R0"], tr["c0"], tr["P0"])
+    lam = 1e-2
+    dpose, dpoint = ba.step(pb, st, lam)
+    gp, gq = dpose.cpu().numpy(), dpoint.cpu().numpy()
+    op, oq = oba.lm_step(tr, tr["R0"], tr["c0"], tr["P0"], DELTA, lam)
+    scale = max(np.abs(op).max(), np.abs(oq).max())
+    np.testing.assert_allclose(gp, op, rtol=0, atol=1e-6 * scale)
+    np.testing.assert_allclose(gq, oq, rtol=0, atol=1e-6 * scale)
+    H, b = oba.normal_equations(tr, tr["R0"], tr["c0"], tr["P0"], DELTA)
+    free = np.r_[oba.free_pose_params(n_cams, tr["gauge_axis"]), 6 * n_cams + np.arange(gq.size)]
+    A = H[np.ix_(free, free)]
+    x = np.r_[gp.ravel(), gq.ravel()][free]
+    res = (A + lam * np.diag(np.diag(A))) @ x - b[free]
+    assert np.abs(res).max() <= 1e-10 * np.abs(b[free]).max()
