@@ -14,8 +14,8 @@
 //            an equal range of pairs (binary search over the offsets), so
 //            large Gaussians do not serialise
 //   sort     stable LSD radix sort on the tile bits only, 8-bit digits;
-//            every pass is histogram -> device scan of the digit-major
-//            histogram -> stable scatter
+//            every pass is histogram -> stable scatter, sorts of more than
+//            2^20 keys with a device scan of the histogram in between
 //   ranges   per-tile [start, end)
 //
 // Every kernel reads the item and pair counts from device memory and is
@@ -31,13 +31,22 @@ constexpr int kScanThreads = 256;
 constexpr int kScanIpt = 8;
 constexpr int kScanItems = kScanThreads * kScanIpt;  // 2048 per block
 
-constexpr int kSortThreads = 256;  // 256 keys per round
-// Rounds per workgroup: 8 (2048 keys) for large sorts; 4 (1024 keys) for
-// sorts of at most kSmallSort keys, which would otherwise run on too few
-// workgroups to fill the chip.
-constexpr int kSortRoundsLarge = 8;
-constexpr int kSortRoundsSmall = 4;
+// Workgroups of a sort.  Up to kSmallSort keys: 4096 keys on 1024 threads, so
+// that at most 256 workgroups exist and each can sum the histograms of the
+// others itself (k_radix_scatter); a pass is two launches, where the scan
+// between histogram and scatter made it four of about 4.5 us each whatever
+// they move.  Beyond: 2048 keys on 256 threads and the scan.
 constexpr uint32_t kSmallSort = 1u << 20;
+struct SmallSort {
+    static constexpr int kThreads = 1024, kRounds = 4, kKeys = kThreads * kRounds;
+    static constexpr bool kDirect = true;
+};
+struct LargeSort {
+    static constexpr int kThreads = 256, kRounds = 8, kKeys = kThreads * kRounds;
+    static constexpr bool kDirect = false;
+};
+// Gaussians that one workgroup sorts and scans by itself.
+constexpr uint32_t kBlockSort = 4096;
 constexpr int kRadix = 256;
 
 inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -139,56 +148,68 @@ __global__ void k_clear_u32(uint32_t* __restrict__ p, uint32_t n) {
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0;
 }
 
+// Where the histogram of digit d in workgroup b goes: block-major (a row of 256
+// per workgroup) for sorts that sum rows themselves, else digit-major, so that
+// one exclusive scan yields every workgroup's output offset for every digit.
+template <class G>
+__device__ __forceinline__ size_t hist_at(uint32_t d, uint32_t b, uint32_t nb) {
+    return G::kDirect ? (size_t)b * kRadix + d : (size_t)d * nb + b;
+}
+
+__device__ __forceinline__ uint32_t depth_key(const float* __restrict__ proj_all,
+                                              const uint32_t* __restrict__ touched_all, uint32_t i) {
+    // the record's depth is read only for items with pairs (one 4-byte read
+    // per 64-byte record, so culled items cost a line)
+    return touched_all[i] ? __float_as_uint(proj_all[(size_t)i * PGS_PROJ_STRIDE + PGS_PROJ_DEPTH]) : 0xffffffffu;
+}
+
 // Depth keys of every item (float32 depth bits; culled items sort last),
 // values = item index, the item count for the depth sort, and the first
-// radix pass's digit histogram: workgroup b takes the same 256 R items as
-// the sort's workgroup b, so it writes its column of the digit-major
-// histogram itself.  Also clears the tile ranges and the pair count.
-template <int R>
-__global__ __launch_bounds__(kSortThreads) void k_depth_keys(uint32_t items, int n,
-                                                             const float* __restrict__ proj_all,
-                                                             const uint32_t* __restrict__ touched_all,
-                                                             uint32_t* __restrict__ dkeys,
-                                                             uint32_t* __restrict__ dvals,
-                                                             uint32_t* __restrict__ count, uint32_t nb,
-                                                             uint32_t* __restrict__ hist,
-                                                             uint32_t* __restrict__ ranges, uint32_t n_ranges,
-                                                             uint32_t* __restrict__ num_pairs) {
+// radix pass's digit histogram: workgroup b takes the same items as the
+// sort's workgroup b.  Also clears the tile ranges and the pair count.
+template <class G>
+__global__ __launch_bounds__(G::kThreads) void k_depth_keys(uint32_t items, const float* __restrict__ proj_all,
+                                                            const uint32_t* __restrict__ touched_all,
+                                                            uint32_t* __restrict__ dkeys,
+                                                            uint32_t* __restrict__ dvals,
+                                                            uint32_t* __restrict__ count, uint32_t nb,
+                                                            uint32_t* __restrict__ hist,
+                                                            uint32_t* __restrict__ ranges, uint32_t n_ranges,
+                                                            uint32_t* __restrict__ num_pairs) {
+    constexpr int NT = G::kThreads;
     __shared__ uint32_t h[kRadix];
     const int t = threadIdx.x;
     if (blockIdx.x == 0 && t == 0) {
         *count = items;
         *num_pairs = 0u;
     }
-    for (uint32_t i = blockIdx.x * kSortThreads + t; i < n_ranges; i += gridDim.x * kSortThreads) ranges[i] = 0u;
-    h[t] = 0u;
+    for (uint32_t i = blockIdx.x * NT + t; i < n_ranges; i += gridDim.x * NT) ranges[i] = 0u;
+    if (t < kRadix) h[t] = 0u;
     __syncthreads();
-    const uint32_t base = blockIdx.x * kSortThreads * R;
+    const uint32_t base = blockIdx.x * G::kKeys;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const uint32_t i = base + r * kSortThreads + t;
+    for (int r = 0; r < G::kRounds; ++r) {
+        const uint32_t i = base + r * NT + t;
         if (i < items) {
-            // the record's depth is read only for items with pairs (one
-            // 4-byte read per 64-byte record, so culled items cost a line)
-            uint32_t key = 0xffffffffu;
-            if (touched_all[i]) key = __float_as_uint(proj_all[(size_t)i * PGS_PROJ_STRIDE + PGS_PROJ_DEPTH]);
+            const uint32_t key = depth_key(proj_all, touched_all, i);
             dkeys[i] = key;
             dvals[i] = i;
             atomicAdd(&h[key & 0xffu], 1u);
         }
     }
     __syncthreads();
-    hist[(size_t)t * nb + blockIdx.x] = h[t];
+    if (t < kRadix) hist[hist_at<G>(t, blockIdx.x, nb)] = h[t];
 }
 
 // Pairs of the items in depth order.  Workgroup b fills pairs
-// [256 R b, 256 R (b + 1)), the range of the pair sort's workgroup b: one
-// binary search over the scanned counts finds the item of its first pair;
-// every item of the range has at least one pair (empty items share their
-// successor's offset), so the range spans at most 256 R items, whose offsets
-// go to LDS; each thread then finds its pairs' items there.  The work per
-// workgroup is even however unevenly the rectangles are sized.  Each
-// workgroup also writes its column of the pair sort's first digit-major
+// [G::kKeys b, G::kKeys (b + 1)), the range of the pair sort's workgroup b: a
+// search over the scanned counts finds the item of its first pair (one wave,
+// 64 probes a step: a binary search's 19 dependent reads were a third of the
+// kernel at 300k items); every item of the range has at least one pair (empty
+// items share their successor's offset), so the range spans at most G::kKeys
+// items, whose offsets go to LDS; each thread then finds its pairs' items
+// there.  The work per workgroup is even however unevenly the rectangles are
+// sized.  Each workgroup also writes its part of the pair sort's first
 // histogram (the tile's low 8 bits), zeros past the pair count.
 
 __device__ __forceinline__ uint32_t last_le(const uint32_t* off, uint32_t n, uint32_t p) {
@@ -201,18 +222,33 @@ __device__ __forceinline__ uint32_t last_le(const uint32_t* off, uint32_t n, uin
     return lo;
 }
 
-template <int R>
-__global__ __launch_bounds__(kSortThreads) void k_emit_sorted(uint32_t items, int n, EmitViews ev,
-                                                              const uint32_t* __restrict__ dkeys,
-                                                              const uint32_t* __restrict__ rect_all,
-                                                              const uint32_t* __restrict__ dvals,
-                                                              const uint32_t* __restrict__ off,
-                                                              const uint32_t* __restrict__ num_pairs,
-                                                              uint32_t capacity, uint64_t* __restrict__ keys,
-                                                              uint32_t* __restrict__ values,
-                                                              uint32_t* __restrict__ flags, uint32_t nb,
-                                                              uint32_t* __restrict__ hist) {
-    constexpr uint32_t kPairs = kSortThreads * R;
+// The same by a whole wave: each step probes 64 evenly spaced positions of
+// [lo, lo + n) and keeps the stretch from the last one not past p.
+__device__ __forceinline__ uint32_t wave_last_le(const uint32_t* __restrict__ off, uint32_t n, uint32_t p, int lane) {
+    uint32_t lo = 0;
+    while (n > 1) {
+        const uint32_t step = (n + 63) >> 6, at = lane * step;
+        const uint64_t le = __ballot(at < n && off[lo + (at < n ? at : 0u)] <= p);
+        const uint32_t k = 63u - (uint32_t)__clzll((long long)le);  // lane 0 always holds
+        lo += k * step;
+        n = min(step, n - k * step);
+    }
+    return lo;
+}
+
+template <class G>
+__global__ __launch_bounds__(G::kThreads) void k_emit_sorted(uint32_t items, int n, EmitViews ev,
+                                                             const uint32_t* __restrict__ dkeys,
+                                                             const uint32_t* __restrict__ rect_all,
+                                                             const uint32_t* __restrict__ dvals,
+                                                             const uint32_t* __restrict__ off,
+                                                             const uint32_t* __restrict__ num_pairs,
+                                                             uint32_t capacity, uint64_t* __restrict__ keys,
+                                                             uint32_t* __restrict__ values,
+                                                             uint32_t* __restrict__ flags, uint32_t nb,
+                                                             uint32_t* __restrict__ hist) {
+    constexpr uint32_t kPairs = G::kKeys;
+    constexpr int NT = G::kThreads;
     __shared__ uint32_t s_off[kPairs + 1];
     __shared__ uint32_t s_first;
     __shared__ uint32_t h[kRadix];
@@ -221,16 +257,19 @@ __global__ __launch_bounds__(kSortThreads) void k_emit_sorted(uint32_t items, in
     if (blockIdx.x == 0 && t == 0 && total > capacity) atomicOr(flags, PGS_FLAG_PAIR_OVERFLOW);
     const uint32_t count = min(total, capacity);
     const uint32_t p0 = blockIdx.x * kPairs;
-    h[t] = 0u;
+    if (t < kRadix) h[t] = 0u;
     if (p0 < count) {  // uniform for the block
         const uint32_t p1 = min(p0 + kPairs, count);
-        if (t == 0) s_first = last_le(off, items, p0);
+        if (t < 64) {
+            const uint32_t j = wave_last_le(off, items, p0, t);
+            if (t == 0) s_first = j;
+        }
         __syncthreads();
         const uint32_t i0 = s_first;
         const uint32_t span = min(kPairs + 1, items - i0);
-        for (uint32_t q = t; q < span; q += kSortThreads) s_off[q] = off[i0 + q];
+        for (uint32_t q = t; q < span; q += NT) s_off[q] = off[i0 + q];
         __syncthreads();
-        for (uint32_t p = p0 + t; p < p1; p += kSortThreads) {
+        for (uint32_t p = p0 + t; p < p1; p += NT) {
             const uint32_t j = last_le(s_off, span, p);
             const uint32_t item = dvals[i0 + j], local = p - s_off[j];
             const uint32_t v = item / (uint32_t)n, g = item - v * (uint32_t)n;
@@ -249,7 +288,7 @@ __global__ __launch_bounds__(kSortThreads) void k_emit_sorted(uint32_t items, in
         }
     }
     __syncthreads();
-    if (blockIdx.x < nb) hist[(size_t)t * nb + blockIdx.x] = h[t];
+    if (blockIdx.x < nb && t < kRadix) hist[hist_at<G>(t, blockIdx.x, nb)] = h[t];
 }
 
 __device__ __forceinline__ uint32_t clamp_count(const uint32_t* num, uint32_t capacity) {
@@ -257,24 +296,23 @@ __device__ __forceinline__ uint32_t clamp_count(const uint32_t* num, uint32_t ca
     return c < capacity ? c : capacity;
 }
 
-// Digit histogram of each block's chunk of 256 R keys, stored digit-major
-// hist[d * nb + block] so that one exclusive scan yields every block's
-// output offset for every digit.
-template <int R, class K>
-__global__ __launch_bounds__(kSortThreads) void k_radix_hist(const K* __restrict__ keys,
-                                                             const uint32_t* __restrict__ num,
-                                                             uint32_t capacity, int shift, uint32_t nb,
-                                                             uint32_t* __restrict__ hist) {
+// Digit histogram of each workgroup's chunk of keys.
+template <class G, class K>
+__global__ __launch_bounds__(G::kThreads) void k_radix_hist(const K* __restrict__ keys,
+                                                            const uint32_t* __restrict__ num, uint32_t capacity,
+                                                            int shift, uint32_t nb, uint32_t* __restrict__ hist) {
+    constexpr int NT = G::kThreads, R = G::kRounds;
     __shared__ uint32_t h[kRadix];
     const uint32_t count = clamp_count(num, capacity);
-    h[threadIdx.x] = 0;
+    const uint32_t base = blockIdx.x * G::kKeys;
+    if (G::kDirect && base >= count) return;  // rows past the last key are not read
+    if (threadIdx.x < kRadix) h[threadIdx.x] = 0;
     __syncthreads();
-    const uint32_t base = blockIdx.x * kSortThreads * R;
     if (base < count) {
         uint32_t d[R];  // every load in flight before the first atomic
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const uint32_t idx = base + r * kSortThreads + threadIdx.x;
+            const uint32_t idx = base + r * NT + threadIdx.x;
             d[r] = idx < count ? (uint32_t)(keys[idx] >> shift) & 0xffu : kRadix;
         }
 #pragma unroll
@@ -282,88 +320,162 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_hist(const K* __restrict
             if (d[r] < kRadix) atomicAdd(&h[d[r]], 1u);
     }
     __syncthreads();
-    hist[(size_t)threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
+    if (threadIdx.x < kRadix) hist[hist_at<G>(threadIdx.x, blockIdx.x, nb)] = h[threadIdx.x];
 }
 
-// Stable scatter through LDS.  The block's digit counts are the differences
-// of consecutive entries of the scanned digit-major histogram (the last
-// entry's successor is the key count).  Each round handles 256 consecutive
-// keys; a key's position inside the block is (the digit's start in the
-// block) + (keys of its digit already placed) + (same digit in lower waves
-// of this round) + (same digit in lower lanes of its wave), the last found
-// by matching the 8 digit bits with wave ballots.  The keys go to LDS in
-// that order and leave as one contiguous run per digit, so the global
-// writes coalesce.  With gdst, the pass also writes gdst[pos] = gsrc[value]
-// (a gather in the output order).
-template <int R, class K>
-__global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
-    const K* __restrict__ kin, const uint32_t* __restrict__ vin,
-    K* __restrict__ kout, uint32_t* __restrict__ vout, const uint32_t* __restrict__ num,
-    uint32_t capacity, int shift, uint32_t nb, const uint32_t* __restrict__ offs,
-    const uint32_t* __restrict__ gsrc, uint32_t* __restrict__ gdst) {
-    constexpr int NW = kSortThreads / 64;
-    __shared__ K s_key[kSortThreads * R];
-    __shared__ uint32_t s_val[kSortThreads * R];
-    __shared__ uint32_t s_run[kRadix];     // next local position per digit
-    __shared__ uint32_t s_lbase[kRadix];   // digit start inside the block
-    __shared__ uint32_t s_gbase[kRadix];   // digit start in the output
-    __shared__ uint32_t s_wcnt[2][NW][kRadix];  // per-wave digit counts, two rounds in flight
-    __shared__ uint32_t s_scan[kSortThreads];
-    const uint32_t count = clamp_count(num, capacity);
-    const uint32_t base = blockIdx.x * kSortThreads * R;
-    if (base >= count) return;  // uniform for the block
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    const size_t e = (size_t)t * nb + blockIdx.x;
-    const uint32_t g0 = offs[e];
-    const uint32_t g1 = (e + 1 < (size_t)kRadix * nb) ? offs[e + 1] : count;
-    s_gbase[t] = g0;
-    for (int w = 0; w < NW; ++w) s_wcnt[0][w][t] = s_wcnt[1][w][t] = 0;
-    uint32_t total;
-    const uint32_t lb = block_exclusive_scan(g1 - g0, s_scan, total);
-    s_lbase[t] = lb;
-    s_run[t] = lb;
-    // All of the block's loads are issued before the first round, so the
-    // rounds wait on LDS only.
-    K kreg[R];
-    uint32_t vreg[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const uint32_t idx = base + r * kSortThreads + t;
-        kreg[r] = idx < count ? kin[idx] : (K)0;
-        vreg[r] = idx < count ? vin[idx] : 0u;
-    }
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Ranks of a wave's R 64-key rounds: rank[r] = keys of the same digit that come
+// before lane's key of round r in the wave, cnt[d] the wave's count of digit d
+// so far (LDS, zero at the start).  Same-digit lanes are found by matching the
+// 8 digit bits with wave ballots; every lane reads its digit's count before
+// the first lane of the digit raises it.
+template <int R>
+__device__ __forceinline__ void wave_ranks(const uint32_t (&digit)[R], const bool (&valid)[R], uint32_t* cnt,
+                                           uint32_t (&rank)[R], int lane) {
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        uint32_t (*cnt)[kRadix] = s_wcnt[r & 1];
-        const bool valid = base + r * kSortThreads + t < count;
-        const uint32_t digit = (uint32_t)(kreg[r] >> shift) & 0xffu;
-        uint64_t peers = __ballot(valid);
+        uint64_t peers = __ballot(valid[r]);
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
-            const bool bit = (digit >> b) & 1u;
+            const bool bit = (digit[r] >> b) & 1u;
             const uint64_t m = __ballot(bit);
             peers &= bit ? m : ~m;
         }
-        const uint32_t rank = __popcll(peers & lt_mask);
-        if (valid && rank == 0) cnt[wv][digit] = __popcll(peers);
-        __syncthreads();
-        // The other buffer was last read before this barrier; clear it for
-        // the next round, whose writes come after the next barrier.
-        for (int w = 0; w < NW; ++w) s_wcnt[(r + 1) & 1][w][t] = 0;
-        if (valid) {
-            uint32_t pos = s_run[digit] + rank;
-            for (int w = 0; w < wv; ++w) pos += cnt[w][digit];
+        const uint32_t below = __popcll(peers & lt_mask);
+        const uint32_t before = valid[r] ? cnt[digit[r]] : 0u;
+        rank[r] = before + below;
+        wave_fence();
+        if (valid[r] && below == 0) cnt[digit[r]] = before + __popcll(peers);
+        wave_fence();
+    }
+}
+
+// Exclusive scan over threads 0..255 of v (wave shuffles, the four wave totals
+// through s_wave); the workgroup's other threads only pass the barriers.
+__device__ __forceinline__ uint32_t scan_256(uint32_t v, uint32_t* s_wave) {
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    uint32_t inc = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t u = __shfl_up(inc, o);
+        if (lane >= o) inc += u;
+    }
+    if (t < kRadix && lane == 63) s_wave[wv] = inc;
+    __syncthreads();
+    uint32_t before = 0;
+    if (t < kRadix)
+        for (int w = 0; w < wv; ++w) before += s_wave[w];
+    __syncthreads();
+    return before + inc - v;
+}
+
+// Stable scatter through LDS.  Each wave ranks its own contiguous run of the
+// chunk (64 R keys) without waiting for the others; the waves' digit counts
+// then give every (digit, wave) its place in the workgroup, the keys go to
+// LDS in that order and leave as one contiguous run per digit, so the global
+// writes coalesce.  Three barriers around the ranking, where ranking 256 keys
+// at a time across the workgroup took two for every round.  The digits'
+// places in the output: DIRECT sums the other workgroups' histograms here
+// (thread (q, d): every fourth row of digit d), else the scanned digit-major
+// histogram.  With gdst, the pass also writes gdst[pos] = gsrc[value] (a
+// gather in the output order).
+template <class G, class K>
+__global__ __launch_bounds__(G::kThreads) void k_radix_scatter(
+    const K* __restrict__ kin, const uint32_t* __restrict__ vin, K* __restrict__ kout, uint32_t* __restrict__ vout,
+    const uint32_t* __restrict__ num, uint32_t capacity, int shift, uint32_t nb, const uint32_t* __restrict__ hist,
+    const uint32_t* __restrict__ gsrc, uint32_t* __restrict__ gdst) {
+    constexpr int NT = G::kThreads, R = G::kRounds, NW = NT / 64;
+    __shared__ K s_key[G::kKeys];
+    __shared__ uint32_t s_val[G::kKeys];
+    __shared__ uint32_t s_cnt[NW][kRadix];  // per-wave digit counts, then each wave's places
+    __shared__ uint32_t s_lbase[kRadix];    // digit start inside the block
+    __shared__ uint32_t s_gbase[kRadix];    // digit start in the output
+    __shared__ uint32_t s_wave[4];
+    const uint32_t count = clamp_count(num, capacity);
+    const uint32_t base = blockIdx.x * G::kKeys;
+    if (base >= count) return;  // uniform for the block
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    // the block's loads are all issued before anything waits
+    K kreg[R];
+    uint32_t vreg[R], digit[R], rank[R];
+    bool valid[R];
+    const uint32_t first = base + (uint32_t)wv * 64 * R + lane;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint32_t idx = first + r * 64;
+        valid[r] = idx < count;
+        kreg[r] = valid[r] ? kin[idx] : (K)0;
+        vreg[r] = valid[r] ? vin[idx] : 0u;
+    }
+    uint32_t g_total = 0, g_before = 0;  // this thread's share of digit t % 256
+    if constexpr (G::kDirect) {
+        const uint32_t blocks = (count + G::kKeys - 1) / G::kKeys, d = t & (kRadix - 1);
+        for (uint32_t b0 = t / kRadix; b0 < blocks; b0 += 8 * (NT / kRadix)) {
+            uint32_t v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const uint32_t b = b0 + u * (NT / kRadix);
+                v[u] = b < blocks ? hist[(size_t)b * kRadix + d] : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                g_total += v[u];
+                if (b0 + u * (NT / kRadix) < blockIdx.x) g_before += v[u];
+            }
+        }
+    } else {
+        g_before = hist[(size_t)t * nb + blockIdx.x];
+    }
+#pragma unroll
+    for (int k = 0; k < kRadix / 64; ++k) s_cnt[wv][64 * k + lane] = 0u;
+    wave_fence();
+#pragma unroll
+    for (int r = 0; r < R; ++r) digit[r] = (uint32_t)(kreg[r] >> shift) & 0xffu;
+    wave_ranks<R>(digit, valid, s_cnt[wv], rank, lane);
+    if constexpr (G::kDirect) {  // shares of the four threads of a digit, in LDS words that are free until the keys come
+        s_val[t] = g_total;
+        s_val[NT + t] = g_before;
+    }
+    __syncthreads();
+    uint32_t here = 0, total = 0;
+    if (t < kRadix) {
+        for (int w = 0; w < NW; ++w) here += s_cnt[w][t];
+        if constexpr (G::kDirect) {
+            g_before = 0;
+            for (int q = 0; q < NT / kRadix; ++q) {
+                total += s_val[q * kRadix + t];
+                g_before += s_val[NT + q * kRadix + t];
+            }
+        }
+    }
+    if constexpr (G::kDirect) g_before += scan_256(total, s_wave);
+    const uint32_t lb = scan_256(here, s_wave);
+    if (t < kRadix) {
+        s_lbase[t] = lb;
+        s_gbase[t] = g_before;
+        uint32_t run = lb;
+        for (int w = 0; w < NW; ++w) {
+            const uint32_t c = s_cnt[w][t];
+            s_cnt[w][t] = run;
+            run += c;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (valid[r]) {
+            const uint32_t pos = s_cnt[wv][digit[r]] + rank[r];
             s_key[pos] = kreg[r];
             s_val[pos] = vreg[r];
         }
-        __syncthreads();
-        uint32_t add = 0;
-        for (int w = 0; w < NW; ++w) add += cnt[w][t];
-        s_run[t] += add;
-    }
-    const uint32_t here = min((uint32_t)kSortThreads * R, count - base);
-    for (uint32_t i = t; i < here; i += kSortThreads) {
+    __syncthreads();
+    const uint32_t mine = min((uint32_t)G::kKeys, count - base);
+    for (uint32_t i = t; i < mine; i += NT) {
         const K key = s_key[i];
         const uint32_t d = (uint32_t)(key >> shift) & 0xffu;
         const uint32_t pos = s_gbase[d] + (i - s_lbase[d]);
@@ -371,6 +483,94 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
         vout[pos] = s_val[i];
         if (gdst) gdst[pos] = gsrc[s_val[i]];
     }
+}
+
+// The whole depth order of at most kBlockSort items by one workgroup: keys,
+// four passes in LDS, and the pair offsets (the scan of tiles_touched in depth
+// order) with their total.  Also clears the tile ranges.  1000 items: one
+// launch of 18 us, where the launches it replaces took about 75.
+__global__ __launch_bounds__(1024) void k_depth_order(uint32_t items, const float* __restrict__ proj_all,
+                                                      const uint32_t* __restrict__ touched_all,
+                                                      uint32_t* __restrict__ dkeys, uint32_t* __restrict__ dvals,
+                                                      uint32_t* __restrict__ off, uint32_t* __restrict__ ranges,
+                                                      uint32_t n_ranges, uint32_t* __restrict__ num_pairs) {
+    constexpr int NT = 1024, NW = NT / 64, R = kBlockSort / NT;
+    __shared__ uint32_t s_key[kBlockSort], s_val[kBlockSort], s_cnt[NW][kRadix], s_wave[NW];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    for (uint32_t i = t; i < n_ranges; i += NT) ranges[i] = 0u;
+    uint32_t key[R], val[R], digit[R], rank[R];
+    bool valid[R];
+    const uint32_t first = (uint32_t)wv * 64 * R + lane;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint32_t i = first + r * 64;
+        valid[r] = i < items;
+        val[r] = i;
+        key[r] = valid[r] ? depth_key(proj_all, touched_all, i) : 0u;
+    }
+    for (int shift = 0; shift < 32; shift += 8) {
+#pragma unroll
+        for (int k = 0; k < kRadix / 64; ++k) s_cnt[wv][64 * k + lane] = 0u;
+        wave_fence();
+#pragma unroll
+        for (int r = 0; r < R; ++r) digit[r] = (key[r] >> shift) & 0xffu;
+        wave_ranks<R>(digit, valid, s_cnt[wv], rank, lane);
+        __syncthreads();
+        uint32_t here = 0;
+        if (t < kRadix)
+            for (int w = 0; w < NW; ++w) here += s_cnt[w][t];
+        uint32_t run = scan_256(here, s_wave);
+        if (t < kRadix)
+            for (int w = 0; w < NW; ++w) {
+                const uint32_t c = s_cnt[w][t];
+                s_cnt[w][t] = run;
+                run += c;
+            }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (valid[r]) {
+                const uint32_t pos = s_cnt[wv][digit[r]] + rank[r];
+                s_key[pos] = key[r];
+                s_val[pos] = val[r];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (valid[r]) {
+                key[r] = s_key[first + r * 64];
+                val[r] = s_val[first + r * 64];
+            }
+        __syncthreads();
+    }
+    // offsets: the wave's keys are consecutive, round by round
+    uint32_t own[R], before = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint32_t c = valid[r] ? touched_all[val[r]] : 0u;
+        uint32_t inc = c;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t u = __shfl_up(inc, o);
+            if (lane >= o) inc += u;
+        }
+        own[r] = before + inc - c;
+        before += __shfl(inc, 63);
+    }
+    if (lane == 0) s_wave[wv] = before;
+    __syncthreads();
+    uint32_t run = 0, all = 0;
+    for (int w = 0; w < NW; ++w) {
+        if (w < wv) run += s_wave[w];
+        all += s_wave[w];
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (valid[r]) {
+            dkeys[first + r * 64] = key[r];
+            dvals[first + r * 64] = val[r];
+            off[first + r * 64] = run + own[r];
+        }
+    if (t == 0) *num_pairs = all;
 }
 
 template <class K>
@@ -412,20 +612,15 @@ __global__ __launch_bounds__(kOrderThreads) void k_tile_order(const uint32_t* __
                                                               uint32_t n_view, uint32_t offset,
                                                               uint32_t n_tiles_total,
                                                               uint32_t* __restrict__ order) {
-    __shared__ uint32_t hist[kOrderBuckets];
+    __shared__ uint32_t hist[kOrderBuckets], s_wave[4];
+    static_assert(kOrderBuckets == kRadix, "one bucket per scanned thread");
     for (int b = threadIdx.x; b < kOrderBuckets; b += kOrderThreads) hist[b] = 0;
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < n_view; i += kOrderThreads)
         atomicAdd(&hist[order_bucket(ranges, n_tiles_total, offset + i)], 1u);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t run = 0;
-        for (int b = 0; b < kOrderBuckets; ++b) {
-            const uint32_t c = hist[b];
-            hist[b] = run;
-            run += c;
-        }
-    }
+    const uint32_t place = scan_256(threadIdx.x < kOrderBuckets ? hist[threadIdx.x] : 0u, s_wave);
+    if (threadIdx.x < kOrderBuckets) hist[threadIdx.x] = place;
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < n_view; i += kOrderThreads) {
         const uint32_t pos = atomicAdd(&hist[order_bucket(ranges, n_tiles_total, offset + i)], 1u);
@@ -439,67 +634,73 @@ struct SortWs {
     uint32_t* hist;
     uint32_t* partial;
     uint32_t nb;
-    int rounds;
+    bool small;
     size_t bytes;
 };
 
 SortWs sort_layout(void* base, uint32_t capacity) {
     SortWs w{};
-    const int rounds = capacity <= kSmallSort ? kSortRoundsSmall : kSortRoundsLarge;
-    const uint32_t nb = div_up(capacity, (uint64_t)kSortThreads * rounds);
+    w.small = capacity <= kSmallSort;
+    w.nb = div_up(capacity, w.small ? SmallSort::kKeys : LargeSort::kKeys);
     size_t off = 0;
     char* p = static_cast<char*>(base);
     w.keys_alt = reinterpret_cast<uint64_t*>(p + off); off += align_up((size_t)capacity * 8);
     w.vals_alt = reinterpret_cast<uint32_t*>(p + off); off += align_up((size_t)capacity * 4);
-    w.hist = reinterpret_cast<uint32_t*>(p + off); off += align_up((size_t)nb * kRadix * 4);
-    w.partial = reinterpret_cast<uint32_t*>(p + off); off += scan_workspace(nb * kRadix);
-    w.nb = nb;
-    w.rounds = rounds;
+    w.hist = reinterpret_cast<uint32_t*>(p + off); off += align_up((size_t)w.nb * kRadix * 4);
+    w.partial = reinterpret_cast<uint32_t*>(p + off); off += scan_workspace(w.nb * kRadix);
     w.bytes = off;
     return w;
 }
 
-// Sorts key bits [start_bit, start_bit + key_bits) (stable).  first_hist:
-// the caller already wrote the first pass's digit histogram into w.hist.
-// With gdst, the last pass also writes gdst[i] = gsrc[value at i].
-// Keys of type K (uint64_t, or uint32_t for the depth sort, whose keys are
-// 32 bits: a third less traffic per pass); the ping-pong key buffer is sized
-// for 64-bit keys and holds either.
-template <class K>
-pgs_status radix_sort(K* keys, uint32_t* vals, const uint32_t* num, uint32_t capacity,
-                      int key_bits, const SortWs& w, hipStream_t s, int start_bit = 0, bool first_hist = false,
-                      const uint32_t* gsrc = nullptr, uint32_t* gdst = nullptr) {
-    if (capacity == 0) return PGS_OK;
-    const int passes = (key_bits + 7) / 8;
-    K* kin = keys; uint32_t* vin = vals;
-    K* kout = reinterpret_cast<K*>(w.keys_alt); uint32_t* vout = w.vals_alt;
+int sort_passes(int key_bits) { return (key_bits + 7) / 8; }
+
+template <class G, class K>
+pgs_status radix_passes(K* kin, uint32_t* vin, K* kout, uint32_t* vout, const uint32_t* num, uint32_t capacity,
+                        int passes, const SortWs& w, hipStream_t s, int start_bit, bool first_hist,
+                        const uint32_t* gsrc, uint32_t* gdst) {
     for (int p = 0; p < passes; ++p) {
         const int shift = start_bit + 8 * p;
         const bool last = p + 1 == passes;
-        const uint32_t* gs = last ? gsrc : nullptr;
-        uint32_t* gd = last ? gdst : nullptr;
-        if (p > 0 || !first_hist) {
-            if (w.rounds == kSortRoundsSmall)
-                k_radix_hist<kSortRoundsSmall, K><<<w.nb, kSortThreads, 0, s>>>(kin, num, capacity, shift, w.nb,
-                                                                                w.hist);
-            else
-                k_radix_hist<kSortRoundsLarge, K><<<w.nb, kSortThreads, 0, s>>>(kin, num, capacity, shift, w.nb,
-                                                                                w.hist);
+        if (p > 0 || !first_hist)
+            k_radix_hist<G, K><<<w.nb, G::kThreads, 0, s>>>(kin, num, capacity, shift, w.nb, w.hist);
+        if (!G::kDirect) {
+            pgs_status st = scan_u32(w.hist, w.hist, w.nb * kRadix, nullptr, w.partial, s);
+            if (st != PGS_OK) return st;
         }
-        pgs_status st = scan_u32(w.hist, w.hist, w.nb * kRadix, nullptr, w.partial, s);
-        if (st != PGS_OK) return st;
-        if (w.rounds == kSortRoundsSmall)
-            k_radix_scatter<kSortRoundsSmall, K><<<w.nb, kSortThreads, 0, s>>>(kin, vin, kout, vout, num, capacity,
-                                                                               shift, w.nb, w.hist, gs, gd);
-        else
-            k_radix_scatter<kSortRoundsLarge, K><<<w.nb, kSortThreads, 0, s>>>(kin, vin, kout, vout, num, capacity,
-                                                                               shift, w.nb, w.hist, gs, gd);
+        k_radix_scatter<G, K><<<w.nb, G::kThreads, 0, s>>>(kin, vin, kout, vout, num, capacity, shift, w.nb, w.hist,
+                                                           last ? gsrc : nullptr, last ? gdst : nullptr);
         PGS_CHECK_LAUNCH("radix pass");
         K* tk = kin; kin = kout; kout = tk;
         uint32_t* tv = vin; vin = vout; vout = tv;
     }
-    if (kin != keys) {
-        k_copy_pairs<K><<<1024, 256, 0, s>>>(kin, vin, keys, vals, num, capacity);
+    return PGS_OK;
+}
+
+// Sorts key bits [start_bit, start_bit + key_bits) (stable) into (keys, vals),
+// the workspace holding the ping-pong copy.  The unsorted input is in
+// (keys, vals), or with input_in_ws and an odd number of passes in the
+// ping-pong copy, which saves the copy back.  first_hist: the caller already
+// wrote the first pass's digit histogram into w.hist.  With gdst, the last
+// pass also writes gdst[i] = gsrc[value at i].  Keys of type K (uint64_t, or
+// uint32_t for the depth sort, whose keys are 32 bits: a third less traffic
+// per pass); the ping-pong key buffer is sized for 64-bit keys and holds
+// either.
+template <class K>
+pgs_status radix_sort(K* keys, uint32_t* vals, const uint32_t* num, uint32_t capacity,
+                      int key_bits, const SortWs& w, hipStream_t s, int start_bit = 0, bool first_hist = false,
+                      const uint32_t* gsrc = nullptr, uint32_t* gdst = nullptr, bool input_in_ws = false) {
+    if (capacity == 0) return PGS_OK;
+    const int passes = sort_passes(key_bits);
+    K* alt = reinterpret_cast<K*>(w.keys_alt);
+    const bool swap = input_in_ws && (passes & 1);
+    K *kin = swap ? alt : keys, *kout = swap ? keys : alt;
+    uint32_t *vin = swap ? w.vals_alt : vals, *vout = swap ? vals : w.vals_alt;
+    const pgs_status st =
+        w.small ? radix_passes<SmallSort, K>(kin, vin, kout, vout, num, capacity, passes, w, s, start_bit, first_hist, gsrc, gdst)
+                : radix_passes<LargeSort, K>(kin, vin, kout, vout, num, capacity, passes, w, s, start_bit, first_hist, gsrc, gdst);
+    if (st != PGS_OK) return st;
+    if (!swap && (passes & 1)) {
+        k_copy_pairs<K><<<1024, 256, 0, s>>>(alt, w.vals_alt, keys, vals, num, capacity);
         PGS_CHECK_LAUNCH("radix copy");
     }
     return PGS_OK;
@@ -636,37 +837,50 @@ pgs_status bin_sort_items(uint32_t items, int n, const EmitViews& ev, int n_tile
         PGS_CHECK_LAUNCH(who);
         return PGS_OK;
     }
-    // depth keys with the first depth pass's histogram (and the clears of
-    // ranges and pair count); the depth sort's last pass gathers
-    // tiles_touched into depth order; the emit writes the pair sort's first
-    // histogram
+    // few items: their whole depth order and offsets in one launch; else depth
+    // keys with the first depth pass's histogram (and the clears of ranges and
+    // pair count), the depth sort, whose last pass gathers tiles_touched into
+    // depth order, and the scan.  The emit writes the pair sort's first
+    // histogram, and its pairs where an odd number of passes will end in
+    // (keys, values).
     const SortWs& iw = w.items_ws;
-    if (iw.rounds == kSortRoundsSmall)
-        k_depth_keys<kSortRoundsSmall><<<iw.nb, kSortThreads, 0, s>>>(items, n, proj_all, touched_all, w.dkeys,
-                                                                      w.dvals, w.count, iw.nb, iw.hist, ranges,
-                                                                      2u * (uint32_t)n_tiles, num_pairs);
-    else
-        k_depth_keys<kSortRoundsLarge><<<iw.nb, kSortThreads, 0, s>>>(items, n, proj_all, touched_all, w.dkeys,
-                                                                      w.dvals, w.count, iw.nb, iw.hist, ranges,
-                                                                      2u * (uint32_t)n_tiles, num_pairs);
-    PGS_CHECK_LAUNCH(who);
-    pgs_status st = radix_sort(w.dkeys, w.dvals, w.count, items, 32, iw, s, 0, true, touched_all, w.off);
-    if (st != PGS_OK) return st;
-    st = scan_u32(w.off, w.off, items, num_pairs, w.partial, s);
-    if (st != PGS_OK) return st;
+    const uint32_t n_ranges = 2u * (uint32_t)n_tiles;
+    if (items <= kBlockSort) {
+        k_depth_order<<<1, 1024, 0, s>>>(items, proj_all, touched_all, w.dkeys, w.dvals, w.off, ranges, n_ranges,
+                                         num_pairs);
+        PGS_CHECK_LAUNCH(who);
+    } else {
+        if (iw.small)
+            k_depth_keys<SmallSort><<<iw.nb, SmallSort::kThreads, 0, s>>>(items, proj_all, touched_all, w.dkeys,
+                                                                          w.dvals, w.count, iw.nb, iw.hist, ranges,
+                                                                          n_ranges, num_pairs);
+        else
+            k_depth_keys<LargeSort><<<iw.nb, LargeSort::kThreads, 0, s>>>(items, proj_all, touched_all, w.dkeys,
+                                                                          w.dvals, w.count, iw.nb, iw.hist, ranges,
+                                                                          n_ranges, num_pairs);
+        PGS_CHECK_LAUNCH(who);
+        pgs_status st = radix_sort(w.dkeys, w.dvals, w.count, items, 32, iw, s, 0, true, touched_all, w.off);
+        if (st != PGS_OK) return st;
+        st = scan_u32(w.off, w.off, items, num_pairs, w.partial, s);
+        if (st != PGS_OK) return st;
+    }
     const SortWs& pw = w.pairs_ws;
+    const int tile_bits = bits_for((uint32_t)n_tiles);
+    const bool odd = (sort_passes(tile_bits) & 1) != 0;
+    uint64_t* ekeys = odd ? pw.keys_alt : keys;
+    uint32_t* evals = odd ? pw.vals_alt : values;
     const uint32_t ge = pw.nb > 0 ? pw.nb : 1u;
-    if (pw.rounds == kSortRoundsSmall)
-        k_emit_sorted<kSortRoundsSmall><<<ge, kSortThreads, 0, s>>>(items, n, ev, w.dkeys, rect_all, w.dvals,
-                                                                    w.off, num_pairs, capacity, keys, values,
-                                                                    flags, pw.nb, pw.hist);
+    if (pw.small)
+        k_emit_sorted<SmallSort><<<ge, SmallSort::kThreads, 0, s>>>(items, n, ev, w.dkeys, rect_all, w.dvals, w.off,
+                                                                    num_pairs, capacity, ekeys, evals, flags, pw.nb,
+                                                                    pw.hist);
     else
-        k_emit_sorted<kSortRoundsLarge><<<ge, kSortThreads, 0, s>>>(items, n, ev, w.dkeys, rect_all, w.dvals,
-                                                                    w.off, num_pairs, capacity, keys, values,
-                                                                    flags, pw.nb, pw.hist);
+        k_emit_sorted<LargeSort><<<ge, LargeSort::kThreads, 0, s>>>(items, n, ev, w.dkeys, rect_all, w.dvals, w.off,
+                                                                    num_pairs, capacity, ekeys, evals, flags, pw.nb,
+                                                                    pw.hist);
     PGS_CHECK_LAUNCH(who);
     if (capacity == 0) return PGS_OK;
-    st = radix_sort(keys, values, num_pairs, capacity, bits_for((uint32_t)n_tiles), pw, s, 32, true);
+    pgs_status st = radix_sort(keys, values, num_pairs, capacity, tile_bits, pw, s, 32, true, nullptr, nullptr, true);
     if (st != PGS_OK) return st;
     const uint32_t grid = div_up(capacity, 256) < 4096 ? div_up(capacity, 256) : 4096;
     k_ranges<<<grid, 256, 0, s>>>(keys, num_pairs, capacity, (uint32_t)n_tiles, ranges);

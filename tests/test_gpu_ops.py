@@ -435,3 +435,51 @@ def test_knn_lists_and_grid_sizes(case, k):
     ids, dd = o_seed.knn(pts, q, k)
     np.testing.assert_array_equal(nbr.cpu().numpy()[:, q].T, ids)
     np.testing.assert_array_equal(d2.cpu().numpy()[:, q].T, dd)
+
+
+@pytest.mark.parametrize("n,tx,ty,cap", [
+    (1, 1, 1, 8), (4096, 20, 5, 60_000), (4097, 20, 5, 60_000), (4095, 23, 29, (1 << 20) + 1),
+    (70_001, 40, 30, 1 << 20), (20_000, 300, 251, 200_000), (6000, 40, 30, 30_001), (5000, 16, 16, 0)])
+def test_bin_sort_workgroup_and_pass_edges(n, tx, ty, cap):
+    # either side of the one-workgroup depth order (4096 items) and of the
+    # sort without a device scan (2^20 keys), with none to three passes over
+    # the tile bits; equal depths keep the id order, items without pairs come
+    # last, and past the capacity the first pairs in depth order remain
+    from paper_2601_17354_amd import binding as B
+    rng = np.random.default_rng(n + tx)
+    say(f"[bin_sort] n={n} tiles={tx}x{ty} cap={cap}")
+    x0, y0 = rng.integers(0, tx, n), rng.integers(0, ty, n)
+    x1, y1 = np.minimum(x0 + rng.integers(0, 4, n), tx - 1), np.minimum(y0 + rng.integers(0, 3, n), ty - 1)
+    touched = (x1 - x0 + 1) * (y1 - y0 + 1)
+    touched[rng.random(n) < 0.1 * (n > 1)] = 0
+    depth = rng.uniform(0.5, 9.0, max(n // 3, 1)).astype(np.float32)[rng.integers(0, max(n // 3, 1), n)]
+    proj = np.zeros((n, 16), np.float32)
+    proj[:, 2] = depth
+    rect = np.stack([x0 | (y0 << 16), x1 | (y1 << 16)]).astype(np.int32)
+    order = np.lexsort((np.arange(n), depth.view(np.uint32), touched == 0))
+    keys, ids = [], []
+    for g in order[:int((touched > 0).sum())]:
+        tile = (np.arange(y0[g], y1[g] + 1)[:, None] * tx + np.arange(x0[g], x1[g] + 1)).ravel().astype(np.uint64)
+        keys.append((tile << np.uint64(32)) | np.uint64(depth.view(np.uint32)[g]))
+        ids.append(np.full(len(tile), g))
+    keys, ids = np.concatenate(keys)[:cap], np.concatenate(ids)[:cap]
+    perm = np.argsort(keys >> np.uint64(32), kind="stable")
+    keys, ids, total = keys[perm], ids[perm], int(touched.sum())
+
+    dev = lambda a: torch.as_tensor(a, device=DEV)
+    k = torch.zeros(max(cap, 1), dtype=torch.int64, device=DEV)
+    v = torch.zeros(max(cap, 1), dtype=torch.int32, device=DEV)
+    ranges = torch.full((2, tx * ty), -1, dtype=torch.int32, device=DEV)
+    num, flags = torch.full((1,), -1, dtype=torch.int32, device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)
+    ws = torch.empty(B.pgs_bin_sort_workspace(n, cap), dtype=torch.uint8, device=DEV)
+    B.pgs_bin_sort(n, dev(proj), dev(rect), dev(touched.astype(np.int32)), tx, tx * ty, 0, cap, k, v, ranges, num,
+                   flags, ws)
+    torch.cuda.synchronize()
+    m = len(keys)
+    assert int(num.item()) == total and (int(flags.item()) != 0) == (total > cap)
+    np.testing.assert_array_equal(k.cpu().numpy().view(np.uint64)[:m], keys)
+    np.testing.assert_array_equal(v.cpu().numpy()[:m], ids)
+    counts = np.bincount((keys >> np.uint64(32)).astype(np.int64), minlength=tx * ty)
+    r = ranges.cpu().numpy()
+    np.testing.assert_array_equal(r[1] - r[0], counts)
+    np.testing.assert_array_equal(r[0][counts > 0], (np.cumsum(counts) - counts)[counts > 0])
