@@ -323,12 +323,6 @@ __global__ __launch_bounds__(G::kThreads) void k_radix_hist(const K* __restrict_
     if (threadIdx.x < kRadix) hist[hist_at<G>(threadIdx.x, blockIdx.x, nb)] = h[threadIdx.x];
 }
 
-__device__ __forceinline__ void wave_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Ranks of a wave's R 64-key rounds: rank[r] = keys of the same digit that come
 // before lane's key of round r in the wave, cnt[d] the wave's count of digit d
 // so far (LDS, zero at the start).  Same-digit lanes are found by matching the

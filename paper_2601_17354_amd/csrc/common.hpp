@@ -91,6 +91,13 @@ pgs_status check_views(const pgs_view_batch* vb, const char* who);
         }                                                                            \
     } while (0)
 
+// Orders a wave's LDS writes before the reads of its other lanes that follow.
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Wave-wide float sum on wave64 with DPP: an inclusive scan inside each row of
 // 16 lanes (row_shr 1, 2, 4, 8), then row_bcast:15 and row_bcast:31 fold the
 // rows together.  Lane 63 ends up holding the sum of all 64 inputs.

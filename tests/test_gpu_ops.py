@@ -100,6 +100,33 @@ def test_loss_matches_oracle(W, H, lam):
         assert_block_close(dl.cpu().numpy()[c], wg[c], 1e-4, what=f"dL/dx[{c}]")
 
 
+@pytest.mark.parametrize("W,H", [(1, 1), (5, 300), (118, 4), (119, 21), (237, 66), (355, 9)])
+@pytest.mark.parametrize("place", ["out", "over_x", "over_y"])
+def test_loss_strip_edges_and_in_place(W, H, place):
+    # widths around the 118-column strips, heights around the waves' rows,
+    # images smaller than the window, and gradients written over an input; a
+    # second pair is identical, where SSIM is 1 and the gradient 0
+    from paper_2601_17354_amd import binding as B
+    rng = np.random.default_rng(W + H)
+    x = rng.uniform(size=(3, H, W)).astype(np.float32)
+    y = np.clip(x + rng.normal(0, 0.2, x.shape), 0, 1).astype(np.float32)
+    ws = torch.empty(B.pgs_loss_workspace(W, H), dtype=torch.uint8, device=DEV)
+    loss = torch.zeros(1, device=DEV)
+    for b in (y, x):
+        xt, yt = torch.as_tensor(x, device=DEV), torch.as_tensor(b, device=DEV)
+        dl = {"out": torch.full_like(xt, 7.0), "over_x": xt, "over_y": yt}[place]
+        B.pgs_loss_l1_dssim(xt, yt, W, H, 0.3, loss, dl, ws)
+        torch.cuda.synchronize()
+        want, wg = o_loss.l1_dssim(x, b, 0.3)
+        assert abs(loss.item() - want) <= 1e-5 * abs(want) + 1e-6
+        got = dl.cpu().numpy()
+        if b is x:
+            assert np.abs(got).max() <= 1e-4 / x.size
+        else:
+            for c in range(3):
+                assert_block_close(got[c], wg[c], 1e-4, what=f"dL/dx[{c}]")
+
+
 def test_adam_matches_oracle():
     from paper_2601_17354_amd import binding as B
     rng = np.random.default_rng(3)
