@@ -125,9 +125,8 @@ __device__ __forceinline__ void shape_of(const float* __restrict__ P, int n, int
     S3.Sig[3] = sig(1, 1); S3.Sig[4] = sig(1, 2); S3.Sig[5] = sig(2, 2);
 }
 
-__device__ __forceinline__ void view_geometry(const float* __restrict__ P, int n, int i, const Shape& S3,
-                                              const CamD& cam, Geo& G) {
-    const double mx = prow(P, 0, n, i), my = prow(P, 1, n, i), mz = prow(P, 2, n, i);
+__device__ __forceinline__ void view_geometry(const double (&mu)[3], const Shape& S3, const CamD& cam, Geo& G) {
+    const double mx = mu[0], my = mu[1], mz = mu[2];
     G.x = cam.R[0] * mx + cam.R[1] * my + cam.R[2] * mz + cam.t[0];
     G.y = cam.R[3] * mx + cam.R[4] * my + cam.R[5] * mz + cam.t[1];
     G.z = cam.R[6] * mx + cam.R[7] * my + cam.R[8] * mz + cam.t[2];
@@ -164,7 +163,9 @@ __device__ __forceinline__ void view_geometry(const float* __restrict__ P, int n
 // to tau).  (-1, -1) when o is below the threshold (no pixel qualifies);
 // (inf, inf) when the conic is too close to degenerate (1 - rho < 1e-3) for
 // the bound, so that nothing is skipped.
-__device__ void alpha_extent(float A, float B, float C, float o, float& hx, float& hy) {
+__device__ __forceinline__ double alpha_tau(float o) { return 2.0 * log(255.0 * fmax((double)o, 1.0 / 255.0)); }
+
+__device__ __forceinline__ void alpha_extent(float A, float B, float C, float o, double tau, float& hx, float& hy) {
     if (o < pgs::kAlphaMin * (1.0f - 1e-6f)) {
         hx = hy = -1.f;
         return;
@@ -176,23 +177,28 @@ __device__ void alpha_extent(float A, float B, float C, float o, float& hx, floa
         hx = hy = INFINITY;
         return;
     }
-    const double tau = 2.0 * log(255.0 * fmax((double)o, 1.0 / 255.0));
     const double eta = 20.0 * 0x1p-24 / one_m_rho;
     const double t = (tau + 1e-3) / (1.0 - eta);
     hx = (float)(sqrt(t * c / det) * (1.0 + 1e-5) + 1e-2);
     hy = (float)(sqrt(t * a / det) * (1.0 + 1e-5) + 1e-2);
 }
 
-// Projection of Gaussian i into one view (record, radius, rectangle and
-// tile count at index i of that view's arrays).
-template <int D>
-__device__ __forceinline__ void project_view(const float* __restrict__ P, int n, int i, const Shape& S3,
-                                             const CamD& cam, int tw, int th, int TX, int TY,
-                                             float* __restrict__ out, int* __restrict__ radius,
+__device__ __forceinline__ float opacity_of(const float* __restrict__ P, int n, int i) {
+    return (float)(1.0 / (1.0 + exp(-prow(P, 10, n, i))));
+}
+
+// Projection of Gaussian i into one view: its record's first 12 words in rec
+// (the last four are zero; all zero where it is culled), radius, rectangle and
+// tile count at index i of that view's arrays.  coef(k, ch): SH coefficient;
+// o32, tau: its opacity and alpha_tau of it.
+template <int D, class Coef>
+__device__ __forceinline__ void project_view(const double (&mu)[3], int n, int i, const Shape& S3, float o32, double tau,
+                                             Coef&& coef, const CamD& cam, int tw, int th, int TX, int TY,
+                                             float4 (&rec)[3], int* __restrict__ radius,
                                              uint32_t* __restrict__ rect, uint32_t* __restrict__ touched) {
     constexpr int K = (D + 1) * (D + 1);
     Geo G;
-    view_geometry(P, n, i, S3, cam, G);
+    view_geometry(mu, S3, cam, G);
     bool ok = G.z > 0.2 && G.det > 0.0;
     double u = 0, v = 0, r = 0, x0 = 0, x1 = -1, y0 = 0, y1 = -1;
     if (ok) {
@@ -208,12 +214,7 @@ __device__ __forceinline__ void project_view(const float* __restrict__ P, int n,
         ok = isfinite(u) && isfinite(v) && x0 <= x1 && y0 <= y1;
     }
     if (!ok) {
-        float4* rec = reinterpret_cast<float4*>(out + (size_t)i * PGS_PROJ_STRIDE);
-        const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-        rec[0] = z;
-        rec[1] = z;
-        rec[2] = z;
-        rec[3] = z;
+        rec[0] = rec[1] = rec[2] = make_float4(0.f, 0.f, 0.f, 0.f);
         radius[i] = 0;
         rect[i] = 0;
         rect[(size_t)n + i] = 0;
@@ -221,9 +222,9 @@ __device__ __forceinline__ void project_view(const float* __restrict__ P, int n,
         return;
     }
     // colour from the view direction
-    double d0 = prow(P, 0, n, i) - cam.campos[0];
-    double d1 = prow(P, 1, n, i) - cam.campos[1];
-    double d2 = prow(P, 2, n, i) - cam.campos[2];
+    double d0 = mu[0] - cam.campos[0];
+    double d1 = mu[1] - cam.campos[1];
+    double d2 = mu[2] - cam.campos[2];
     const double dl = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
     d0 /= dl; d1 /= dl; d2 /= dl;
     double Y[K];
@@ -231,23 +232,19 @@ __device__ __forceinline__ void project_view(const float* __restrict__ P, int n,
     double col[3];
     for (int ch = 0; ch < 3; ++ch) {
         double acc = 0.5;
-        for (int k = 0; k < K; ++k) acc += Y[k] * prow(P, 11 + 3 * k + ch, n, i);
+        for (int k = 0; k < K; ++k) acc += Y[k] * coef(k, ch);
         col[ch] = fmax(acc, 0.0);
     }
-    const double o = 1.0 / (1.0 + exp(-prow(P, 10, n, i)));
     static_assert(PGS_PROJ_U == 0 && PGS_PROJ_V == 1 && PGS_PROJ_DEPTH == 2 && PGS_PROJ_A == 3 &&
                       PGS_PROJ_B == 4 && PGS_PROJ_C == 5 && PGS_PROJ_OPACITY == 6 && PGS_PROJ_R == 7 &&
                       PGS_PROJ_G == 8 && PGS_PROJ_BLUE == 9 && PGS_PROJ_STRIDE == 16,
                   "record layout");
-    float4* rec = reinterpret_cast<float4*>(out + (size_t)i * PGS_PROJ_STRIDE);
     const float A32 = (float)(G.c / G.det), B32 = (float)(-G.b / G.det), C32 = (float)(G.a / G.det);
-    const float o32 = (float)o;
     float hx, hy;
-    alpha_extent(A32, B32, C32, o32, hx, hy);
+    alpha_extent(A32, B32, C32, o32, tau, hx, hy);
     rec[0] = make_float4((float)u, (float)v, (float)G.z, A32);
     rec[1] = make_float4(B32, C32, o32, (float)col[0]);
     rec[2] = make_float4((float)col[1], (float)col[2], hx, hy);
-    rec[3] = make_float4(0.f, 0.f, 0.f, 0.f);
     radius[i] = (int)r;
     const uint32_t ix0 = (uint32_t)x0, ix1 = (uint32_t)x1, iy0 = (uint32_t)y0, iy1 = (uint32_t)y1;
     rect[i] = ix0 | (iy0 << 16);
@@ -265,7 +262,17 @@ __global__ __launch_bounds__(256) void k_project(const float* __restrict__ P, in
     if (i >= n) return;
     Shape S3;
     shape_of(P, n, i, S3);
-    project_view<D>(P, n, i, S3, cam, tw, th, TX, TY, out, radius, rect, touched);
+    const float o = opacity_of(P, n, i);
+    const double mu[3] = {prow(P, 0, n, i), prow(P, 1, n, i), prow(P, 2, n, i)};
+    float4 rec[3];
+    project_view<D>(mu, n, i, S3, o, alpha_tau(o),
+                    [&](int k, int ch) { return prow(P, 11 + 3 * k + ch, n, i); }, cam, tw, th, TX, TY, rec, radius,
+                    rect, touched);
+    float4* dst = reinterpret_cast<float4*>(out + (size_t)i * PGS_PROJ_STRIDE);
+    dst[0] = rec[0];
+    dst[1] = rec[1];
+    dst[2] = rec[2];
+    dst[3] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
 // Up to kLaunchViews views per multi-view launch, cameras by value.
@@ -276,46 +283,105 @@ struct LaunchViews {
     int TX[kLaunchViews], TY[kLaunchViews];
 };
 
-// Every view of a launch for one Gaussian: the view-independent shape once,
-// the parameters read once from HBM (the views re-read them from cache).
+// Start of row r at a wave's first Gaussian, kept a scalar: left to itself the
+// compiler steps a 64-bit address per lane from row to row and holds all of
+// them until the stores.
+template <class T>
+__device__ __forceinline__ T* row_start(T* base, int r, int n) {
+    size_t off = (size_t)r * n;
+    asm volatile("" : "+s"(off));
+    return base + off;
+}
+
+// Every view of a launch for one Gaussian: shape and opacity once, the SH
+// coefficients read once and kept in LDS (a column per lane, no barrier).
+// Re-read from cache by every view, they and their addresses left room for
+// one wave per SIMD at SH degree 3: eight views of 1M Gaussians 422 us, now
+// 361, bound by the store of their records and by float64 arithmetic.
+// Up to degree 1 a view's 64 records, 4 KB in a row, turn in LDS (chunks
+// swizzled over the banks) and leave as whole lines: 300k at degree 0 60 us
+// stored lane by lane, 53 turned.  From degree 2 on the LDS for it costs more
+// waves than it gains (degree 2 74 against 84 us, degree 3 361 against 393).
 template <int D>
-__global__ __launch_bounds__(256) void k_project_views(const float* __restrict__ P, int n, LaunchViews lv,
-                                                       int tw, int th, float* __restrict__ out_all,
-                                                       int* __restrict__ radius_all,
-                                                       uint32_t* __restrict__ rect_all,
-                                                       uint32_t* __restrict__ touched_all) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+__global__ __launch_bounds__(64, 3) void k_project_views(const float* __restrict__ P, int n, LaunchViews lv,
+                                                         int tw, int th, float* __restrict__ out_all,
+                                                         int* __restrict__ radius_all,
+                                                         uint32_t* __restrict__ rect_all,
+                                                         uint32_t* __restrict__ touched_all) {
+    constexpr int K = (D + 1) * (D + 1);
+    __shared__ float sh[3 * K][64];
+    __shared__ float4 turn[D < 2 ? 64 * 4 : 1];
+    const int i0 = blockIdx.x * 64, lane = threadIdx.x;
+    if (i0 + lane >= n) return;
+    const int chunks = 4 * min(64, n - i0);
+#pragma unroll
+    for (int r = 0; r < 3 * K; ++r) sh[r][lane] = row_start(P + i0, 11 + r, n)[lane];
     Shape S3;
-    shape_of(P, n, i, S3);
+    shape_of(P + i0, n, lane, S3);
+    const double mu[3] = {prow(P + i0, 0, n, lane), prow(P + i0, 1, n, lane), prow(P + i0, 2, n, lane)};
+    const float o = opacity_of(P + i0, n, lane);
+    const double tau = alpha_tau(o);
+#pragma unroll 1
     for (int k = 0; k < lv.nv; ++k) {
-        const size_t v = (size_t)(lv.v0 + k);
-        project_view<D>(P, n, i, S3, lv.cam[k], tw, th, lv.TX[k], lv.TY[k], out_all + v * n * PGS_PROJ_STRIDE,
-                        radius_all + v * n, rect_all + 2 * v * n, touched_all + v * n);
+        const size_t at = (size_t)(lv.v0 + k) * n + i0;
+        int l = lane;  // opaque per view: the coefficients stay in LDS
+        asm volatile("" : "+v"(l));
+        float4 rec[3];
+        project_view<D>(mu, n, lane, S3, o, tau, [&](int q, int ch) { return (double)sh[3 * q + ch][l]; },
+                        lv.cam[k], tw, th, lv.TX[k], lv.TY[k], rec, radius_all + at,
+                        rect_all + at + (size_t)(lv.v0 + k) * n, touched_all + at);
+        float4* dst = reinterpret_cast<float4*>(out_all + at * PGS_PROJ_STRIDE);
+        const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+        if constexpr (D < 2) {
+            const auto slot = [](int record, int c) { return 4 * record + (c ^ ((record >> 2) & 3)); };
+#pragma unroll
+            for (int c = 0; c < 4; ++c) turn[slot(lane, c)] = c < 3 ? rec[c] : zero;
+            wave_fence();
+            for (int q = lane; q < chunks; q += min(64, n - i0)) dst[q] = turn[slot(q >> 2, q & 3)];
+            wave_fence();
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) dst[4 * lane + c] = c < 3 ? rec[c] : zero;
+        }
     }
 }
 
 // Backward: exact derivative of k_project's outputs (u, v, A, B, C, o, rgb)
 // with every discrete decision frozen, accumulated into the canonical
-// gradient rows.
-// The gradient contributions of one view to Gaussian i's canonical rows,
-// handed to acc(row, value) (float64).
-template <int D, class Acc>
-__device__ __forceinline__ void project_bwd_view(const float* __restrict__ P, int n, int i, const Shape& S3,
-                                                 const CamD& cam, const float* __restrict__ g2d_row, Acc&& acc) {
-    constexpr int K = (D + 1) * (D + 1);
-    auto gin = [&](int f) { return (double)g2d_row[f]; };
-    const double gu = gin(0), gv = gin(1), gA = gin(2), gB = gin(3), gC = gin(4), go = gin(5);
-    const double gcol[3] = {gin(6), gin(7), gin(8)};
+// gradient rows: each view adds in float64 and rounds to float32, in view
+// order, whether the views share a launch or not.
+//
+// One thread walks the views twice.  The first walk keeps the eleven rows of
+// mean, scale, rotation and opacity in registers and decides which colour
+// channels are clamped; the second keeps the SH rows, with the direction and
+// the basis formed again.  The SH coefficients, which the first walk reads
+// twice in every view, wait in LDS (a column per lane, no barrier).  One walk
+// with all rows and coefficients in registers left room for a single wave per
+// SIMD at SH degree 3, whose memory accesses nothing hid: eight views of 1M
+// Gaussians 1335 us, now 388; one view of 100k 39, now 25.
 
-    double gmu[3], glog[3], gqraw[4];
+// Unit vector from the camera to the mean and its length's reciprocal.
+__device__ __forceinline__ double view_direction(const double (&mu)[3], const CamD& cam, double (&d)[3]) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) d[k] = mu[k] - cam.campos[k];
+    const double inv = 1.0 / sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) d[k] *= inv;
+    return inv;
+}
+
+// What one view adds to a Gaussian's rows 0..9 (mean, log-scales,
+// quaternion), without the mean's part through the colour.
+__device__ __forceinline__ void bwd_geometry(const double (&mu)[3], const Shape& S3, const CamD& cam, double gu,
+                                             double gv, double gA, double gB, double gC, double (&gmu)[3],
+                                             double (&glog)[3], double (&gqraw)[4]) {
     Geo G;
-    view_geometry(P, n, i, S3, cam, G);
-    const double a = G.a, b = G.b, c = G.c, det2 = G.det * G.det;
+    view_geometry(mu, S3, cam, G);
+    const double a = G.a, b = G.b, c = G.c, idet2 = 1.0 / (G.det * G.det);
     // conic (A, B, C) = (c, -b, a) / det  ->  Sigma2D entries
-    const double ga = (-c * c * gA + b * c * gB - b * b * gC) / det2;
-    const double gb = (2.0 * b * c * gA - (a * c + b * b) * gB + 2.0 * a * b * gC) / det2;
-    const double gc = (-b * b * gA + a * b * gB - a * a * gC) / det2;
+    const double ga = (-c * c * gA + b * c * gB - b * b * gC) * idet2;
+    const double gb = (2.0 * b * c * gA - (a * c + b * b) * gB + 2.0 * a * b * gC) * idet2;
+    const double gc = (-b * b * gA + a * b * gB - a * a * gC) * idet2;
     // symmetric 2x2 gradient of Sigma2D
     const double G00 = ga, G01 = 0.5 * gb, G11 = gc;
     const double* S = S3.Sig;
@@ -343,23 +409,23 @@ __device__ __forceinline__ void project_bwd_view(const float* __restrict__ P, in
     const double gJ02 = dT0[0] * W[6] + dT0[1] * W[7] + dT0[2] * W[8];
     const double gJ11 = dT1[0] * W[3] + dT1[1] * W[4] + dT1[2] * W[5];
     const double gJ12 = dT1[0] * W[6] + dT1[1] * W[7] + dT1[2] * W[8];
-    const double z = G.z, z2 = z * z;
+    const double iz = 1.0 / G.z, iz2 = iz * iz;
     double gx = 0, gy = 0, gz = 0;
     // J00 = fx/z, J02 = -fx tx/z (tx = x/z unless clamped), same in y
-    gz += -cam.fx / z2 * gJ00 - cam.fy / z2 * gJ11;
-    gz += cam.fx * G.tx / z2 * gJ02 + cam.fy * G.ty / z2 * gJ12;
+    gz -= iz2 * (cam.fx * gJ00 + cam.fy * gJ11);
+    gz += iz2 * (cam.fx * G.tx * gJ02 + cam.fy * G.ty * gJ12);
     if (!G.clx) {
-        gx += -cam.fx / z2 * gJ02;
-        gz += cam.fx * G.x / (z2 * z) * gJ02;
+        gx -= cam.fx * iz2 * gJ02;
+        gz += cam.fx * G.x * (iz2 * iz) * gJ02;
     }
     if (!G.cly) {
-        gy += -cam.fy / z2 * gJ12;
-        gz += cam.fy * G.y / (z2 * z) * gJ12;
+        gy -= cam.fy * iz2 * gJ12;
+        gz += cam.fy * G.y * (iz2 * iz) * gJ12;
     }
     // pixel mean
-    gx += gu * cam.fx / z;
-    gy += gv * cam.fy / z;
-    gz += -gu * cam.fx * G.x / z2 - gv * cam.fy * G.y / z2;
+    gx += gu * cam.fx * iz;
+    gy += gv * cam.fy * iz;
+    gz -= iz2 * (gu * cam.fx * G.x + gv * cam.fy * G.y);
     // x_c = W mu + t
     for (int k = 0; k < 3; ++k) gmu[k] = W[k] * gx + W[3 + k] * gy + W[6 + k] * gz;
 
@@ -390,100 +456,168 @@ __device__ __forceinline__ void project_bwd_view(const float* __restrict__ P, in
                    y * gR[5] + x * gR[6] + y * gR[7]);
     const double dotq = gq[0] * w + gq[1] * x + gq[2] * y + gq[3] * zq;
     for (int k = 0; k < 4; ++k) gqraw[k] = (gq[k] - S3.qn[k] * dotq) / S3.qlen;
-    // colour: c = max(0, sum_k Y_k(d) f_k + 1/2), d = unit(mu - campos)
-    double d0 = prow(P, 0, n, i) - cam.campos[0];
-    double d1 = prow(P, 1, n, i) - cam.campos[1];
-    double d2 = prow(P, 2, n, i) - cam.campos[2];
-    const double dl = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
-    d0 /= dl; d1 /= dl; d2 /= dl;
-    double Y[K];
-    sh_eval<D>(d0, d1, d2, Y);
-    double graw[3];
-    for (int ch = 0; ch < 3; ++ch) {
-        double c_ = 0.5;
-        for (int k = 0; k < K; ++k) c_ += Y[k] * prow(P, 11 + 3 * k + ch, n, i);
-        graw[ch] = c_ >= 0.0 ? gcol[ch] : 0.0;
-    }
+}
+
+// Lane's Gaussian of a wave; P and grads point at the wave's first Gaussian, so
+// that a row's address is a scalar and the lane's offset.  Bit k of seen: view k
+// holds the Gaussian.  view(k, rec) gives view k's camera and where its 2D
+// gradients of the wave begin; they are loaded one view ahead.
+template <int D, class View>
+__device__ __forceinline__ void project_bwd_rows(const float* __restrict__ P, int n, int lane, int nv, uint32_t seen, View&& view,
+                                                 float* __restrict__ grads, float (*sh)[64]) {
+    constexpr int K = (D + 1) * (D + 1);
 #pragma unroll
-    for (int k = 0; k < K; ++k)
+    for (int r = 0; r < 3 * K; ++r) sh[r][lane] = row_start(P, 11 + r, n)[lane];
+    double mu[3];
 #pragma unroll
-        for (int ch = 0; ch < 3; ++ch) acc(11 + 3 * k + ch, Y[k] * graw[ch]);
-    if (D >= 1) {
-        double gd[3] = {0, 0, 0};
+    for (int k = 0; k < 3; ++k) mu[k] = prow(P, k, n, lane);
+    Shape S3;
+    shape_of(P, n, lane, S3);
+    const double o = 1.0 / (1.0 + exp(-prow(P, 10, n, lane))), go_do = o * (1.0 - o);
+    uint32_t open = 0u;  // bits 3k..3k+2: unclamped channels of view k
+    {
+        float acc[11];
 #pragma unroll
-        for (int k = 1; k < K; ++k) {
-            const double gy_k = prow(P, 11 + 3 * k, n, i) * graw[0] +
-                                prow(P, 12 + 3 * k, n, i) * graw[1] +
-                                prow(P, 13 + 3 * k, n, i) * graw[2];
-            double dx, dy, dz;
-            sh_grad_k(k, d0, d1, d2, dx, dy, dz);
-            gd[0] += gy_k * dx;
-            gd[1] += gy_k * dy;
-            gd[2] += gy_k * dz;
+        for (int r = 0; r < 11; ++r) acc[r] = row_start(grads, r, n)[lane];
+        const auto add = [&](int r, double g) { acc[r] = (float)((double)acc[r] + g); };
+        float4 n0, n1;
+        float n2;
+        const auto fetch = [&](int k) {
+            if (!((seen >> k) & 1u)) return;  // also past the last view
+            const float* rec;
+            view(k, rec);
+            rec += lane * PGS_GRAD2D_STRIDE;
+            n0 = reinterpret_cast<const float4*>(rec)[0];
+            n1 = reinterpret_cast<const float4*>(rec)[1];
+            n2 = rec[8];
+        };
+        fetch(0);
+#pragma unroll 1
+        for (int k = 0; k < nv; ++k) {
+            const float* rec;
+            const CamD& cam = view(k, rec);
+            const float4 r0 = n0, r1 = n1;
+            const float gcol[3] = {r1.z, r1.w, n2};
+            fetch(k + 1);
+            if (!((seen >> k) & 1u)) continue;
+            // opaque per view: the coefficients stay in LDS, and products of
+            // scales and rotation are formed again, instead of being held in
+            // registers across the loop
+            int l = lane;
+            asm volatile("" : "+v"(l), "+v"(S3.s[0]), "+v"(S3.s[1]), "+v"(S3.s[2]));
+            asm volatile("" : "+v"(S3.qn[0]), "+v"(S3.qn[1]), "+v"(S3.qn[2]), "+v"(S3.qn[3]));
+            // colour: c = max(0, sum_k Y_k(d) f_k + 1/2), d = unit(mu - campos)
+            double gd[3] = {0.0, 0.0, 0.0};
+            {
+                double d[3], Y[K], graw[3];
+                const double inv = view_direction(mu, cam, d);
+                sh_eval<D>(d[0], d[1], d[2], Y);
+#pragma unroll
+                for (int ch = 0; ch < 3; ++ch) {
+                    double c_ = 0.5;
+#pragma unroll
+                    for (int q = 0; q < K; ++q) c_ += Y[q] * (double)sh[3 * q + ch][l];
+                    graw[ch] = c_ >= 0.0 ? (double)gcol[ch] : 0.0;
+                    open |= c_ >= 0.0 ? 1u << (3 * k + ch) : 0u;
+                }
+                if (D >= 1) {
+                    asm volatile("" : "+v"(l));  // read again, not kept
+#pragma unroll
+                    for (int q = 1; q < K; ++q) {
+                        const double g = (double)sh[3 * q][l] * graw[0] + (double)sh[3 * q + 1][l] * graw[1] +
+                                         (double)sh[3 * q + 2][l] * graw[2];
+                        double dx, dy, dz;
+                        sh_grad_k(q, d[0], d[1], d[2], dx, dy, dz);
+                        gd[0] += g * dx;
+                        gd[1] += g * dy;
+                        gd[2] += g * dz;
+                    }
+                    const double dd = gd[0] * d[0] + gd[1] * d[1] + gd[2] * d[2];
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) gd[q] = (gd[q] - d[q] * dd) * inv;
+                }
+            }
+            double gmu[3], glog[3], gqraw[4];
+            bwd_geometry(mu, S3, cam, r0.x, r0.y, r0.z, r0.w, r1.x, gmu, glog, gqraw);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) add(q, gmu[q] + gd[q]);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) add(3 + q, glog[q]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) add(6 + q, gqraw[q]);
+            add(10, (double)r1.y * go_do);
         }
-        const double dd = gd[0] * d0 + gd[1] * d1 + gd[2] * d2;
-        gmu[0] += (gd[0] - d0 * dd) / dl;
-        gmu[1] += (gd[1] - d1 * dd) / dl;
-        gmu[2] += (gd[2] - d2 * dd) / dl;
+#pragma unroll
+        for (int r = 0; r < 11; ++r) row_start(grads, r, n)[lane] = acc[r];
     }
-    const double o = 1.0 / (1.0 + exp(-prow(P, 10, n, i)));
+    __builtin_amdgcn_sched_barrier(0);  // one view: the SH rows are not loaded ahead of the first walk
+    float acc[3 * K];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) acc(k, gmu[k]);
+    for (int r = 0; r < 3 * K; ++r) acc[r] = row_start(grads, 11 + r, n)[lane];
+    float ahead[3];
+    const auto fetch = [&](int k) {
+        if (!((seen >> k) & 1u)) return;
+        const float* rec;
+        view(k, rec);
 #pragma unroll
-    for (int k = 0; k < 3; ++k) acc(3 + k, glog[k]);
+        for (int ch = 0; ch < 3; ++ch) ahead[ch] = rec[lane * PGS_GRAD2D_STRIDE + 6 + ch];
+    };
+    fetch(0);
+#pragma unroll 1
+    for (int k = 0; k < nv; ++k) {
+        const float* rec;
+        const CamD& cam = view(k, rec);
+        double d[3], Y[K], graw[3];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) acc(6 + k, gqraw[k]);
-    acc(10, go * o * (1.0 - o));
+        for (int ch = 0; ch < 3; ++ch) graw[ch] = (open >> (3 * k + ch)) & 1u ? (double)ahead[ch] : 0.0;
+        fetch(k + 1);
+        if (!((seen >> k) & 1u)) continue;
+        view_direction(mu, cam, d);
+        sh_eval<D>(d[0], d[1], d[2], Y);
+#pragma unroll
+        for (int q = 0; q < K; ++q)
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) acc[3 * q + ch] = (float)((double)acc[3 * q + ch] + Y[q] * graw[ch]);
+    }
+#pragma unroll
+    for (int r = 0; r < 3 * K; ++r) row_start(grads, 11 + r, n)[lane] = acc[r];
 }
 
 template <int D>
-__global__ __launch_bounds__(256) void k_project_bwd(const float* __restrict__ P, int n, CamD cam,
-                                                     const int* __restrict__ radius,
-                                                     const float* __restrict__ g2d,
-                                                     float* __restrict__ grads) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n || radius[i] == 0) return;
-    Shape S3;
-    shape_of(P, n, i, S3);
-    project_bwd_view<D>(P, n, i, S3, cam, g2d + (size_t)i * PGS_GRAD2D_STRIDE, [&](int r, double g) {
-        float* dst = &grads[(size_t)r * n + i];
-        *dst = (float)((double)*dst + g);
-    });
+__global__ __launch_bounds__(64, D == 3 ? 2 : 3) void k_project_bwd(const float* __restrict__ P, int n, CamD cam,
+                                                       const int* __restrict__ radius,
+                                                       const float* __restrict__ g2d, float* __restrict__ grads) {
+    __shared__ float sh[3 * (D + 1) * (D + 1)][64];
+    const int i0 = blockIdx.x * 64, lane = threadIdx.x;
+    if (i0 + lane >= n || radius[i0 + lane] == 0) return;
+    project_bwd_rows<D>(P + i0, n, lane, 1, 1u,
+                        [&](int, const float*& rec) -> const CamD& {
+                            rec = g2d + (size_t)i0 * PGS_GRAD2D_STRIDE;
+                            return cam;
+                        },
+                        grads + i0, sh);
 }
 
-// Every view of a launch for one Gaussian, its canonical rows accumulated
-// in registers: each view adds in float64 and rounds to float32, in view
-// order, as launching the one-view kernel per view would; the rows are read
-// and written once.
 template <int D>
-__global__ __launch_bounds__(256) void k_project_bwd_views(const float* __restrict__ P, int n, LaunchViews lv,
-                                                           const int* __restrict__ radius_all,
-                                                           const float* __restrict__ g2d_all,
-                                                           float* __restrict__ grads) {
-    constexpr int F = 11 + 3 * (D + 1) * (D + 1);
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    bool any = false;
-    for (int k = 0; k < lv.nv; ++k) any |= radius_all[(size_t)(lv.v0 + k) * n + i] != 0;
-    if (!any) return;
-    float acc[F];
+__global__ __launch_bounds__(64, 3) void k_project_bwd_views(const float* __restrict__ P, int n, LaunchViews lv,
+                                                             const int* __restrict__ radius_all,
+                                                             const float* __restrict__ g2d_all,
+                                                             float* __restrict__ grads) {
+    static_assert(3 * kLaunchViews <= 32, "a bit per view and channel");
+    __shared__ float sh[3 * (D + 1) * (D + 1)][64];
+    const int i0 = blockIdx.x * 64, lane = threadIdx.x;
+    if (i0 + lane >= n) return;
+    uint32_t seen = 0u;
 #pragma unroll
-    for (int r = 0; r < F; ++r) acc[r] = grads[(size_t)r * n + i];
-    Shape S3;
-    shape_of(P, n, i, S3);
-    for (int k = 0; k < lv.nv; ++k) {
-        const size_t v = (size_t)(lv.v0 + k);
-        if (radius_all[v * n + i] == 0) continue;
-        // the parameter pointer made opaque per view: the parameters are
-        // re-read (from cache) by every view instead of being held in
-        // registers across the loop
-        const float* Pv = P;
-        asm volatile("" : "+s"(Pv));
-        project_bwd_view<D>(Pv, n, i, S3, lv.cam[k], g2d_all + (v * n + i) * PGS_GRAD2D_STRIDE,
-                            [&](int r, double g) { acc[r] = (float)((double)acc[r] + g); });
-    }
-#pragma unroll
-    for (int r = 0; r < F; ++r) grads[(size_t)r * n + i] = acc[r];
+    for (int k = 0; k < kLaunchViews; ++k)
+        if (k < lv.nv && radius_all[(size_t)(lv.v0 + k) * n + i0 + lane] != 0) seen |= 1u << k;
+    if (seen == 0u) return;
+    project_bwd_rows<D>(P + i0, n, lane, lv.nv, seen,
+                        [&](int k, const float*& rec) -> const CamD& {
+                            rec = g2d_all + ((size_t)(lv.v0 + k) * n + i0) * PGS_GRAD2D_STRIDE;
+                            return lv.cam[k];
+                        },
+                        grads + i0, sh);
 }
 
 }  // namespace
@@ -525,7 +659,7 @@ extern "C" pgs_status pgs_project_bwd(const float* params_dev, int32_t n, int32_
     if (n == 0) return PGS_OK;
     PGS_REQUIRE(params_dev && radius_dev && grad2d_dev && grads_dev, "pgs_project_bwd: null pointer");
     const pgs::CamD cam = pgs::make_cam(*cam_host);
-    const dim3 grid((n + 255) / 256), block(256);
+    const dim3 grid((n + 63) / 64), block(64);
     hipStream_t s = pgs::as_stream(stream);
     switch (sh_degree) {
         case 0: k_project_bwd<0><<<grid, block, 0, s>>>(params_dev, n, cam, radius_dev, grad2d_dev, grads_dev); break;
@@ -564,7 +698,7 @@ extern "C" pgs_status pgs_project_views(const pgs_view_batch* views, const float
     if (n == 0) return PGS_OK;
     PGS_REQUIRE(params_dev && proj_all_dev && radius_all_dev && rect_all_dev && touched_all_dev,
                 "pgs_project_views: null pointer");
-    const dim3 grid((n + 255) / 256), block(256);
+    const dim3 grid((n + 63) / 64), block(64);
     hipStream_t s = pgs::as_stream(stream);
     const int tw = views->tile_w, th = views->tile_h;
     for (int v0 = 0; v0 < views->n_views; v0 += kLaunchViews) {
@@ -588,7 +722,7 @@ extern "C" pgs_status pgs_project_bwd_views(const pgs_view_batch* views, const f
     PGS_REQUIRE(sh_degree >= 0 && sh_degree <= 3, "pgs_project_bwd_views: sh_degree %d", sh_degree);
     if (n == 0) return PGS_OK;
     PGS_REQUIRE(params_dev && radius_all_dev && grad2d_all_dev && grads_dev, "pgs_project_bwd_views: null pointer");
-    const dim3 grid((n + 255) / 256), block(256);
+    const dim3 grid((n + 63) / 64), block(64);
     hipStream_t s = pgs::as_stream(stream);
     for (int v0 = 0; v0 < views->n_views; v0 += kLaunchViews) {
         const LaunchViews lv = launch_views(*views, v0, min(kLaunchViews, views->n_views - v0));

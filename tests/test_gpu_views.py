@@ -278,6 +278,39 @@ def test_project_views_match_per_view_calls(deg):
     np.testing.assert_array_equal(grads.cpu().numpy(), grads1.cpu().numpy())
 
 
+@pytest.mark.parametrize("n", [1, 63, 64, 130])
+@pytest.mark.parametrize("deg", [0, 1, 2, 3])
+def test_project_views_part_waves(n, deg):
+    # last waves of every fill, at every SH degree (its own register and LDS
+    # layout): the same bits as view by view, gradients of culled Gaussians
+    # and records past the last untouched
+    from paper_2601_17354_amd import binding as B
+    P = synth.surface_gaussians(synth.spheres_planes_scene(2), 400, seed=5, sh_degree=deg, logit_sigma=0.5)[:, :n]
+    cams = [dict(c, fx=0.4 * c["fx"]) for c in synth.ring_cameras(3, 160, 120)]
+    views, V, F = B.ViewBatch(cams, (16, 16)), 3, P.shape[0]
+    say(f"[views] part waves n={n} sh={deg}")
+    params = torch.as_tensor(np.ascontiguousarray(P), device=DEV)
+    a, b = ([torch.full((V * n * 16 + 64,), 7.0, device=DEV), torch.zeros((V, n), dtype=torch.int32, device=DEV),
+             torch.zeros((V, 2, n), dtype=torch.int32, device=DEV), torch.zeros((V, n), dtype=torch.int32, device=DEV)]
+            for _ in range(2))
+    B.pgs_project_views(views, params, n, deg, *a)
+    proj1 = b[0][:V * n * 16].view(V, n, 16)
+    for v, cam in enumerate(cams):
+        B.pgs_project(params, n, deg, cam, 16, 16, proj1[v], b[1][v], b[2][v], b[3][v])
+    rng = np.random.default_rng(n + deg)
+    g2d = torch.as_tensor(rng.normal(size=(V, n, 16)).astype(np.float32), device=DEV)
+    g0 = rng.normal(size=(F, n)).astype(np.float32)
+    ga, gb = torch.as_tensor(g0, device=DEV), torch.as_tensor(g0, device=DEV)
+    B.pgs_project_bwd_views(views, params, n, deg, a[1], g2d, ga)
+    for v, cam in enumerate(cams):
+        B.pgs_project_bwd(params, n, deg, cam, a[1][v], g2d[v], gb)
+    torch.cuda.synchronize()
+    for x, y in zip(a + [ga], b + [gb]):
+        np.testing.assert_array_equal(x.cpu().numpy(), y.cpu().numpy())
+    culled = (a[1] == 0).all(0).cpu().numpy()
+    np.testing.assert_array_equal(ga.cpu().numpy()[:, culled], g0[:, culled])
+
+
 def test_adam_step_dev_matches_host_counter():
     from paper_2601_17354_amd import binding as B
     rng = np.random.default_rng(12)
