@@ -207,3 +207,45 @@ def test_cached_and_recompute_agree(case):
     a, b = case["gc"]["grads"], case["gr"]["grads"]
     for r in range(a.shape[0]):
         assert_block_close(a[r], b[r], GRAD_TOL, what=f"row {r}")
+
+
+@pytest.mark.parametrize("tile", [(16, 16), (8, 8), (32, 8)], ids=lambda t: f"{t[0]}x{t[1]}")
+@pytest.mark.parametrize("n", [1, 3, 5, 64, 66, 257, 515])
+def test_list_lengths_and_tile_widths(n, tile):
+    # lists around the four steps taken together, the 64-step windows and the
+    # 256-splat batches, in tiles whose 16-lane rows are one pixel row and two
+    P, cam, _ = synth.cfg1_inputs(5, n=n, width=35, height=27, focal=30.0)
+    P[3:6] += 1.5
+    P[10] -= 2.0
+    dl = np.random.default_rng(n).normal(size=(3, 27, 35)).astype(np.float32)
+    bg = (0.2, 0.4, 0.1)
+    say(f"[parity] lists n={n} tile={tile}")
+    proj, bins, fwd = pipeline.forward(P, cam, *tile, bg=bg)
+    o_grads, o_g2d, taint = pipeline.backward(P, cam, proj, bins, fwd, dl, "cached")
+    ok = ~fwd["marginal"]
+    for cached in (True, False):
+        g = run_gpu(P, cam, 0, cached=cached, bg=bg, dl_dimage=dl, tile=tile)
+        for c in range(3):
+            assert_block_close(g["image"][c], fwd["image"][c], IMG_TOL, mask=ok, what=f"image[{c}]")
+        assert (g["n_contrib"][ok] == fwd["n_contrib"][ok]).all()
+        for f, name in enumerate(OUT_FIELDS):
+            assert_block_close(g["grad2d"][f], o_g2d[f], GRAD_TOL, mask=~taint, what=f"cached={cached} d{name}")
+
+
+def test_recompute_keeps_a_bad_pixel_to_its_own_splats():
+    # an infinite and a not-a-number dL/dC reach only the splats that those
+    # pixels composite
+    P, cam, _ = synth.cfg1_inputs(6, n=300, width=48, height=32, focal=40.0)
+    _, _, fwd = pipeline.forward(P, cam)
+    dl = np.random.default_rng(1).normal(size=(3, 32, 48)).astype(np.float32)
+    clean = run_gpu(P, cam, 0, cached=False, dl_dimage=dl)
+    bad = dl.copy()
+    bad[:, 13, 20], bad[1, 18, 26] = np.nan, np.inf
+    g = run_gpu(P, cam, 0, cached=False, dl_dimage=bad)
+    from oracle.render import replay_entries
+    hit = {int(clean["values"][e[0]]) for x, y in ((20, 13), (26, 18)) for e in replay_entries(fwd, x, y)}
+    rest = np.asarray([i not in hit for i in range(300)])
+    assert len(hit) > 3 and not np.isfinite(g["grad2d"][:, ~rest]).all()
+    assert np.isfinite(g["grad2d"][:, rest]).all()
+    for f, name in enumerate(OUT_FIELDS):
+        assert_block_close(g["grad2d"][f], clean["grad2d"][f], GRAD_TOL, mask=rest, what=f"d{name}")
