@@ -4,15 +4,26 @@
 // SSIM (Wang et al. 2004): 11x11 Gaussian window (sigma 1.5), C1 = 1e-4,
 // C2 = 9e-4, zero padding, mean over pixels and channels.
 //
-// One kernel of one-wave workgroups does all of it: the windowed sums mu_x,
-// mu_y, E[(x - y)^2], E[xy] (the denominators need the squares only as the
-// sums mu_x^2 + mu_y^2 = 2 mu_x mu_y + (mu_x - mu_y)^2 and var_x + var_y =
-// 2 cov + var(x - y), and so equal the numerators where x equals y), the
-// SSIM map's partial derivatives m1 = dS/dmu_x, m2 = dS/dE[x^2],
-// m3 = dS/dE[xy], and
+// Forward: the windowed sums mu_x, mu_y, E[x^2], E[y^2], E[xy] -> the SSIM map's
+// partial derivatives m1 = dS/dmu_x, m2 = dS/dE[x^2], m3 = dS/dE[xy] and the
+// sum of the map.  Backward: the same windowed pass over (m1, m2, m3) gives
 //     dSSIM/dx_p = (1/N) (w*m1 + 2 x_p w*m2 + y_p w*m3)(p),
-// the adjoint of the zero-padded blur being the zero-padded blur (m is zero
-// outside the image).
+// the adjoint of the zero-padded blur being the zero-padded blur.
+//
+// Both walk a strip of 128 columns, two neighbouring ones a lane, down some
+// rows with a workgroup of one wave.  Each input row (with a 5-column halo),
+// loaded two rows ahead, passes through LDS and is blurred horizontally; the
+// results of the last 11 rows sit in a register ring, from which the vertical
+// pass forms the 11 x 11 window sums.  Where the image is flat the gradient is a
+// difference of terms a thousand times its size, so every sum is taken in the
+// order of its taps, with the roundings of the plain formula.
+//
+// Bound by vector issue (forward) and by memory (backward).  With one column
+// a lane, 22 (33) single LDS reads a pixel, addresses and bounds in vector
+// registers and 32 rows a wave whatever the image, 1920 x 1440 took 125 us with
+// the final sum, now 119; 1024 x 1024 77, now 60; 317 x 243 55, now 26.  (One
+// kernel for both, with the denominators from the blurred squared difference,
+// took 93 for the largest but changed flat gradients by 1e-4 of themselves.)
 #include <math.h>
 
 #include "common.hpp"
@@ -20,9 +31,8 @@
 namespace {
 
 constexpr int kHalo = 5;
-constexpr int kMW = 128;                // columns of a strip whose m a wave forms, two per lane
-constexpr int kSW = kMW - 2 * kHalo;    // 118 output columns
-constexpr int kRowW = kMW + 2 * kHalo;  // 138 input columns
+constexpr int kSW = 128;                // output columns of a strip, two per lane
+constexpr int kRowW = kSW + 2 * kHalo;  // 138 input columns
 constexpr float kC1 = 1e-4f, kC2 = 9e-4f;
 
 struct Win {
@@ -83,150 +93,197 @@ __device__ __forceinline__ float row_load(__amdgpu_buffer_rsrc_t row, int byte) 
     return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(row, byte, 0, 0));
 }
 
-// Horizontal blur of the two windows that begin at p[0] and p[1].
-__device__ __forceinline__ void blur_pair(const Win& win, const float* p, float (&out)[2]) {
-    float2 v[6];
+__device__ __forceinline__ void row_store(__amdgpu_buffer_rsrc_t row, int byte, float v) {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(v), row, byte, 0, 0);
+}
+
+// Input row r0 - 5 + ii of a strip of NQ planes: lane l takes columns l, l + 64
+// and (for l < 10) l + 128.
+template <int NQ>
+struct RowLoad {
+    float v[NQ][3];
+    __device__ __forceinline__ void load(const float* const* planes, int W, int H, int c0, int gy, int l) {
+        const int byte = (c0 - kHalo + l) * 4;
 #pragma unroll
-    for (int u = 0; u < 6; ++u) v[u] = *reinterpret_cast<const float2*>(p + 2 * u);
+        for (int f = 0; f < NQ; ++f) {
+            const auto row = row_buffer(planes[f], gy, W, H);
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-        float a = win.w[0] * (c ? v[0].y : v[0].x);
+            for (int h = 0; h < 3; ++h) v[f][h] = row_load(row, byte + 256 * h >= 0 ? byte + 256 * h : kNoByte);
+        }
+    }
+    __device__ __forceinline__ void store(float (*lds)[kRowW + 2], int l) const {
 #pragma unroll
-        for (int t = 1; t < 11; ++t) a = fmaf(win.w[t], (t + c) & 1 ? v[(t + c) / 2].y : v[(t + c) / 2].x, a);
-        out[c] = a;
+        for (int h = 0; h < 3; ++h)
+            if (h < 2 || l < kRowW - 128) {
+#pragma unroll
+                for (int f = 0; f < NQ; ++f) lds[f][l + 64 * h] = v[f][h];
+            }
+    }
+};
+
+// The 12 values of two neighbouring windows.
+__device__ __forceinline__ void read_windows(const float* p, float (&v)[12]) {
+#pragma unroll
+    for (int u = 0; u < 6; ++u) {
+        const float2 q = *reinterpret_cast<const float2*>(p + 2 * u);
+        v[2 * u] = q.x;
+        v[2 * u + 1] = q.y;
     }
 }
 
-// A wave walks a strip of 118 output columns down `rows` output rows.  Each
-// input row (10 columns of halo on either side, loaded two rows ahead) passes
-// through LDS and is blurred horizontally, two neighbouring columns a lane, so
-// that a product x y is formed once for both windows and the LDS is read in
-// pairs; the results of the last 11 rows sit in a register ring, from which
-// the vertical pass forms the window sums of row i - 5 and the lane's two m
-// triples.  These take the same way again, LDS, horizontal, ring, vertical,
-// to the gradient of row i - 10.
-//
-// Bound by the vector units (about 300 instructions a pixel, the 20 halo rows
-// of a strip included).  Two kernels with the nine planes of m in memory
-// between them moved 3.7 times the bytes and spent 11 x 3 products and 22
-// single LDS reads a pixel on each window: 1920 x 1440 125 us with the final sum, now 93;
-// 317 x 243 55 us, now 26.
-__global__ __launch_bounds__(64, 2) void k_ssim(const float* __restrict__ x, const float* __restrict__ y, int W, int H,
-                                                int rows, Win win, float l1_scale, float ssim_scale,
-                                                float* __restrict__ dl, float* __restrict__ part_l1,
-                                                float* __restrict__ part_s) {
-    __shared__ __align__(8) float s_in[2][4][kRowW + 6];
-    __shared__ __align__(8) float s_m[2][3][kRowW + 2];
+template <int NF>
+__device__ __forceinline__ void vertical(const Win& win, const float (&ring)[11][NF][2], int k, int c, float (&q)[NF]) {
+#pragma unroll
+    for (int f = 0; f < NF; ++f) q[f] = win.w[0] * ring[(k + 1) % 11][f][c];
+#pragma unroll
+    for (int t = 1; t < 11; ++t)
+#pragma unroll
+        for (int f = 0; f < NF; ++f) q[f] = fmaf(win.w[t], ring[(k + 1 + t) % 11][f][c], q[f]);
+}
+
+__global__ __launch_bounds__(64, 2) void k_ssim_fwd(const float* __restrict__ x, const float* __restrict__ y, int W,
+                                                    int H, int rows, Win win, float* __restrict__ m,
+                                                    float* __restrict__ part) {
+    __shared__ __align__(8) float lds[2][2][kRowW + 2];
     const int l = threadIdx.x, ch = blockIdx.z, c0 = blockIdx.x * kSW, r0 = blockIdx.y * rows;
     const size_t plane = (size_t)W * H;
-    x += ch * plane;
-    y += ch * plane;
-    dl += ch * plane;
-    const int rows_out = min(rows, H - r0), rows_in = rows_out + 4 * kHalo;
-    const int mcol = c0 - kHalo + 2 * l;  // this lane's columns of m
-    const bool m_in[2] = {mcol >= 0 && mcol < W, mcol + 1 >= 0 && mcol + 1 < W};
-    const bool own[2] = {m_in[0] && mcol >= c0 && mcol < c0 + kSW, m_in[1] && mcol + 1 >= c0 && mcol + 1 < c0 + kSW};
-    const int in_byte = (c0 - 2 * kHalo + l) * 4;
-    const int in_first = in_byte >= 0 ? in_byte : kNoByte;
-    const int out_byte = l < kSW / 2 ? (c0 + 2 * l) * 4 : kNoByte;  // lanes 59..63 have no output column
-    float ring[11][4][2], mring[11][3][2];
-    float ssum = 0.f, l1sum = 0.f;
-    float ahead[2][2][3];  // [rows ahead][plane][column group]
-    const auto fetch = [&](int ii, float (&v)[2][3]) {
-        const int gy = r0 - 2 * kHalo + ii;
-        const auto xr = row_buffer(x, gy, W, H), yr = row_buffer(y, gy, W, H);
-#pragma unroll
-        for (int h = 0; h < 3; ++h) {
-            v[0][h] = row_load(xr, h ? in_byte + 256 * h : in_first);
-            v[1][h] = row_load(yr, h ? in_byte + 256 * h : in_first);
-        }
-    };
-    fetch(0, ahead[0]);
-    fetch(1, ahead[1]);
+    const float* planes[2] = {x + ch * plane, y + ch * plane};
+    m += 3 * ch * plane;
+    const int col = c0 + 2 * l, rows_in = min(rows, H - r0) + 2 * kHalo;
+    float ring[11][5][2];
+    float ssum = 0.f;
+    RowLoad<2> a1, a2;
+    a1.load(planes, W, H, c0, r0 - kHalo, l);
+    a2.load(planes, W, H, c0, r0 - kHalo + 1, l);
     for (int base = 0; base < rows_in; base += 11) {
 #pragma unroll
         for (int k = 0; k < 11; ++k) {
             const int ii = base + k;
             if (ii < rows_in) {
-                float(*row)[kRowW + 6] = s_in[ii & 1];
-#pragma unroll
-                for (int h = 0; h < 3; ++h) {
-                    const float xe = ahead[0][0][h], ye = ahead[0][1][h], d = xe - ye;
-                    if (h < 2 || l < kRowW - 128) {
-                        row[0][l + 64 * h] = xe;
-                        row[1][l + 64 * h] = ye;
-                        row[2][l + 64 * h] = d * d;
-                        row[3][l + 64 * h] = xe * ye;
-                    }
-#pragma unroll
-                    for (int f = 0; f < 2; ++f) ahead[0][f][h] = ahead[1][f][h];
-                }
-                fetch(ii + 2, ahead[1]);
+                float(*row)[kRowW + 2] = lds[ii & 1];
+                a1.store(row, l);
+                a1 = a2;
+                a2.load(planes, W, H, c0, r0 - kHalo + ii + 2, l);
                 wave_fence();
+                float xv[12], yv[12];
+                read_windows(&row[0][2 * l], xv);
+                read_windows(&row[1][2 * l], yv);
 #pragma unroll
-                for (int f = 0; f < 4; ++f) blur_pair(win, &row[f][2 * l], ring[k][f]);
-                if (ii >= 2 * kHalo) {
-                    const int gm = r0 - 3 * kHalo + ii;  // row of m
-                    const bool row_in = gm >= 0 && gm < H, own_row = gm >= r0 && gm < r0 + rows_out;
-                    float m[3][2];
+                for (int c = 0; c < 2; ++c) {
+                    float a[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int c = 0; c < 2; ++c) {
-                        float q[4];
-#pragma unroll
-                        for (int f = 0; f < 4; ++f) {
-                            q[f] = win.w[0] * ring[(k + 1) % 11][f][c];
-#pragma unroll
-                            for (int t = 1; t < 11; ++t) q[f] = fmaf(win.w[t], ring[(k + 1 + t) % 11][f][c], q[f]);
+                    for (int t = 0; t < 11; ++t) {
+                        const float w = win.w[t], xe = xv[t + c], ye = yv[t + c], wx = w * xe, wy = w * ye;
+                        if (t == 0) {
+                            a[0] = wx;
+                            a[1] = wy;
+                            a[2] = wx * xe;
+                            a[3] = wy * ye;
+                            a[4] = wx * ye;
+                        } else {
+                            a[0] = fmaf(w, xe, a[0]);
+                            a[1] = fmaf(w, ye, a[1]);
+                            a[2] = fmaf(wx, xe, a[2]);
+                            a[3] = fmaf(wy, ye, a[3]);
+                            a[4] = fmaf(wx, ye, a[4]);
                         }
-                        const float mx = q[0], my = q[1];
-                        const float N1 = 2.f * mx * my + kC1, N2 = 2.f * (q[3] - mx * my) + kC2;
-                        const float md = mx - my, md2 = md * md;
-                        const float D1 = N1 + md2, D2 = N2 + (q[2] - md2);
-                        const float inv = 1.f / (D1 * D2), i1 = D2 * inv, i2 = D1 * inv;
-                        const float S = N1 * N2 * inv;
-                        const bool in = row_in && m_in[c];
-                        m[0][c] = in ? 2.f * (my * (N2 - N1) * inv - S * mx * (i1 - i2)) : 0.f;
-                        m[1][c] = in ? -S * i2 : 0.f;
-                        m[2][c] = in ? 2.f * N1 * inv : 0.f;
-                        ssum += own_row && own[c] ? S : 0.f;
                     }
-                    float(*mrow)[kRowW + 2] = s_m[ii & 1];
 #pragma unroll
-                    for (int f = 0; f < 3; ++f)
-                        *reinterpret_cast<float2*>(&mrow[f][2 * l]) = make_float2(m[f][0], m[f][1]);
-                    wave_fence();
-#pragma unroll
-                    for (int f = 0; f < 3; ++f) blur_pair(win, &mrow[f][2 * l], mring[k][f]);
+                    for (int f = 0; f < 5; ++f) ring[k][f][c] = a[f];
                 }
-                if (ii >= 4 * kHalo) {
-                    const int o = r0 + ii - 4 * kHalo;
-                    const auto xr = row_buffer(x, o, W, H), yr = row_buffer(y, o, W, H), dr = row_buffer(dl, o, W, H);
+                if (ii >= 2 * kHalo) {
+                    const int o = r0 + ii - 2 * kHalo;  // output row
 #pragma unroll
                     for (int c = 0; c < 2; ++c) {
-                        const float xv = row_load(xr, out_byte + 4 * c), yv = row_load(yr, out_byte + 4 * c);
-                        float b[3];
-#pragma unroll
-                        for (int f = 0; f < 3; ++f) {
-                            b[f] = win.w[0] * mring[(k + 1) % 11][f][c];
-#pragma unroll
-                            for (int t = 1; t < 11; ++t) b[f] = fmaf(win.w[t], mring[(k + 1 + t) % 11][f][c], b[f]);
-                        }
-                        const float d = xv - yv;  // zero outside the image
-                        l1sum += fabsf(d);
-                        const float sgn = d > 0.f ? l1_scale : (d < 0.f ? -l1_scale : 0.f);
-                        const float g = sgn - ssim_scale * (b[0] + 2.f * xv * b[1] + yv * b[2]);
-                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(g), dr, out_byte + 4 * c, 0, 0);
+                        float q[5];
+                        vertical<5>(win, ring, k, c, q);
+                        const float mx = q[0], my = q[1];
+                        const float vx = q[2] - mx * mx, vy = q[3] - my * my, cxy = q[4] - mx * my;
+                        const float N1 = 2.f * mx * my + kC1, N2 = 2.f * cxy + kC2;
+                        const float D1 = mx * mx + my * my + kC1, D2 = vx + vy + kC2;
+                        const float inv = 1.f / (D1 * D2);
+                        const float S = N1 * N2 * inv;
+                        const float m1 = (2.f * my * N2 - 2.f * my * N1) * inv - S * (2.f * mx / D1 - 2.f * mx / D2);
+                        const float m2 = -S / D2;
+                        const float m3 = 2.f * N1 * inv;
+                        row_store(row_buffer(m, o, W, H), (col + c) * 4, m1);
+                        row_store(row_buffer(m + plane, o, W, H), (col + c) * 4, m2);
+                        row_store(row_buffer(m + 2 * plane, o, W, H), (col + c) * 4, m3);
+                        ssum += col + c < W ? S : 0.f;
                     }
                 }
             }
         }
     }
-    const float tot_s = wave_sum_to_lane63(ssum), tot_l1 = wave_sum_to_lane63(l1sum);
-    if (l == 63) {
-        const int b = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-        part_s[b] = tot_s;
-        part_l1[b] = tot_l1;
+    const float tot = wave_sum_to_lane63(ssum);
+    if (l == 63) part[(blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = tot;
+}
+
+__global__ __launch_bounds__(64, 3) void k_ssim_bwd(const float* __restrict__ x, const float* __restrict__ y, int W,
+                                                    int H, int rows, Win win, const float* __restrict__ m,
+                                                    float l1_scale, float ssim_scale, float* __restrict__ dl,
+                                                    float* __restrict__ part) {
+    __shared__ __align__(8) float lds[2][3][kRowW + 2];
+    const int l = threadIdx.x, ch = blockIdx.z, c0 = blockIdx.x * kSW, r0 = blockIdx.y * rows;
+    const size_t plane = (size_t)W * H;
+    const float* planes[3] = {m + 3 * ch * plane, m + (3 * ch + 1) * plane, m + (3 * ch + 2) * plane};
+    x += ch * plane;
+    y += ch * plane;
+    dl += ch * plane;
+    const int byte = (c0 + 2 * l) * 4, rows_in = min(rows, H - r0) + 2 * kHalo;
+    float ring[11][3][2];
+    float l1sum = 0.f;
+    RowLoad<3> a1, a2;
+    a1.load(planes, W, H, c0, r0 - kHalo, l);
+    a2.load(planes, W, H, c0, r0 - kHalo + 1, l);
+    for (int base = 0; base < rows_in; base += 11) {
+#pragma unroll
+        for (int k = 0; k < 11; ++k) {
+            const int ii = base + k;
+            if (ii < rows_in) {
+                float(*row)[kRowW + 2] = lds[ii & 1];
+                a1.store(row, l);
+                a1 = a2;
+                a2.load(planes, W, H, c0, r0 - kHalo + ii + 2, l);
+                const int o = r0 + ii - 2 * kHalo;  // output row, from ii = 10 on
+                const auto xr = row_buffer(x, o, W, H), yr = row_buffer(y, o, W, H);
+                float xv[2], yv[2];
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    xv[c] = row_load(xr, byte + 4 * c);
+                    yv[c] = row_load(yr, byte + 4 * c);
+                }
+                wave_fence();
+#pragma unroll
+                for (int f = 0; f < 3; ++f) {
+                    float v[12];
+                    read_windows(&row[f][2 * l], v);
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        float a = win.w[0] * v[c];
+#pragma unroll
+                        for (int t = 1; t < 11; ++t) a = fmaf(win.w[t], v[t + c], a);
+                        ring[k][f][c] = a;
+                    }
+                }
+                if (ii >= 2 * kHalo) {
+                    const auto dr = row_buffer(dl, o, W, H);
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        float b[3];
+                        vertical<3>(win, ring, k, c, b);
+                        const float d = xv[c] - yv[c];  // zero outside the image
+                        l1sum += fabsf(d);
+                        const float sgn = d > 0.f ? 1.f : (d < 0.f ? -1.f : 0.f);
+                        row_store(dr, byte + 4 * c,
+                                  l1_scale * sgn - ssim_scale * (b[0] + 2.f * xv[c] * b[1] + yv[c] * b[2]));
+                    }
+                }
+            }
+        }
     }
+    const float tot = wave_sum_to_lane63(l1sum);
+    if (l == 63) part[(blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = tot;
 }
 
 // Sums the per-block partials in a fixed order (deterministic, no atomics):
@@ -269,16 +326,6 @@ __global__ __launch_bounds__(kFinalThreads) void k_loss_final(const float* __res
 
 constexpr int kL1Blocks = 1024;
 
-__global__ __launch_bounds__(256) void k_copy(const float* __restrict__ from, float* __restrict__ to, size_t N) {
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < N; i += (size_t)gridDim.x * blockDim.x)
-        to[i] = from[i];
-}
-
-inline bool overlap(const float* a, const float* b, size_t N) {
-    const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b), bytes = N * sizeof(float);
-    return p < q + bytes && q < p + bytes;
-}
-
 // Squared error of the two images clamped to [0, 1], per-block partials.
 __global__ __launch_bounds__(256) void k_sq_err(const float* __restrict__ x, const float* __restrict__ y,
                                                 size_t N, float* __restrict__ part) {
@@ -304,17 +351,18 @@ __global__ __launch_bounds__(kFinalThreads) void k_psnr_final(const float* __res
     }
 }
 
-// Output rows of a wave.  Two waves fit on each of the card's 1024 SIMDs, and
-// two take about 1.25 times as long as one; a wave lasts about rows + 12 row
-// times (the 20 halo rows skip the later stages).  Hence few rows where the
-// image has little work, and waves just below a multiple of 1024 elsewhere.
+// Output rows of a wave.  A wave lasts about rows + 8 row times (the first 10
+// input rows skip the later stages); two waves on one of the card's 1024 SIMDs
+// take about 1.25 times as long as one.  Hence few rows where the image has
+// little work (317 x 243 with 4 rows 26 us, with 32 58) and waves just below
+// a multiple of 2048 elsewhere.
 inline int ssim_rows(int W, int H) {
     const long strips = 3L * ((W + kSW - 1) / kSW);
     int best = 4;
     long best_cost = -1;
     for (int rows = 4; rows <= 64; ++rows) {
         const long per_simd = (strips * ((H + rows - 1) / rows) + 1023) / 1024;
-        const long cost = (5 * (per_simd / 2) + 4 * (per_simd % 2)) * (rows + 12);
+        const long cost = (5 * (per_simd / 2) + 4 * (per_simd % 2)) * (rows + 8);
         if (best_cost < 0 || cost < best_cost) {
             best = rows;
             best_cost = cost;
@@ -351,7 +399,7 @@ extern "C" pgs_status pgs_psnr(const float* x_dev, const float* y_dev, int32_t w
 
 extern "C" size_t pgs_loss_workspace(int32_t width, int32_t height) {
     if (width <= 0 || height <= 0) return 256;
-    return part_bytes(width, height) + (size_t)3 * width * height * sizeof(float);
+    return part_bytes(width, height) + (size_t)9 * width * height * sizeof(float);
 }
 
 extern "C" pgs_status pgs_loss_l1_dssim(const float* x_dev, const float* y_dev, int32_t width,
@@ -376,14 +424,10 @@ extern "C" pgs_status pgs_loss_l1_dssim(const float* x_dev, const float* y_dev, 
         const int rows = ssim_rows(width, height);
         const dim3 grid((width + kSW - 1) / kSW, (height + rows - 1) / rows, 3);
         nl = ns = ssim_blocks(width, height);
-        // a wave reads its neighbours' columns and rows of x and y while they
-        // write their gradients: written in place, these go to the workspace first
-        const bool in_place = overlap(dl_dx_dev, x_dev, N) || overlap(dl_dx_dev, y_dev, N);
-        float* out = in_place ? reinterpret_cast<float*>(static_cast<char*>(workspace_dev) + part_bytes(width, height))
-                              : dl_dx_dev;
-        k_ssim<<<grid, 64, 0, s>>>(x_dev, y_dev, width, height, rows, win, (1.f - lambda) * invN, lambda * invN, out,
-                                   part_l1, part_s);
-        if (in_place) k_copy<<<kL1Blocks, 256, 0, s>>>(out, dl_dx_dev, N);
+        float* m = reinterpret_cast<float*>(static_cast<char*>(workspace_dev) + part_bytes(width, height));
+        k_ssim_fwd<<<grid, 64, 0, s>>>(x_dev, y_dev, width, height, rows, win, m, part_s);
+        k_ssim_bwd<<<grid, 64, 0, s>>>(x_dev, y_dev, width, height, rows, win, m, (1.f - lambda) * invN,
+                                       lambda * invN, dl_dx_dev, part_l1);
     }
     k_loss_final<<<1, kFinalThreads, 0, s>>>(part_l1, nl, part_s, ns, lambda, invN, loss_dev);
     PGS_CHECK_LAUNCH("pgs_loss_l1_dssim");
