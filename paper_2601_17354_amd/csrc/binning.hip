@@ -31,20 +31,21 @@ constexpr int kScanThreads = 256;
 constexpr int kScanIpt = 8;
 constexpr int kScanItems = kScanThreads * kScanIpt;  // 2048 per block
 
-// Workgroups of a sort.  Up to kSmallSort keys: 4096 keys on 1024 threads, so
-// that at most 256 workgroups exist and each can sum the histograms of the
-// others itself (k_radix_scatter); a pass is two launches, where the scan
-// between histogram and scatter made it four of about 4.5 us each whatever
-// they move.  Beyond: 2048 keys on 256 threads and the scan.
+// Workgroups of a sort: 4096 keys on 1024 threads.  Up to kSmallSort keys at
+// most 256 workgroups exist and each sums the histograms of the others itself
+// (k_radix_scatter); a pass is two launches, where the scan between histogram
+// and scatter made it four of about 4.5 us each whatever they move.  Beyond, the
+// scan.  2048 keys on 256 threads gave a digit's run 64 bytes and scans of
+// twice the size: the sorts of eight views of 1M Gaussians 1100 us, with 4096
+// keys 940, with 8192 1010.
 constexpr uint32_t kSmallSort = 1u << 20;
-struct SmallSort {
+template <bool DIRECT>
+struct SortShape {
     static constexpr int kThreads = 1024, kRounds = 4, kKeys = kThreads * kRounds;
-    static constexpr bool kDirect = true;
+    static constexpr bool kDirect = DIRECT;
 };
-struct LargeSort {
-    static constexpr int kThreads = 256, kRounds = 8, kKeys = kThreads * kRounds;
-    static constexpr bool kDirect = false;
-};
+using SmallSort = SortShape<true>;
+using LargeSort = SortShape<false>;
 // Gaussians that one workgroup sorts and scans by itself.
 constexpr uint32_t kBlockSort = 4096;
 constexpr int kRadix = 256;
@@ -423,7 +424,7 @@ __global__ __launch_bounds__(G::kThreads) void k_radix_scatter(
             }
         }
     } else {
-        g_before = hist[(size_t)t * nb + blockIdx.x];
+        if (t < kRadix) g_before = hist[(size_t)t * nb + blockIdx.x];
     }
 #pragma unroll
     for (int k = 0; k < kRadix / 64; ++k) s_cnt[wv][64 * k + lane] = 0u;
@@ -635,7 +636,7 @@ struct SortWs {
 SortWs sort_layout(void* base, uint32_t capacity) {
     SortWs w{};
     w.small = capacity <= kSmallSort;
-    w.nb = div_up(capacity, w.small ? SmallSort::kKeys : LargeSort::kKeys);
+    w.nb = div_up(capacity, SmallSort::kKeys);
     size_t off = 0;
     char* p = static_cast<char*>(base);
     w.keys_alt = reinterpret_cast<uint64_t*>(p + off); off += align_up((size_t)capacity * 8);
