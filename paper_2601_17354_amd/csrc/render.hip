@@ -30,8 +30,8 @@ __global__ __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(EW == 3 
     int W, int H, int TX, int tile_offset, int n_tiles_total, const float* __restrict__ proj, int n,
     const uint32_t* __restrict__ values, const uint32_t* __restrict__ ranges, Trace tr,
     const float* __restrict__ dl_dimage, float* __restrict__ grad2d, const uint32_t* __restrict__ order) {
-    constexpr int BG = TW * TH;
-    __shared__ TileLds<BG> L;
+    constexpr int NW = TW * TH / 64, BG = pgs::kBwdBatch<TW * TH, NW>;
+    __shared__ TileLds<BG, pgs::kAccs<NW>> L;
     const int tile = order ? (int)order[blockIdx.x] : (int)blockIdx.x;
     const TileJob j{W, H, tile % TX, tile / TX, tile_offset + tile, proj, nullptr, nullptr, nullptr, nullptr};
     pgs::bwd_cached_tile<TW, TH, BG, EW>(j, n_tiles_total, n, values, ranges, tr, dl_dimage, grad2d, L);
@@ -43,8 +43,8 @@ __global__ __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(6))) voi
     const uint32_t* __restrict__ values, const uint32_t* __restrict__ ranges, float bg0, float bg1,
     float bg2, const float* __restrict__ t_final, const uint32_t* __restrict__ n_contrib,
     const float* __restrict__ dl_dimage, float* __restrict__ grad2d, const uint32_t* __restrict__ order) {
-    constexpr int BG = TW * TH;
-    __shared__ TileLds<BG> L;
+    constexpr int NW = TW * TH / 64, BG = pgs::kBwdBatch<TW * TH, NW>;
+    __shared__ TileLds<BG, pgs::kAccs<NW>> L;
     const int tile = order ? (int)order[blockIdx.x] : (int)blockIdx.x;
     const TileJob j{W, H, tile % TX, tile / TX, tile_offset + tile, proj, nullptr, const_cast<float*>(t_final),
                     const_cast<uint32_t*>(n_contrib), nullptr};

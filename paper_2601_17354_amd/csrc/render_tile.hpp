@@ -260,7 +260,20 @@ struct FwdLds {
     unsigned long long wbase[4];
 };
 
-template <int BG>
+// The four waves' partial sums of a splat meet in two accumulators, two waves in
+// each: a sum of two does not depend on which comes first, so a tile's sums
+// are the same in every run (added to one accumulator by all four, they varied
+// with the order, by as much as the order of the tiles makes the totals vary).
+// Batches of the single-view backward then hold 224 splats at most, which keeps
+// six workgroups on a CU, as many as their registers allow (with 256 five:
+// 1920 x 1440 447 us, with 224 427); those of the multi-view backward 192 (with
+// 224 its registers spill, 2279 us against 2166).
+template <int NW>
+constexpr int kAccs = NW > 2 ? 2 : 1;
+template <int BG, int NW, int MOST = 224>
+constexpr int kBwdBatch = NW > 2 && BG > MOST ? MOST : BG;
+
+template <int BG, int NA = 1>
 struct TileLds {
     float4 a[BG];
     float4 b[BG];
@@ -268,7 +281,7 @@ struct TileLds {
     uint32_t g[BG];
     float io[BG];  // 1 / opacity
     uint8_t reach[BG];  // bit w: the splat can reach a pixel of wave w (recompute backward)
-    float acc[9][BG + 1];  // one word of padding per row: a splat's nine terms fall in nine banks
+    float acc[NA][9][BG + 1];  // one word of padding per row: a splat's nine terms fall in nine banks
     uint32_t steps;
 };
 
@@ -785,16 +798,22 @@ __device__ __forceinline__ void accumulate_groups(float* v, const float* dy, flo
 // share one 64-byte record, so consecutive lanes hit the same line.  Each
 // accumulator word is cleared as it is read, so the next batch starts from
 // zeros (slots past nb are never written).
-template <int BG>
-__device__ __forceinline__ void flush_batch(TileLds<BG>& L, int nb, int n, float* __restrict__ grad2d, int t,
+template <int BG, int NA>
+__device__ __forceinline__ void flush_batch(TileLds<BG, NA>& L, int nb, int n, float* __restrict__ grad2d, int t,
                                             int NT) {
     (void)n;
-    float (*acc)[BG + 1] = L.acc;
+    float (*acc)[BG + 1] = L.acc[0];
     const uint32_t* gid = L.g;
     for (int jj = t; jj < nb; jj += NT) {
         float f[6];
 #pragma unroll
-        for (int k = 0; k < 6; ++k) f[k] = acc[k][jj];
+        for (int k = 0; k < 6; ++k) {
+            f[k] = acc[k][jj];
+            if constexpr (NA == 2) {
+                f[k] += L.acc[1][k][jj];
+                L.acc[1][k][jj] = 0.f;
+            }
+        }
         grad2d_from_sums(L.a[jj].z, L.a[jj].w, L.b[jj].x, L.io[jj], f);
 #pragma unroll
         for (int k = 0; k < 6; ++k) acc[k][jj] = f[k];
@@ -802,15 +821,19 @@ __device__ __forceinline__ void flush_batch(TileLds<BG>& L, int nb, int n, float
     __syncthreads();
     for (int idx = t; idx < nb * 9; idx += NT) {
         const int jj = idx / 9, f = idx - jj * 9;
-        const float s = acc[f][jj];
+        float s = acc[f][jj];
         acc[f][jj] = 0.f;
+        if constexpr (NA == 2) {
+            s += L.acc[1][f][jj];
+            L.acc[1][f][jj] = 0.f;
+        }
         if (s != 0.f) unsafeAtomicAdd(&grad2d[(size_t)gid[jj] * PGS_GRAD2D_STRIDE + f], s);
     }
 }
 
-template <int BG>
-__device__ __forceinline__ void zero_acc(float (*acc)[BG + 1], int t, int NT) {
-    for (int idx = t; idx < 9 * (BG + 1); idx += NT) (&acc[0][0])[idx] = 0.f;
+template <int BG, int NA>
+__device__ __forceinline__ void zero_acc(float (&acc)[NA][9][BG + 1], int t, int NT) {
+    for (int idx = t; idx < NA * 9 * (BG + 1); idx += NT) (&acc[0][0][0])[idx] = 0.f;
 }
 
 // Up to four non-empty groups of a 64-step window, front to back: the
@@ -853,7 +876,7 @@ __device__ __forceinline__ void load_groups(__amdgpu_buffer_rsrc_t went, const T
 // exact zeros there and keeps its dL/dC_out.
 template <int BG, int EW, int NT, class Lds>
 __device__ __forceinline__ void bwd_groups(const TraceGroups& g, const float4* e, Lds& L, uint32_t slot0, float fpx,
-                                           float fpy, int lane, float& g0, float& g1, float& g2) {
+                                           float fpy, int lane, int half, float& g0, float& g1, float& g2) {
     float v[4 * NT], dys[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -880,7 +903,7 @@ __device__ __forceinline__ void bwd_groups(const TraceGroups& g, const float4* e
         g1 *= om;
         g2 *= om;
     }
-    accumulate_groups<BG, NT>(v, dys, L.acc, lane, slot0, g.gi, g.gm);
+    accumulate_groups<BG, NT>(v, dys, L.acc[half], lane, slot0, g.gi, g.gm);
 }
 
 template <int TW, int TH, int BG, int EW = 4>
@@ -888,10 +911,11 @@ __device__ __forceinline__ void bwd_cached_tile(const TileJob& j, int n_tiles_to
                                                 const uint32_t* __restrict__ values,
                                                 const uint32_t* __restrict__ ranges, const Trace& tr,
                                                 const float* __restrict__ dl_dimage,
-                                                float* __restrict__ grad2d, TileLds<BG>& L) {
+                                                float* __restrict__ grad2d, TileLds<BG, kAccs<TW * TH / 64>>& L) {
     constexpr int NT = TW * TH;
     constexpr int NW = NT / 64;
     const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int half = kAccs<NW> == 2 ? wv >> 1 : 0;
     const int px = j.tx * TW + (t % TW), py = j.ty * TH + (t / TW);
     const bool inside = px < j.W && py < j.H;
     const uint32_t start = ranges[j.gt], end = ranges[n_tiles_total + j.gt];
@@ -939,19 +963,19 @@ __device__ __forceinline__ void bwd_cached_tile(const TileJob& j, int n_tiles_to
             load_groups<EW>(went, ga, ea);
             for (;;) {
                 if (!any) {
-                    bwd_groups<BG, EW, kTerms<TW>>(ga, ea, L, c0 - base, fpx, fpy, lane, g0, g1, g2);
+                    bwd_groups<BG, EW, kTerms<TW>>(ga, ea, L, c0 - base, fpx, fpy, lane, half, g0, g1, g2);
                     break;
                 }
                 take_groups(any, mv, cursor, gb);
                 load_groups<EW>(went, gb, eb);
-                bwd_groups<BG, EW, kTerms<TW>>(ga, ea, L, c0 - base, fpx, fpy, lane, g0, g1, g2);
+                bwd_groups<BG, EW, kTerms<TW>>(ga, ea, L, c0 - base, fpx, fpy, lane, half, g0, g1, g2);
                 if (!any) {
-                    bwd_groups<BG, EW, kTerms<TW>>(gb, eb, L, c0 - base, fpx, fpy, lane, g0, g1, g2);
+                    bwd_groups<BG, EW, kTerms<TW>>(gb, eb, L, c0 - base, fpx, fpy, lane, half, g0, g1, g2);
                     break;
                 }
                 take_groups(any, mv, cursor, ga);
                 load_groups<EW>(went, ga, ea);
-                bwd_groups<BG, EW, kTerms<TW>>(gb, eb, L, c0 - base, fpx, fpy, lane, g0, g1, g2);
+                bwd_groups<BG, EW, kTerms<TW>>(gb, eb, L, c0 - base, fpx, fpy, lane, half, g0, g1, g2);
             }
         }
         __syncthreads();
@@ -965,7 +989,7 @@ __device__ __forceinline__ void bwd_recompute_tile(const TileJob& j, int n,
                                                    const uint32_t* __restrict__ values,
                                                    const uint32_t* __restrict__ ranges, float bg0,
                                                    float bg1, float bg2, const float* __restrict__ dl_dimage,
-                                                   float* __restrict__ grad2d, TileLds<BG>& L) {
+                                                   float* __restrict__ grad2d, TileLds<BG, kAccs<TW * TH / 64>>& L) {
     constexpr int NT = TW * TH;
     const int t = threadIdx.x, lane = t & 63;
     const int px = j.tx * TW + (t % TW), py = j.ty * TH + (t / TW);
@@ -990,7 +1014,7 @@ __device__ __forceinline__ void bwd_recompute_tile(const TileJob& j, int n,
     if (last) atomicMax(&L.steps, last);
     __syncthreads();
     const uint32_t top = L.steps;
-    const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wv = __builtin_amdgcn_readfirstlane(t >> 6), half = kAccs<NT / 64> == 2 ? wv >> 1 : 0;
     zero_acc<BG>(L.acc, t, NT);  // once: each flush leaves the accumulator cleared
     uint32_t wlast = last;  // the wave's last contributing step
 #pragma unroll
@@ -1062,7 +1086,7 @@ __device__ __forceinline__ void bwd_recompute_tile(const TileJob& j, int n,
                     a2 = alpha * cb + om * a2;
                 }
             }
-            accumulate_groups<BG, kT>(v, dys, L.acc, lane, 0u, gi, gm);
+            accumulate_groups<BG, kT>(v, dys, L.acc[half], lane, 0u, gi, gm);
         }
         __syncthreads();
         flush_batch<BG>(L, nb, n, grad2d, t, NT);

@@ -85,13 +85,13 @@ __global__ __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(8))) voi
 // whose six would spill (16-byte entries, narrow tiles, small batches) keep five.
 template <int TW, int TH, int BG, bool CACHED, int EW = 4>
 __global__ __launch_bounds__(TW* TH)
-    __attribute__((amdgpu_waves_per_eu(CACHED && (EW == 4 || TW < 16 || BG < 256) ? 5 : 6))) void k_render_bwd_views(
+    __attribute__((amdgpu_waves_per_eu(CACHED && (EW == 4 || TW < 16 || BG < 192) ? 5 : 6))) void k_render_bwd_views(
     ViewTable vt, int n_tiles_total, const float* __restrict__ proj_all, int n,
     const uint32_t* __restrict__ values, const uint32_t* __restrict__ ranges,
     const float* __restrict__ t_final_all, const uint32_t* __restrict__ n_contrib_all, Trace tr,
     const float* __restrict__ dl_all, float* __restrict__ grad2d_all, const uint32_t* __restrict__ order,
     uint32_t* __restrict__ queue) {
-    __shared__ pgs::TileLds<BG> L;
+    __shared__ pgs::TileLds<BG, pgs::kAccs<TW * TH / 64>> L;
     __shared__ uint32_t s_item;
     for (;;) {
         const uint32_t item = next_item(queue, &s_item);
@@ -262,19 +262,19 @@ extern "C" pgs_status pgs_render_bwd_views(const pgs_view_batch* vb, const float
     with_config(vb->tile_w, vb->tile_h, vb->batch, [&](auto TWc, auto THc, auto BGc) {
         constexpr int TW = decltype(TWc)::value, TH = decltype(THc)::value, BG = decltype(BGc)::value;
         if (cache && tr.words == 3) {
-            auto k = k_render_bwd_views<TW, TH, BG, true, 3>;
+            auto k = k_render_bwd_views<TW, TH, pgs::kBwdBatch<BG, TW * TH / 64, 192>, true, 3>;
             const int blocks = resident_blocks(k, TW * TH, vb->blocks, total);
             k<<<blocks, TW * TH, 0, s>>>(vt, total, proj_all_dev, n, values_dev, ranges_dev, t_final_all_dev,
                                          n_contrib_all_dev, tr, dl_all_dev, grad2d_all_dev, tile_order_dev,
                                          queue_dev);
         } else if (cache) {
-            auto k = k_render_bwd_views<TW, TH, BG, true, 4>;
+            auto k = k_render_bwd_views<TW, TH, pgs::kBwdBatch<BG, TW * TH / 64, 192>, true, 4>;
             const int blocks = resident_blocks(k, TW * TH, vb->blocks, total);
             k<<<blocks, TW * TH, 0, s>>>(vt, total, proj_all_dev, n, values_dev, ranges_dev, t_final_all_dev,
                                          n_contrib_all_dev, tr, dl_all_dev, grad2d_all_dev, tile_order_dev,
                                          queue_dev);
         } else {
-            auto k = k_render_bwd_views<TW, TH, BG, false>;
+            auto k = k_render_bwd_views<TW, TH, pgs::kBwdBatch<BG, TW * TH / 64, 192>, false>;
             const int blocks = resident_blocks(k, TW * TH, vb->blocks, total);
             k<<<blocks, TW * TH, 0, s>>>(vt, total, proj_all_dev, n, values_dev, ranges_dev, t_final_all_dev,
                                          n_contrib_all_dev, tr, dl_all_dev, grad2d_all_dev, tile_order_dev,
