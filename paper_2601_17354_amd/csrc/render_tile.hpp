@@ -140,10 +140,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t region_rsrc(const void* region
 typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// Entries are written once and read once, gigabytes apart, so they pass the
-// caches as streams (the non-temporal bit): the traced forward of eight views
-// of 1M Gaussians 2.56 -> 2.34 ms, the backward of 300k at 1920 x 1440 441 ->
-// 417 us.
+// Entries are read once, so loads pass the caches as streams (the non-temporal
+// bit): the backward of 300k Gaussians at 1920 x 1440 441 -> 417 us.  Stores do
+// so only where several views record one trace of many gigabytes (eight views of
+// 1M Gaussians 2.56 -> 2.34 ms); for one view they lose as much or more than they
+// gain (300k Gaussians at 1920 x 1440: 488 us streamed, 486 not; a scene with half
+// as many pairs again: 725 and 647).
 constexpr int kStream = 2;
 
 // Entry `rank` (< 64) of the run of EW-word entries that starts `first`
@@ -167,16 +169,16 @@ __device__ __forceinline__ float4 load_entry(__amdgpu_buffer_rsrc_t rs, uint32_t
 // needs before its data registers are overwritten only for that form, and
 // with a register scalar offset the store was measured to pick up the next
 // value of its data registers.
-template <int EW>
+template <int EW, bool STREAM>
 __device__ __forceinline__ void store_entry(__amdgpu_buffer_rsrc_t rs, uint32_t first, uint64_t lanes, float c0,
                                             float c1, float c2, float alpha) {
     const uint32_t voff = __umul24(lane_rank(lanes, first), 4u * EW);  // a region: far below 2^24 entries
     if constexpr (EW == 4) {
         u32x4 d = {__float_as_uint(c0), __float_as_uint(c1), __float_as_uint(c2), __float_as_uint(alpha)};
-        __builtin_amdgcn_raw_buffer_store_b128(d, rs, voff, 0, kStream);
+        __builtin_amdgcn_raw_buffer_store_b128(d, rs, voff, 0, STREAM ? kStream : 0);
     } else {
         u32x3 d = {__float_as_uint(c0), __float_as_uint(c1), __float_as_uint(c2)};
-        __builtin_amdgcn_raw_buffer_store_b96(d, rs, voff, 0, kStream);
+        __builtin_amdgcn_raw_buffer_store_b96(d, rs, voff, 0, STREAM ? kStream : 0);
         (void)alpha;
     }
 }
@@ -377,7 +379,7 @@ __device__ __forceinline__ void stage_batch_reach(Lds& L, const float* __restric
     }
 }
 
-template <int TW, int TH, int BG, bool CACHED, int EW = 4>
+template <int TW, int TH, int BG, bool CACHED, int EW = 4, bool STREAM = false>
 __device__ __forceinline__ void fwd_tile(const TileJob& j, int n_tiles_total, int n,
                                          const uint32_t* __restrict__ values,
                                          const uint32_t* __restrict__ ranges, float bg0, float bg1,
@@ -597,7 +599,7 @@ __device__ __forceinline__ void fwd_tile(const TileJob& j, int n_tiles_total, in
                 for (int q = 0; q < 4; ++q) {
                     if (lane_in(gm[q])) {
                         const float a = al[q], om = 1.f - a;
-                        store_entry<EW>(went, gc[q], gm[q], a0, a1, a2, a);
+                        store_entry<EW, STREAM>(went, gc[q], gm[q], a0, a1, a2, a);
                         // blended in place after the store, without copies
                         asm volatile("" : "+v"(a0), "+v"(a1), "+v"(a2));
                         a0 = a * sq[q].r + om * a0;

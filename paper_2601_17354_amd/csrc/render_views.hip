@@ -75,7 +75,7 @@ __global__ __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(8))) voi
         int v;
         const TileJob j = job_of(vt, gt, proj_all, n, image_all, t_final_all, n_contrib_all,
                                  CACHED ? tr.count : nullptr, v);
-        pgs::fwd_tile<TW, TH, BG, CACHED, EW>(j, n_tiles_total, n, values, ranges, vt.bg[0], vt.bg[1], vt.bg[2],
+        pgs::fwd_tile<TW, TH, BG, CACHED, EW, true>(j, n_tiles_total, n, values, ranges, vt.bg[0], vt.bg[1], vt.bg[2],
                                               tr, flags, L);
     }
 }
