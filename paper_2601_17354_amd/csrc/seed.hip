@@ -465,12 +465,12 @@ __global__ __launch_bounds__(kKnnThreads) void k_knn_grid(const float4* __restri
     const int rmax = max(nx, max(ny, nz));
     for (int r = 2;; ++r) {
         // visited: every cell within r - 1; the k-th distance is at most its
-        // rounded key's value and a unit of rounding more
+        // rounded key's value and a unit of rounding more (relative, or among
+        // the subnormal numbers their spacing)
         const double reach = ((double)(r - 1) + gap) * h;
         const uint32_t kth = (uint32_t)__double2hiint(a[K - 1]);
-        if (r > rmax ||
-            (kth < kInfBits && (double)__uint_as_float(kth) * (1.0 + 1e-6) <= reach * reach * (1.0 - 1e-12)))
-            break;
+        const double kth_most = (double)__uint_as_float(kth) * (1.0 + 1e-6) + 0x1p-149;
+        if (r > rmax || (kth < kInfBits && kth_most <= reach * reach * (1.0 - 1e-12))) break;
         for (int dz = -r; dz <= r; ++dz)
             for (int dy = -r; dy <= r; ++dy) {
                 if (dz == -r || dz == r || dy == -r || dy == r) {

@@ -510,3 +510,17 @@ def test_bin_sort_workgroup_and_pass_edges(n, tx, ty, cap):
     r = ranges.cpu().numpy()
     np.testing.assert_array_equal(r[1] - r[0], counts)
     np.testing.assert_array_equal(r[0][counts > 0], (np.cumsum(counts) - counts)[counts > 0])
+
+
+@pytest.mark.parametrize("scale", [1.5e-23, 3e-23, 6e-23, 1.2e-22])
+def test_knn_of_minute_spacing(scale):
+    # squared distances among float32's subnormal numbers, whose rounding is
+    # an absolute half step: every query against brute force
+    for seed in range(6):
+        pts = (np.random.default_rng(seed).normal(size=(600, 3)) * scale).astype(np.float32)
+        for k in (4, 16):
+            _, nbr, d2 = _knn_gpu(pts, k)
+            torch.cuda.synchronize()
+            ids, dd = o_seed.knn(pts, list(range(600)), k)
+            np.testing.assert_array_equal(nbr.cpu().numpy().T, ids)
+            np.testing.assert_array_equal(d2.cpu().numpy().T, dd)
