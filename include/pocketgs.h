@@ -794,8 +794,8 @@ pgs_status pgs_mvs_cost(const pgs_camera* cams_dev, int32_t width, int32_t heigh
                         const int32_t* targets_dev, int32_t n_targets, const int32_t* ref_dev,
                         const double* range_dev, const pgs_mvs_params* params, uint8_t* cost_dev, void* stream);
 
-/* Workspace bytes of pgs_mvs_sgm (one direction's path costs as bytes,
- * then the path-cost sum as uint16). */
+/* Workspace bytes of pgs_mvs_sgm: three volumes of a byte per cell (path costs,
+ * their checkpoints or sums of two directions) and a word per four rows. */
 size_t pgs_mvs_sgm_workspace(int32_t n_targets, int32_t width, int32_t height, int32_t n_planes);
 
 /*
@@ -808,9 +808,9 @@ size_t pgs_mvs_sgm_workspace(int32_t n_targets, int32_t width, int32_t height, i
  * 1/d = 1/d_max + (k* + delta) h.  depth_dev [n_targets][height][width]
  * float32 (0 where rejected), conf_dev the same shape (1 - S(k*)/S2).
  * agg_out_dev (optional, [n_targets][height][width][n_planes] uint16)
- * receives S; without it the partial sums live in the workspace, which is
- * required either way.  p2 <= 207 (each path cost, <= 48 + p2, is stored in
- * a byte between the two sweeps of a line).
+ * receives S; the workspace is required either way.  Path costs are held in
+ * bytes between two sweeps of a line: p2 <= 207, and the costs (48 at most
+ * from pgs_mvs_cost) may reach 255 - p2.
  */
 pgs_status pgs_mvs_sgm(const uint8_t* cost_dev, int32_t width, int32_t height, const int32_t* targets_dev,
                        int32_t n_targets, const double* range_dev, const pgs_mvs_params* params, float* depth_dev,

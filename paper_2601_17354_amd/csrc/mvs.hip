@@ -439,15 +439,17 @@ void launch_cost(dim3 grid, hipStream_t s, const pgs_camera* cams, int W, int H,
 struct SgmArgs {
     const uint8_t* cost;
     // workspace, e = T H W D bytes each: [0] checkpoints (sweeps of whole lines)
-    // or left-to-right path costs, [1] row sums or right-to-left, [2]
-    // top-to-bottom
+    // or left-to-right path costs, [1] row sums (their low bytes) or
+    // right-to-left, [2] top-to-bottom
     uint8_t* buf[3];
     uint16_t* agg_out;   // the full sums, if wanted
+    uint32_t* over;      // [T][ceil(H / 4)] not 0: a cost of these rows is past byte_cost
     const int32_t* targets;
     const double* range;
     float* depth;        // [T][H][W]
     float* conf;
     int W, H, p1, p2;
+    uint32_t byte_cost;  // 127 - p2: up to it two path costs fit a byte, four 9 bits
     double keep_ratio;   // 1 - confidence threshold
 };
 
@@ -594,10 +596,40 @@ __device__ __forceinline__ void load_seg(const uint8_t* base, const Lines& q, in
     for (int s = 0; s < S; ++s) v[s] = Sweep<D>::load(base + q.at(min(max(seg, 0) * S + s, q.n - 1)));
 }
 
-// Forward sweep of whole segments 0 .. nseg - 2 that keeps only the state
-// before each segment from 1 on (checkpoints, one per kSeg steps).
+// The bits that any of a segment's costs has, byte by byte.
 template <int D>
-__device__ __forceinline__ void checkpoint_sweep(const uint8_t* cost, uint8_t* ck, const Lines& q, u16x2 p1, u16x2 p2) {
+__device__ __forceinline__ void gather_bits(const typename Sweep<D>::Bytes (&c)[Sweep<D>::kSeg], uint32_t& bits) {
+#pragma unroll
+    for (int s = 0; s < Sweep<D>::kSeg; ++s)
+#pragma unroll
+        for (int k = 0; k < Sweep<D>::NB; ++k) bits |= c[s].w[k];
+}
+
+// Whether a cost of the wave's lines is above lim (48 to 127), given the bits
+// of all of them.  A Census cost is at most 48, so for most limits the bits
+// settle it; else the lines are read again and every byte compared (bit 7 of a
+// byte: above lim).
+template <int D>
+__device__ __forceinline__ bool exceeds(uint32_t bits, const uint8_t* cost, const Lines& q, uint32_t lim) {
+    constexpr uint32_t kBytes = 0x01010101u;
+    const uint32_t within = lim >= 127u ? 0x7fu : lim >= 63u ? 0x3fu : 0x1fu;
+    if (__ballot((bits & ~(within * kBytes)) != 0u) == 0ull) return false;
+    uint32_t over = 0u;
+    for (int s = 0; s < q.n; ++s) {
+        const typename Sweep<D>::Bytes c = Sweep<D>::load(cost + q.at(s));
+#pragma unroll
+        for (int k = 0; k < Sweep<D>::NB; ++k)
+            over |= ((c.w[k] & 0x7f7f7f7fu) + (127u - lim) * kBytes) | c.w[k];
+    }
+    return __ballot((over & 0x80808080u) != 0u) != 0ull;
+}
+
+// Forward sweep of whole segments 0 .. nseg - 2 that keeps only the state
+// before each segment from 1 on (checkpoints, one per kSeg steps), and with
+// BITS the bits of those segments' costs.
+template <int D, bool BITS>
+__device__ __forceinline__ void checkpoint_sweep(const uint8_t* cost, uint8_t* ck, const Lines& q, u16x2 p1, u16x2 p2,
+                                                 uint32_t& bits) {
     typedef Sweep<D> SW;
     constexpr int S = SW::kSeg, NR = SW::NR;
     const int nseg = (q.n + S - 1) / S;
@@ -608,6 +640,7 @@ __device__ __forceinline__ void checkpoint_sweep(const uint8_t* cost, uint8_t* c
     load_seg<D>(cost, q, 0, c);
     for (int seg = 0; seg + 1 < nseg; ++seg) {
         load_seg<D>(cost, q, seg + 1, cn);
+        if constexpr (BITS) gather_bits<D>(c, bits);
 #pragma unroll
         for (int s = 0; s < S; ++s) path_step<D>(L, c[s], p1, p2);
         SW::store(ck + q.at((seg + 1) * S), SW::bytes(L));
@@ -637,14 +670,16 @@ __device__ __forceinline__ void recompute(const typename Sweep<D>::Bytes& ck, bo
 // recomputes a segment's forward path before walking it back, both from the
 // segment's costs in registers.  Per cell the costs are read twice and one
 // byte of sum is written (2 (48 + P2) <= 255), where storing the path costs
-// and 16-bit sums moved six bytes.
+// and 16-bit sums moved six bytes.  In rows with a cost past 127 - P2, which no
+// Census cost is, a sum may pass 255: its low byte is written alone.
 template <int D>
 __global__ __launch_bounds__(64) void k_sgm_rows(SgmArgs a) {
     typedef Sweep<D> SW;
     constexpr int S = SW::kSeg, NR = SW::NR, NB = SW::NB;
     const Lines q = lines_of<D>(a, true, blockIdx.x, blockIdx.y);
     const u16x2 p1 = splat((uint32_t)a.p1), p2 = splat((uint32_t)a.p2);
-    checkpoint_sweep<D>(a.cost, a.buf[0], q, p1, p2);
+    uint32_t bits = 0u;
+    checkpoint_sweep<D, true>(a.cost, a.buf[0], q, p1, p2, bits);
     u16x2 L[NR];
 #pragma unroll
     for (int i = 0; i < NR; ++i) L[i] = splat(0u);
@@ -652,7 +687,7 @@ __global__ __launch_bounds__(64) void k_sgm_rows(SgmArgs a) {
     typename SW::Bytes c[S], cn[S], f[S], ck, ckn;
     load_seg<D>(a.cost, q, nseg - 1, c);
     ck = SW::load(a.buf[0] + q.at((nseg - 1) * S));
-    auto back = [&](int seg, auto whole) {
+    auto back = [&](int seg, auto whole, auto wide) {
         load_seg<D>(a.cost, q, seg - 1, cn);
         ckn = SW::load(a.buf[0] + q.at(max(seg - 1, 0) * S));
         recompute<D>(ck, seg == 0, c, f, p1, p2);
@@ -661,10 +696,17 @@ __global__ __launch_bounds__(64) void k_sgm_rows(SgmArgs a) {
             const int x = seg * S + s;
             if (whole || x < q.n) {
                 path_step<D>(L, c[s], p1, p2);
-                typename SW::Bytes b = SW::bytes(L);
+                if constexpr (wide) {
+                    u16x2 sum[NR];
 #pragma unroll
-                for (int k = 0; k < NB; ++k) b.w[k] += f[s].w[k];  // four sums of bytes, none past 255
-                SW::store(a.buf[1] + q.at(x), b);
+                    for (int i = 0; i < NR; ++i) sum[i] = L[i] + SW::pair(f[s], i);
+                    SW::store(a.buf[1] + q.at(x), SW::bytes(sum));
+                } else {
+                    typename SW::Bytes b = SW::bytes(L);
+#pragma unroll
+                    for (int k = 0; k < NB; ++k) b.w[k] += f[s].w[k];  // four sums of bytes, none past 255
+                    SW::store(a.buf[1] + q.at(x), b);
+                }
             }
         }
 #pragma unroll
@@ -672,8 +714,14 @@ __global__ __launch_bounds__(64) void k_sgm_rows(SgmArgs a) {
         ck = ckn;
     };
     // only the last segment may be short
-    if (q.n % S) back(nseg - 1, Const<false>());
-    for (int seg = q.n / S - 1; seg >= 0; --seg) back(seg, Const<true>());
+    gather_bits<D>(c, bits);
+    const bool over = exceeds<D>(bits, a.cost, q, a.byte_cost);
+    if (threadIdx.x == 0) a.over[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = over;
+    if (q.n % S) back(nseg - 1, Const<false>(), Const<true>());
+    for (int seg = q.n / S - 1; seg >= 0; --seg) {
+        if (over) back(seg, Const<true>(), Const<true>());
+        else back(seg, Const<true>(), Const<false>());
+    }
 }
 
 // One direction of four lines, its path costs stored: blocks of the grid take
@@ -697,8 +745,10 @@ __global__ __launch_bounds__(64) void k_sgm_paths(SgmArgs a, int row_waves) {
     for (int i = 0; i < NR; ++i) L[i] = splat(0u);
     typename SW::Bytes c[S], cn[S];
     load_seg<D>(a.cost, w, 0, c);
+    uint32_t bits = 0u;
     auto ahead = [&](int seg, auto whole) {
         load_seg<D>(a.cost, w, seg + 1, cn);
+        if constexpr (D == 128) gather_bits<D>(c, bits);
 #pragma unroll
         for (int s = 0; s < S; ++s) {
             const int x = seg * S + s;
@@ -712,6 +762,10 @@ __global__ __launch_bounds__(64) void k_sgm_paths(SgmArgs a, int row_waves) {
     };
     for (int seg = 0; seg < q.n / S; ++seg) ahead(seg, Const<true>());
     if (q.n % S) ahead(q.n / S, Const<false>());
+    if (D == 128 && a.over && dir == 0) {
+        const bool over = exceeds<D>(bits, a.cost, q, a.byte_cost);
+        if (threadIdx.x == 0) a.over[(size_t)blockIdx.y * row_waves + blockIdx.x] = over;
+    }
 }
 
 // Bottom to top over four columns, added to the other three paths, and each
@@ -724,16 +778,18 @@ __global__ __launch_bounds__(64) void k_sgm_paths(SgmArgs a, int row_waves) {
 // (excluded planes raised past every sum); lane s of the row keeps step s,
 // and at the segment's end every lane finishes one pixel, taking the winner's
 // two neighbours from the segment's sums in LDS.  AGG also stores the sums.
-template <int D, bool STAGED, bool FUSED, bool AGG>
-__global__ __launch_bounds__(64) void k_sgm_cols(SgmArgs a) {
+// WIDE: a target with a cost past 127 - P2, whose row sums' low bytes are to be
+// completed and whose sums may need ten bits.
+template <int D, bool STAGED, bool FUSED, bool AGG, bool WIDE>
+__device__ __forceinline__ void cols_lines(const SgmArgs& a, uint32_t (*sums)[4][D / 2]) {
 #pragma clang fp contract(off)
     typedef Sweep<D> SW;
     constexpr int S = SW::kSeg, NR = SW::NR;
-    __shared__ __align__(16) uint32_t sums[S][4][D / 2];
     const int lane = threadIdx.x & 63, li = lane & 15, row = lane >> 4, ti = blockIdx.y;
     const Lines q = lines_of<D>(a, false, blockIdx.x, ti);
     const u16x2 p1 = splat((uint32_t)a.p1), p2 = splat((uint32_t)a.p2);
-    if (!STAGED) checkpoint_sweep<D>(a.cost, a.buf[0], q, p1, p2);
+    uint32_t bits = 0u;
+    if (!STAGED) checkpoint_sweep<D, false>(a.cost, a.buf[0], q, p1, p2, bits);
     const int tv = a.targets[ti];
     const double d_min = a.range[2 * tv], d_max = a.range[2 * tv + 1];
     const double inv_far = 1.0 / d_max, h = (1.0 / d_min - inv_far) / (double)(D - 1);
@@ -779,6 +835,15 @@ __global__ __launch_bounds__(64) void k_sgm_cols(SgmArgs a) {
                     T[i] = L[i] + SW::pair(f[s], i) + SW::pair(r[s], i);
                     if constexpr (STAGED) T[i] += SW::pair(r2[s], i);
                 }
+                if constexpr (WIDE && !STAGED) {
+                    // a path cost is between C and C + P2, so a row sum lies less
+                    // than 256 above 2 C and its low byte tells the rest
+#pragma unroll
+                    for (int i = 0; i < NR; ++i) {
+                        const u16x2 r0 = SW::pair(r[s], i), c2 = SW::pair(c[s], i) + SW::pair(c[s], i);
+                        T[i] += c2 + ((r0 - c2) & splat(0xffu)) - r0;
+                    }
+                }
                 if constexpr (AGG) {
                     typedef uint32_t Half __attribute__((aligned(2)));
                     Half* o = reinterpret_cast<Half*>(a.agg_out + q.at(y));
@@ -788,7 +853,7 @@ __global__ __launch_bounds__(64) void k_sgm_cols(SgmArgs a) {
 #pragma unroll
                 for (int i = 0; i < NR; ++i) sums[s][row][li * NR + i] = word_of(T[i]);
                 u16x2 v[NR], s1, kw;
-                if constexpr (FUSED) {
+                if constexpr (FUSED && !(WIDE && D == 128)) {
 #pragma unroll
                     for (int i = 0; i < NR; ++i) v[i] = T[i] * splat(D) + plane[i];
                     const u16x2 key = least<NR>(v);
@@ -850,6 +915,24 @@ __global__ __launch_bounds__(64) void k_sgm_cols(SgmArgs a) {
     // only the last segment may be short
     if (q.n % S) back(nseg - 1, Const<false>());
     for (int seg = q.n / S - 1; seg >= 0; --seg) back(seg, Const<true>());
+}
+
+// The two bodies side by side, as one that chose per segment cost 6% (eight
+// 960 x 720 targets of 128 planes 1229 us, 1300 so; 1228 now).  Two waves a
+// SIMD for whole lines, which the second body's registers would make one.
+template <int D, bool STAGED, bool FUSED, bool AGG>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(STAGED ? 1 : 2))) void k_sgm_cols(SgmArgs a) {
+    __shared__ __align__(16) uint32_t sums[Sweep<D>::kSeg][4][D / 2];
+    if constexpr (!STAGED || (FUSED && D == 128)) {
+        const int rows = (a.H + 3) / 4;
+        uint32_t over = 0u;
+        for (int k = threadIdx.x; k < rows; k += 64) over |= a.over[(size_t)blockIdx.y * rows + k];
+        if (__ballot(over != 0u) != 0ull) {
+            cols_lines<D, STAGED, FUSED, AGG, true>(a, sums);
+            return;
+        }
+    }
+    cols_lines<D, STAGED, FUSED, AGG, false>(a, sums);
 }
 
 // ---------------------------------------------------------------- fusion
@@ -968,14 +1051,17 @@ template <int D>
 constexpr long long kSgmWaves = D == 64 ? 1024 : 640;
 
 template <int D>
-pgs_status launch_sgm(const SgmArgs& a, int n_targets, hipStream_t s) {
+pgs_status launch_sgm(SgmArgs a, int n_targets, hipStream_t s) {
     const int rows = (a.H + 3) / 4, cols = (a.W + 3) / 4;
     const bool wide = 2 * (kCostOut + a.p2) > 255;
     if ((long long)rows * n_targets <= kSgmWaves<D> || wide || a.agg_out) {
-        // sums up to 4 (48 + P2) and log2 D bits of plane in 16
+        // four path costs below 256, or below 128 in a segment without costs
+        // past 127 - P2 (Census costs where 4 (48 + P2) < 512), and log2 D
+        // bits of plane in 16
         constexpr bool kFits = D == 64;
         const bool fused = kFits || (D == 128 && 4 * (kCostOut + a.p2) < 512);
         const dim3 grid(cols, n_targets);
+        if (kFits || !fused) a.over = nullptr;  // right for every cost
         k_sgm_paths<D><<<dim3(2 * rows + cols, n_targets), 64, 0, s>>>(a, rows);
         if (fused) {
             if constexpr (D <= 128) {
@@ -1073,7 +1159,7 @@ extern "C" pgs_status pgs_mvs_cost(const pgs_camera* cams_dev, int32_t width, in
 extern "C" size_t pgs_mvs_sgm_workspace(int32_t n_targets, int32_t width, int32_t height, int32_t n_planes) {
     if (n_targets <= 0 || width <= 0 || height <= 0 || n_planes <= 0) return 0;
     const size_t e = (size_t)n_targets * width * height * n_planes;
-    return al256(e) + al256(e * 2);
+    return al256(e) + al256(e * 2) + al256((size_t)n_targets * ((height + 3) / 4) * 4);
 }
 
 extern "C" pgs_status pgs_mvs_sgm(const uint8_t* cost_dev, int32_t width, int32_t height, const int32_t* targets_dev,
@@ -1096,6 +1182,7 @@ extern "C" pgs_status pgs_mvs_sgm(const uint8_t* cost_dev, int32_t width, int32_
     a.buf[0] = reinterpret_cast<uint8_t*>(ws);
     a.buf[1] = reinterpret_cast<uint8_t*>(ws + al256(e));
     a.buf[2] = a.buf[1] + e;
+    a.over = reinterpret_cast<uint32_t*>(ws + al256(e) + al256(e * 2));
     a.agg_out = agg_out_dev;
     a.targets = targets_dev;
     a.range = range_dev;
@@ -1105,6 +1192,7 @@ extern "C" pgs_status pgs_mvs_sgm(const uint8_t* cost_dev, int32_t width, int32_
     a.H = height;
     a.p1 = params->p1;
     a.p2 = params->p2;
+    a.byte_cost = (uint32_t)max(127 - params->p2, 0);
     a.keep_ratio = 1.0 - params->conf_min;
     hipStream_t s = pgs::as_stream(stream);
     switch (params->n_planes) {

@@ -290,3 +290,35 @@ def test_sgm_line_sweeps(T, W, H, D, p2, agg):
         np.testing.assert_array_equal(got > 0, d > 0)
         np.testing.assert_allclose(got, d, rtol=1e-6, atol=0)
         np.testing.assert_allclose(conf[t].cpu().numpy(), c, rtol=1e-6, atol=1e-7)
+
+
+@pytest.mark.parametrize("T,W,H,D,p2,agg", [
+    (1, 37, 21, 64, 32, False), (2, 40, 33, 128, 32, False), (1, 33, 20, 128, 79, True), (1, 21, 30, 256, 60, False),
+    # enough rows for the sweeps of whole lines
+    (2, 9, 2052, 64, 79, False), (2, 37, 1290, 128, 32, False), (2, 19, 1284, 192, 79, False), (1, 18, 2565, 256, 48, False)])
+def test_sgm_costs_past_the_census_range(T, W, H, D, p2, agg):
+    # any cost volume whose path costs fit a byte (cost + p2 <= 255): row sums
+    # past a byte and sums past the joined keys in some segments, few in
+    # others; the last target stays within the 48 of a Census cost
+    from paper_2601_17354_amd import mvs
+    rng = np.random.default_rng(D + p2)
+    cost = rng.integers(0, 49, (T, H, W, D)).astype(np.uint8)
+    wild = rng.integers(0, 256 - p2, (H, W, D)).astype(np.uint8)
+    cost[0, : H // 3] = wild[: H // 3]
+    cost[0, H // 2, W // 2:] = 255 - p2
+    cost[0, -1, -1, D // 2:] = 255 - p2
+    pr = _params(D, p1=7, p2=p2)
+    depth = torch.empty((T, H, W), dtype=torch.float32, device="cuda")
+    conf = torch.empty_like(depth)
+    out = torch.empty((T, H, W, D), dtype=torch.int16, device="cuda") if agg else None
+    mvs.pgs_mvs_sgm(torch.as_tensor(cost, device="cuda"), torch.arange(T, dtype=torch.int32, device="cuda"),
+                    torch.as_tensor(np.array([[1.0, 6.0]] * T), device="cuda"), pr, depth, conf, agg_out=out)
+    torch.cuda.synchronize()
+    for t in range(T):
+        S = omvs.sgm(cost[t], pr.p1, pr.p2)
+        if agg:
+            np.testing.assert_array_equal(out[t].cpu().numpy().view(np.uint16).astype(np.int64), S)
+        d, c, _ = omvs.winner(S, 1.0, 6.0, pr.conf_min)
+        np.testing.assert_array_equal(depth[t].cpu().numpy() > 0, d > 0)
+        np.testing.assert_allclose(depth[t].cpu().numpy(), d, rtol=1e-6, atol=0)
+        np.testing.assert_allclose(conf[t].cpu().numpy(), c, rtol=1e-6, atol=1e-7)
