@@ -364,11 +364,14 @@ __global__ __launch_bounds__(256) void k_ba_rows(int n_cams, int gauge_axis, dou
 // A = L L^T of the rows computes the forward substitution L y = g as that
 // row's entries of L.  Right-looking, in panels of 32 columns with one launch
 // each (k_ba_panel): a workgroup per 32 x 32 tile of the trailing triangle
-// turns its own two row blocks of the panel into L (A L11^-T, one product with
-// the inverse of the panel's diagonal block, which the launch before left)
-// and subtracts their product; the workgroup of the next panel's diagonal
-// block then factors and inverts it.  Nothing but that block's chain is
-// serial.  One workgroup factoring a panel, another launch updating the
+// turns its own two row blocks of the panel into L (rows x of A solved for
+// x L11^T, with the diagonal block's factor that the launch before left) and
+// subtracts their product; the workgroup of the next panel's diagonal block
+// then factors it.  Nothing but that block's chain is serial.  Both triangular
+// solves are substitutions: products with the diagonal blocks' inverses, which
+// took as long, left 20 to 100 times the backward error on views so narrow that
+// turning and moving a camera hardly differ.  One workgroup factoring a panel,
+// another launch updating the
 // trailing triangle and a triangular solve per row of the panel took 505 + 74
 // us at 60 cameras (nf = 353), 12 launches of 12.3 us and 30 + 11 us for the
 // back substitution and the first block now: each launch's fixed 4 us and the
@@ -392,19 +395,17 @@ __device__ __forceinline__ double inv_sqrt(double d) {
     return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
-// Inverse of the Cholesky factor of the 32 x 32 block D (lower triangle,
-// row stride kPS, in LDS), by one wave in registers: lane r < 32 eliminates row
-// r, lane 32 + c carries column c of the identity through the same steps, and
-// both multiply by the same column of L.  The next pivot's entry goes from
-// lane to lane through scalar registers, so that the chain of pivots is a
-// reciprocal root and three products a step; the rest of the column is read
-// back from LDS (col, 32 x 32) in its shadow.  Row-major to inv.
-__device__ __forceinline__ void invert_factor(const double* D, double* col, double* __restrict__ inv, int lane) {
+// Cholesky factor of the 32 x 32 block D (lower triangle, row stride kPS, in
+// LDS), by one wave in registers: lane r < 32 eliminates row r (the other
+// lanes repeat them).  The next pivot's entry goes from lane to lane through
+// scalar registers, so that the chain of pivots is a reciprocal root and three
+// products a step; the rest of the column is read back from LDS (col, 32 x 32)
+// in its shadow.  Column-major to out, what lies above the diagonal arbitrary.
+__device__ __forceinline__ void factor_block(const double* D, double* col, double* __restrict__ out, int lane) {
     double v[kPW];
     const int r = lane & 31;
-    const bool low = lane < 32;
 #pragma unroll
-    for (int c = 0; c < kPW; ++c) v[c] = low ? D[r * kPS + c] : (c == r ? 1.0 : 0.0);
+    for (int c = 0; c < kPW; ++c) v[c] = D[r * kPS + c];
     double pivot = read_lane_f64(v[0], 0);
 #pragma unroll
     for (int p = 0; p < kPW; ++p) {
@@ -415,27 +416,27 @@ __device__ __forceinline__ void invert_factor(const double* D, double* col, doub
             pivot = read_lane_f64(v[p + 1], p + 1);
         }
         if (p + 2 < kPW) {
-            if (low) col[p * kPW + r] = m;
+            if (lane < 32) col[p * kPW + r] = m;
             wave_sync();
 #pragma unroll
             for (int c = p + 2; c < kPW; ++c) v[c] = fma(-m, col[p * kPW + c], v[c]);
         }
     }
-    if (!low) {
+    if (lane < 32) {
 #pragma unroll
-        for (int c = 0; c < kPW; ++c) inv[c * kPW + r] = v[c];
+        for (int c = 0; c < kPW; ++c) out[c * kPW + r] = v[c];
     }
 }
 
 // The first panel's diagonal block (identity past nf).
-__global__ __launch_bounds__(64) void k_ba_first(int nf, const double* __restrict__ A, double* __restrict__ inv) {
+__global__ __launch_bounds__(64) void k_ba_first(int nf, const double* __restrict__ A, double* __restrict__ fac) {
     __shared__ __align__(16) double D[kPW * kPS], col[kPW * kPW];
     for (int e = threadIdx.x; e < kPW * kPW; e += 64) {
         const int r = e / kPW, c = e % kPW;
         D[r * kPS + c] = r < nf && c <= r ? A[(size_t)r * nf + c] : (r == c ? 1.0 : 0.0);
     }
     __syncthreads();
-    invert_factor(D, col, inv, threadIdx.x);
+    factor_block(D, col, fac, threadIdx.x);
 }
 
 // Thread (ty, tx) of a 16 x 16 grid: rows 2 ty, 2 ty + 1 of X times rows
@@ -453,41 +454,97 @@ __device__ __forceinline__ void tile_product(const double* X, const double* Y, i
     }
 }
 
+template <int V>
+struct Int {
+    static constexpr int value = V;
+};
+
+// The value of lane LANE of each four.
+template <int LANE>
+__device__ __forceinline__ double quad_lane_f64(double v) {
+    const long long b = __double_as_longlong(v);
+    constexpr int kCtrl = LANE * 0x55;
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), kCtrl, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), kCtrl, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
 // Panel k0: tile e of the lower triangle of rows k0 + 32 .. nf (the
 // right-hand side last).  L gets the panel's rows below its diagonal block.
+// Four lanes solve a row of each block, lane l its columns 4 i + l: what the
+// factor's words cost from LDS is shared by two rows.  (One row a lane, the
+// whole factor read by every lane, took 1.5 us more a launch.)
 __global__ __launch_bounds__(256) void k_ba_panel(int nf, int k0, double* __restrict__ A, double* __restrict__ L,
-                                                  double* __restrict__ invs) {
-    __shared__ __align__(16) double I[kPW * kPS], X[kPW * kPS], Y[kPW * kPS];
+                                                  double* __restrict__ facs) {
+    __shared__ __align__(16) double F[kPW * kPW], X[kPW * kPS], Y[kPW * kPS], D[kPW * kPS], rd[kPW];
     const int t = threadIdx.x, nb = min(kPW, nf - k0), r0 = k0 + nb;
     const int mt = nf + 1 - r0, mc = nf - r0;  // rows and columns left
     int ti = 0;
     while ((ti + 1) * (ti + 2) / 2 <= (int)blockIdx.x) ++ti;
     const int tj = (int)blockIdx.x - ti * (ti + 1) / 2, i0 = ti * kPW, j0 = tj * kPW;
     if (tj > 0 && j0 >= mc) return;
-    const double* inv = invs + (size_t)(k0 / kPW) * kPW * kPW;
+    const double* fac = facs + (size_t)(k0 / kPW) * kPW * kPW;
     for (int q = t; q < kPW * kPW; q += 256) {
         const int r = q / kPW, p = q % kPW;
-        I[r * kPS + p] = inv[q];
+        F[q] = p > r ? fac[q] : 0.0;  // column r, row p, below the diagonal
         X[r * kPS + p] = i0 + r < mt && p < nb ? A[(size_t)(r0 + i0 + r) * nf + k0 + p] : 0.0;
         Y[r * kPS + p] = j0 + r < mc && p < nb ? A[(size_t)(r0 + j0 + r) * nf + k0 + p] : 0.0;
+        if (r == p) rd[r] = 1.0 / fac[q];
+    }
+    __syncthreads();
+    if (t < 4 * kPW) {
+        const int l = t & 3;
+        double *xr = X + (t >> 2) * kPS + l, *yr = Y + (t >> 2) * kPS + l;
+        const double* fl = F + l;
+        double x[kPW / 4], y[kPW / 4];
+#pragma unroll
+        for (int i = 0; i < kPW / 4; ++i) {
+            x[i] = xr[4 * i];
+            y[i] = yr[4 * i];
+        }
+        auto quad = [&](auto k) {  // columns 4 k .. 4 k + 3
+            constexpr int K = decltype(k)::value;
+            auto column = [&](auto c) {
+                constexpr int C = decltype(c)::value, P = 4 * K + C;
+                const double xp = quad_lane_f64<C>(x[K] * rd[P]), yp = quad_lane_f64<C>(y[K] * rd[P]);
+#pragma unroll
+                for (int i = K; i < kPW / 4; ++i) {
+                    const double f = fl[P * kPW + 4 * i];  // zero up to the column itself
+                    x[i] = fma(-xp, f, x[i]);
+                    y[i] = fma(-yp, f, y[i]);
+                }
+                x[K] = l == C ? xp : x[K];
+                y[K] = l == C ? yp : y[K];
+            };
+            column(Int<0>());
+            column(Int<1>());
+            column(Int<2>());
+            column(Int<3>());
+        };
+        quad(Int<0>());
+        quad(Int<1>());
+        quad(Int<2>());
+        quad(Int<3>());
+        quad(Int<4>());
+        quad(Int<5>());
+        quad(Int<6>());
+        quad(Int<7>());
+        static_assert(kPW == 32, "eight quads of columns");
+#pragma unroll
+        for (int i = 0; i < kPW / 4; ++i) {
+            xr[4 * i] = x[i];
+            yr[4 * i] = y[i];
+        }
     }
     __syncthreads();
     const int ty = t >> 4, tx = t & 15;
-    double li[2][2], lj[2][2];
-    tile_product(X, I, ty, tx, li);
-    tile_product(Y, I, ty, tx, lj);
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int v = 0; v < 2; ++v) {
-            const int r = 2 * ty + u, c = 2 * tx + v;
-            X[r * kPS + c] = li[u][v];
-            Y[r * kPS + c] = lj[u][v];
-            if (tj == 0 && i0 + r < mt && c < nb) L[(size_t)(r0 + i0 + r) * nf + k0 + c] = li[u][v];
+    if (tj == 0) {
+        for (int q = t; q < kPW * kPW; q += 256) {
+            const int r = q / kPW, p = q % kPW;
+            if (i0 + r < mt && p < nb) L[(size_t)(r0 + i0 + r) * nf + k0 + p] = X[r * kPS + p];
         }
+    }
     if (mc == 0) return;  // the last panel: only the right-hand side's row is left
-    __syncthreads();
     double o[2][2];
     tile_product(X, Y, ty, tx, o);
     const bool next = blockIdx.x == 0;  // the next panel's diagonal block
@@ -502,11 +559,11 @@ __global__ __launch_bounds__(256) void k_ba_panel(int nf, int k0, double* __rest
                 w = *at - o[u][v];
                 *at = w;
             }
-            if (next) I[r * kPS + c] = ii < mc && jj <= ii ? w : (r == c ? 1.0 : 0.0);
+            if (next) D[r * kPS + c] = ii < mc && jj <= ii ? w : (r == c ? 1.0 : 0.0);
         }
     if (!next) return;
     __syncthreads();
-    if (t < 64) invert_factor(I, X, invs + (size_t)(k0 / kPW + 1) * kPW * kPW, t);
+    if (t < 64) factor_block(D, F, facs + (size_t)(k0 / kPW + 1) * kPW * kPW, t);
 }
 
 // Sum over each half of the wave, in every lane of the half.
@@ -535,20 +592,21 @@ __device__ __forceinline__ double half_sum(double v) {
 // (slice, column) sums the column's products with the solved entries over
 // every 32nd row below the panel, whose factors are loaded a panel ahead (they
 // do not depend on x); the slices meet through LDS, each half wave adding one
-// column's, and the same halves form the product with the inverse.  The step
-// is scattered to the free pose entries; the fixed ones are 0.
+// column's; one wave then substitutes through the panel's factor, whose entries
+// were loaded a panel ahead too.  The step is scattered to the free pose
+// entries; the fixed ones are 0.
 constexpr int kBackRows = (6 * PGS_BA_MAX_CAMS + kPW - 1) / kPW;  // rows per slice at most
 
 __global__ __launch_bounds__(kSolveThreads) void k_ba_back(int n_cams, int gauge_axis, const double* __restrict__ L,
-                                                           const double* __restrict__ invs,
+                                                           const double* __restrict__ facs,
                                                            double* __restrict__ dpose) {
-    __shared__ double red[kPW][kPS], xs[6 * PGS_BA_MAX_CAMS], z[kPW];
+    __shared__ double red[kPW][kPS], F[kPW][kPS], xs[6 * PGS_BA_MAX_CAMS], z[kPW];
     const int n6 = 6 * n_cams, nf = n6 - 7, t = threadIdx.x, cc = t % kPW, sl = t / kPW;
     const int last = (nf - 1) / kPW, rows = (nf + kPW - 1) / kPW;
-    double f[kBackRows], iv, y;
+    double f[kBackRows], fe, y;
     auto fetch = [&](int pn) {
         const int k0 = pn * kPW, nb = min(kPW, nf - k0), r0 = k0 + nb;
-        iv = y = 0.0;
+        fe = y = 0.0;
         if (pn < 0) return;  // uniform
 #pragma unroll
         for (int q = 0; q < kBackRows; ++q)
@@ -556,8 +614,8 @@ __global__ __launch_bounds__(kSolveThreads) void k_ba_back(int n_cams, int gauge
                 const int r = r0 + sl + q * kPW;
                 f[q] = cc < nb && r < nf ? L[(size_t)r * nf + k0 + cc] : 0.0;
             }
-        // row cc, column sl of the inverse; the right-hand side's entry sl
-        iv = invs[(size_t)pn * kPW * kPW + cc * kPW + sl];
+        // row cc, column sl of the factor; the right-hand side's entry sl
+        fe = facs[(size_t)pn * kPW * kPW + sl * kPW + cc];
         y = sl < nb ? L[(size_t)nf * nf + k0 + sl] : 0.0;
     };
     for (int e = t; e < 6 * PGS_BA_MAX_CAMS; e += kSolveThreads) xs[e] = 0.0;
@@ -573,15 +631,25 @@ __global__ __launch_bounds__(kSolveThreads) void k_ba_back(int n_cams, int gauge
                 if (r < nf) v = fma(f[q], xs[r], v);
             }
         red[sl][cc] = v;
-        const double iw = iv, yy = y;
+        F[sl][cc] = fe;
+        const double yy = y;
         fetch(pn - 1);
         __syncthreads();
         // column sl: its slices' sums, one per lane of the half
         const double w = yy - half_sum(red[cc][sl]);
         if (cc == 0) z[sl] = w;
         __syncthreads();
-        const double x = half_sum(iw * z[cc]);  // (L11^-T z)_sl = sum over q of inv[q][sl] z[q]
-        if (cc == 0 && k0 + sl < nf) xs[k0 + sl] = x;
+        if (t < 64) {  // lane cc: entry cc (both halves alike)
+            double left = z[cc], x = 0.0;
+            const double rd = 1.0 / F[cc][cc];
+#pragma unroll 8
+            for (int q = kPW - 1; q >= 0; --q) {
+                const double own = left * rd, xq = read_lane_f64(own, q);
+                if (cc == q) x = own;
+                left = fma(-xq, F[cc][q], left);  // of no use to lanes past q
+            }
+            if (t < kPW && k0 + cc < nf) xs[k0 + cc] = x;
+        }
         __syncthreads();
     }
     for (int e = t; e < n6; e += kSolveThreads) {
@@ -907,7 +975,7 @@ __global__ __launch_bounds__(256) void k_compact_obs(pgs_ba_problem pb, const ui
 
 // Workspace layout of one problem size.
 struct BaWs {
-    double *pt_rec, *cam_part, *A, *L, *invs, *part;
+    double *pt_rec, *cam_part, *A, *L, *facs, *part;
     size_t bytes;
 };
 
@@ -925,7 +993,7 @@ BaWs ba_layout(void* base, int C, int M, int O) {
     w.cam_part = take((size_t)C * kCamSplit * (36 * (size_t)C + kPose));
     w.A = take((nf + 1) * nf);
     w.L = take((nf + 1) * nf);
-    w.invs = take(((nf + kPW - 1) / kPW) * kPW * kPW);
+    w.facs = take(((nf + kPW - 1) / kPW) * kPW * kPW);
     w.part = take(kCostBlocks);
     w.bytes = off;
     return w;
@@ -943,12 +1011,12 @@ bool cameras_lds_reserved() {
 // The solve as a chain of launches, one per panel.
 void solve_panels(int C, int gauge_axis, const BaWs& w, double* dpose, hipStream_t s) {
     const int nf = 6 * C - 7;
-    k_ba_first<<<1, 64, 0, s>>>(nf, w.A, w.invs);
+    k_ba_first<<<1, 64, 0, s>>>(nf, w.A, w.facs);
     for (int k0 = 0; k0 < nf; k0 += kPW) {
         const int mt = nf + 1 - min(k0 + kPW, nf), tiles = (mt + kPW - 1) / kPW;
-        k_ba_panel<<<tiles * (tiles + 1) / 2, 256, 0, s>>>(nf, k0, w.A, w.L, w.invs);
+        k_ba_panel<<<tiles * (tiles + 1) / 2, 256, 0, s>>>(nf, k0, w.A, w.L, w.facs);
     }
-    k_ba_back<<<1, kSolveThreads, 0, s>>>(C, gauge_axis, w.L, w.invs, dpose);
+    k_ba_back<<<1, kSolveThreads, 0, s>>>(C, gauge_axis, w.L, w.facs, dpose);
 }
 
 pgs_status check_problem(const pgs_ba_problem* pb, const char* who) {

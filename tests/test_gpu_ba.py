@@ -227,3 +227,37 @@ def test_ba_step_panel_and_track_sizes(n_cams, n_points, max_views, twice):
     x = np.r_[gp.ravel(), gq.ravel()][free]
     res = (A + lam * np.diag(np.diag(A))) @ x - b[free]
     assert np.abs(res).max() <= 1e-10 * np.abs(b[free]).max()
+
+
+@pytest.mark.parametrize("n_cams,n_points,lam", [(12, 8, 1e-12), (12, 60, 1e-12), (20, 50, 1e-12), (12, 8, 1e-9)])
+def test_ba_step_of_a_narrow_view_is_backward_stable(n_cams, n_points, lam):
+    # cameras a unit apart looking at a patch of 0.1 from 200 away: turning and
+    # moving a camera do almost the same to its pixels, so the reduced
+    # system's diagonal blocks are close to singular.  A factorisation by
+    # substitution still solves the normal equations to about a unit of
+    # roundoff of their terms, |r_i| <= 2 u sqrt(a_ii) sum_j sqrt(a_jj) |x_j|
+    # (errors of random sign); products with inverted blocks miss that by an
+    # order of magnitude
+    from paper_2601_17354_amd import ba
+    for seed in range(3):
+        rng = np.random.default_rng(seed)
+        C, M = n_cams, n_points
+        R0, c0 = np.tile(np.eye(3), (C, 1, 1)), rng.normal(size=(C, 3))
+        P = np.stack([rng.uniform(-0.05, 0.05, M), rng.uniform(-0.05, 0.05, M), 200 + rng.uniform(-0.005, 0.005, M)], 1)
+        cam, pt = np.tile(np.arange(C), M), np.repeat(np.arange(M), C)
+        x = P[pt] - c0[cam]
+        uv = 2000.0 * x[:, :2] / x[:, 2:] + np.array([960.0, 720.0]) + rng.normal(0, 0.5, (C * M, 2))
+        tr = dict(n_cams=C, n_points=M, fx=2000.0, fy=2000.0, cx=960.0, cy=720.0, obs_cam=cam.astype(np.int32),
+                  obs_pt=pt.astype(np.int32), obs_uv=uv, gauge_axis=int(np.abs(c0[1] - c0[0]).argmax()), R0=R0, c0=c0,
+                  P0=P + rng.normal(0, 0.02, P.shape))
+        pb = ba.BAProblem.from_tracks(tr, huber_delta=DELTA)
+        dpose, dpoint = ba.step(pb, ba.state(R0, c0, tr["P0"]), lam)
+        H, b = oba.normal_equations(tr, R0, c0, tr["P0"], DELTA)
+        free = np.r_[oba.free_pose_params(C, tr["gauge_axis"]), 6 * C + np.arange(3 * M)]
+        A = (H + lam * np.diag(np.diag(H)))[np.ix_(free, free)]
+        sol = np.r_[dpose.cpu().numpy().ravel(), dpoint.cpu().numpy().ravel()][free]
+        d = np.sqrt(np.diag(A))
+        res = np.abs(A.astype(np.longdouble) @ sol - b[free]) / d
+        eta = float(res.max() / (d * np.abs(sol)).sum())
+        say(f"[ba] narrow view C={C} M={M} lam={lam} seed {seed}: backward error {eta:.1e}")
+        assert eta <= 2.0 ** -52
