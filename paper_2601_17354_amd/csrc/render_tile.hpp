@@ -838,6 +838,12 @@ __device__ __forceinline__ void zero_acc(float (&acc)[NA][9][BG + 1], int t, int
     for (int idx = t; idx < NA * 9 * (BG + 1); idx += NT) (&acc[0][0][0])[idx] = 0.f;
 }
 
+// The first step of a 64-step window that `any` marks.  None left: step 0,
+// whose splat every window has staged (a batch of 224 or 32 splats ends inside
+// a window, so step 63 may lie past its arrays).
+__host__ __device__ constexpr int first_step(uint64_t any) { return any ? __builtin_ctzll(any) : 0; }
+static_assert(first_step(0) == 0 && first_step(1ull << 63) == 63 && first_step(0x50) == 4, "steps");
+
 // Up to four non-empty groups of a 64-step window, front to back: the
 // step within the window, the lane mask and the first entry (relative to the
 // wave's region) of each; an unused slot has an empty mask.
@@ -851,7 +857,7 @@ __device__ __forceinline__ void take_groups(uint64_t& any, uint64_t mv, uint32_t
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const uint64_t real = (uint64_t)((int64_t)(any ? -1 : 0));
-        g.gi[q] = __builtin_ctzll(any | (1ull << 63));
+        g.gi[q] = first_step(any);
         g.gm[q] = read_lane64(mv, g.gi[q]) & real;
         g.gc[q] = cursor;
         any &= any - 1;
@@ -875,7 +881,9 @@ __device__ __forceinline__ void load_groups(__amdgpu_buffer_rsrc_t went, const T
 
 // Gradients of four groups at this lane's pixel, reduced over the wave into
 // the batch accumulator; a lane without an entry in a group contributes
-// exact zeros there and keeps its dL/dC_out.
+// zeros there (or what a splat that is not finite makes of zero) and keeps its
+// dL/dC_out.  An unused slot's terms are formed from some staged splat and
+// entry: they stay in the quads of its own group, which add nothing.
 template <int BG, int EW, int NT, class Lds>
 __device__ __forceinline__ void bwd_groups(const TraceGroups& g, const float4* e, Lds& L, uint32_t slot0, float fpx,
                                            float fpy, int lane, int half, float& g0, float& g1, float& g2) {

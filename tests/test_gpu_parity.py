@@ -249,3 +249,21 @@ def test_recompute_keeps_a_bad_pixel_to_its_own_splats():
     assert np.isfinite(g["grad2d"][:, rest]).all()
     for f, name in enumerate(OUT_FIELDS):
         assert_block_close(g["grad2d"][f], clean["grad2d"][f], GRAD_TOL, mask=rest, what=f"d{name}")
+
+
+@pytest.mark.parametrize("words", [3, 4])
+@pytest.mark.parametrize("n", [193, 196, 197, 224, 225, 229, 449])
+def test_traced_lists_that_end_inside_a_window(n, words):
+    # the traced backward's batches hold 224 splats, so their last window has
+    # 32 steps: one to five groups of it, the batch's end, and the next batch
+    P, cam, _ = synth.cfg1_inputs(8, n=n, width=33, height=18, focal=30.0)
+    P[3:6] += 1.5
+    P[10] -= 2.0
+    dl = np.random.default_rng(n).normal(size=(3, 18, 33)).astype(np.float32)
+    say(f"[parity] traced lists n={n} words={words}")
+    proj, bins, fwd = pipeline.forward(P, cam, bg=(0.2, 0.4, 0.1))
+    _, o_g2d, taint = pipeline.backward(P, cam, proj, bins, fwd, dl, "cached")
+    for tile in ((16, 16), (32, 8)):
+        g = run_gpu(P, cam, 0, cached=True, bg=(0.2, 0.4, 0.1), dl_dimage=dl, tile=tile, trace_words=words)
+        for f, name in enumerate(OUT_FIELDS):
+            assert_block_close(g["grad2d"][f], o_g2d[f], GRAD_TOL, mask=~taint, what=f"tile={tile} d{name}")
