@@ -204,14 +204,15 @@ __device__ __forceinline__ uint64_t step_lanes(uint64_t hit, uint64_t below, uin
     return took;
 }
 
+// v_writelane_b32, for which this compiler has no builtin, by the intrinsic's
+// name (the instruction in assembly needs m0, which an asm block must not take).
+extern "C" __device__ __attribute__((const)) uint32_t pgs_writelane(uint32_t v, uint32_t lane,
+                                                                    uint32_t old) __asm("llvm.amdgcn.writelane.i32");
+
 // Puts the wave-uniform v into lane `lane` of (lo, hi).
 __device__ __forceinline__ void write_lane64(uint32_t& lo, uint32_t& hi, uint64_t v, int lane) {
-    asm("s_mov_b32 m0, %4\n"
-        "v_writelane_b32 %0, %2, m0\n"
-        "v_writelane_b32 %1, %3, m0"
-        : "+v"(lo), "+v"(hi)
-        : "s"((uint32_t)v), "s"((uint32_t)(v >> 32)), "s"(lane)
-        : "m0");
+    lo = pgs_writelane((uint32_t)v, (uint32_t)lane, lo);
+    hi = pgs_writelane((uint32_t)(v >> 32), (uint32_t)lane, hi);
 }
 
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
