@@ -272,6 +272,8 @@ __global__ __launch_bounds__(64) void k_mvs_ref(const pgs_camera* __restrict__ c
 
 constexpr int kCostPix = 128;  // pixels per cost workgroup
 constexpr int kCostLane = 4;   // consecutive planes per lane
+// four costs of a volume, of which no alignment beyond a byte's is asked
+typedef uint32_t word_u __attribute__((aligned(1)));
 
 // x / z and y / z, correctly rounded, from one reciprocal: the operations of
 // the hardware's own divide (reciprocal refined once, each quotient corrected
@@ -421,7 +423,7 @@ __global__ __launch_bounds__(256) void k_cost(const pgs_camera* __restrict__ cam
 #pragma unroll
         for (int u = 0; u < kCostLane; ++u)
             word |= (uint32_t)(ok[u] ? __popcll(cen ^ g[u]) : kCostOut) << (8 * u);
-        *reinterpret_cast<uint32_t*>(out + (size_t)i * D) = word;
+        *reinterpret_cast<word_u*>(out + (size_t)i * D) = word;
     }
 }
 
@@ -477,14 +479,12 @@ struct Sweep {
     struct Bytes {
         uint32_t w[NB];
     };
-    // no alignment beyond a byte's is asked of the cost volume
     typedef uint32_t Any __attribute__((ext_vector_type(NB == 1 ? 2 : NB), aligned(1)));
 
     __device__ static __forceinline__ Bytes load(const uint8_t* p) {
         Bytes b;
         if constexpr (NB == 1) {
-            typedef uint32_t One __attribute__((aligned(1)));
-            b.w[0] = *reinterpret_cast<const One*>(p);
+            b.w[0] = *reinterpret_cast<const word_u*>(p);
         } else {
             const Any v = *reinterpret_cast<const Any*>(p);
 #pragma unroll
@@ -494,8 +494,7 @@ struct Sweep {
     }
     __device__ static __forceinline__ void store(uint8_t* p, const Bytes& b) {
         if constexpr (NB == 1) {
-            typedef uint32_t One __attribute__((aligned(1)));
-            *reinterpret_cast<One*>(p) = b.w[0];
+            *reinterpret_cast<word_u*>(p) = b.w[0];
         } else {
             Any v;
 #pragma unroll

@@ -322,3 +322,32 @@ def test_sgm_costs_past_the_census_range(T, W, H, D, p2, agg):
         np.testing.assert_array_equal(depth[t].cpu().numpy() > 0, d > 0)
         np.testing.assert_allclose(depth[t].cpu().numpy(), d, rtol=1e-6, atol=0)
         np.testing.assert_allclose(conf[t].cpu().numpy(), c, rtol=1e-6, atol=1e-7)
+
+
+@pytest.mark.parametrize("shift", [1, 2, 3])
+@pytest.mark.parametrize("W,H,D", [(65, 41, 64), (50, 33, 192)])
+def test_cost_volume_at_any_byte(W, H, D, shift):
+    # the cost volume's address is any byte's: the same costs and depths as at
+    # a word's, nothing written around it
+    from paper_2601_17354_amd import mvs
+    _, cams, g, _, pts = _views(W, H, [0, 1])
+    cams = cams[:2]
+    ranges = np.array([omvs.depth_range(cams[0], pts), [0.0, 0.0]])
+    pr = _params(D)
+    want, _, depth, conf = _gpu_depth(cams, g, [0], [1, 0], ranges, pr, want_agg=False)
+    n = want.size
+    raw = torch.full((n + 16,), 201, dtype=torch.uint8, device="cuda")
+    cost = raw[shift:shift + n].view(1, H, W, D)
+    cen = torch.empty((2, H, W), dtype=torch.int64, device="cuda")
+    mvs.pgs_mvs_census(torch.as_tensor(g, device="cuda"), cen)
+    tg = torch.zeros(1, dtype=torch.int32, device="cuda")
+    rg = torch.as_tensor(ranges, device="cuda")
+    mvs.pgs_mvs_cost(mvs.cameras_tensor(cams), W, H, cen, tg, torch.as_tensor(np.int32([1, 0]), device="cuda"), rg, pr,
+                     cost)
+    d, c = torch.empty((1, H, W), device="cuda"), torch.empty((1, H, W), device="cuda")
+    mvs.pgs_mvs_sgm(cost, tg, rg, pr, d, c)
+    out = raw.cpu().numpy()
+    np.testing.assert_array_equal(out[shift:shift + n], want.ravel())
+    assert (out[:shift] == 201).all() and (out[shift + n:] == 201).all()
+    np.testing.assert_array_equal(d.cpu().numpy(), depth)
+    np.testing.assert_array_equal(c.cpu().numpy(), conf)
