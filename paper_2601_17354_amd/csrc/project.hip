@@ -458,6 +458,9 @@ __device__ __forceinline__ void bwd_geometry(const double (&mu)[3], const Shape&
     for (int k = 0; k < 4; ++k) gqraw[k] = (gq[k] - S3.qn[k] * dotq) / S3.qlen;
 }
 
+// Four words of a 2D-gradient record, of which a float's alignment is asked.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
 // Lane's Gaussian of a wave; P and grads point at the wave's first Gaussian, so
 // that a row's address is a scalar and the lane's offset.  Bit k of seen: view k
 // holds the Gaussian.  view(k, rec) gives view k's camera and where its 2D
@@ -480,15 +483,15 @@ __device__ __forceinline__ void project_bwd_rows(const float* __restrict__ P, in
 #pragma unroll
         for (int r = 0; r < 11; ++r) acc[r] = row_start(grads, r, n)[lane];
         const auto add = [&](int r, double g) { acc[r] = (float)((double)acc[r] + g); };
-        float4 n0, n1;
+        f32x4u n0, n1;
         float n2;
         const auto fetch = [&](int k) {
             if (!((seen >> k) & 1u)) return;  // also past the last view
             const float* rec;
             view(k, rec);
             rec += lane * PGS_GRAD2D_STRIDE;
-            n0 = reinterpret_cast<const float4*>(rec)[0];
-            n1 = reinterpret_cast<const float4*>(rec)[1];
+            n0 = reinterpret_cast<const f32x4u*>(rec)[0];
+            n1 = reinterpret_cast<const f32x4u*>(rec)[1];
             n2 = rec[8];
         };
         fetch(0);
@@ -496,7 +499,7 @@ __device__ __forceinline__ void project_bwd_rows(const float* __restrict__ P, in
         for (int k = 0; k < nv; ++k) {
             const float* rec;
             const CamD& cam = view(k, rec);
-            const float4 r0 = n0, r1 = n1;
+            const f32x4u r0 = n0, r1 = n1;
             const float gcol[3] = {r1.z, r1.w, n2};
             fetch(k + 1);
             if (!((seen >> k) & 1u)) continue;

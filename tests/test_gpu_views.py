@@ -450,3 +450,33 @@ def test_bin_sort_views_past_one_million_items_matches_per_view_calls():
         np.testing.assert_array_equal(got_r[1, t0:t1][nonempty], r1n[1, t0:t1][nonempty] + base)
         np.testing.assert_array_equal(got_r[1, t0:t1][~nonempty] - got_r[0, t0:t1][~nonempty], 0)
         base += m
+
+
+@pytest.mark.parametrize("deg", [0, 3])
+def test_projection_gradients_from_records_at_any_float(deg):
+    # 2D-gradient records that start at any float, not a 16-byte line: the
+    # same bits, one view and several
+    from paper_2601_17354_amd import binding as B
+    n, V = 130, 3
+    P = synth.surface_gaussians(synth.spheres_planes_scene(2), 400, seed=5, sh_degree=deg, logit_sigma=0.5)[:, :n]
+    cams = synth.ring_cameras(V, 160, 120)
+    views, F = B.ViewBatch(cams, (16, 16)), P.shape[0]
+    params = torch.as_tensor(np.ascontiguousarray(P), device=DEV)
+    out = [torch.empty((V, n, 16), device=DEV), torch.zeros((V, n), dtype=torch.int32, device=DEV),
+           torch.zeros((V, 2, n), dtype=torch.int32, device=DEV), torch.zeros((V, n), dtype=torch.int32, device=DEV)]
+    B.pgs_project_views(views, params, n, deg, *out)
+    rec = np.random.default_rng(deg).normal(size=V * n * 16).astype(np.float32)
+    got = []
+    for shift in range(4):
+        raw = torch.full((V * n * 16 + 4,), float("nan"), device=DEV)
+        g2d = raw[shift:shift + V * n * 16].view(V, n, 16)
+        g2d.copy_(torch.as_tensor(rec, device=DEV).view(V, n, 16))
+        a, b = torch.zeros((F, n), device=DEV), torch.zeros((F, n), device=DEV)
+        B.pgs_project_bwd_views(views, params, n, deg, out[1], g2d, a)
+        for v in range(V):
+            B.pgs_project_bwd(params, n, deg, cams[v], out[1][v], g2d[v], b)
+        got.append((a.cpu().numpy(), b.cpu().numpy()))
+    assert np.isfinite(got[0][0]).all() and np.abs(got[0][0]).max() > 0
+    for a, b in got:
+        np.testing.assert_array_equal(a, got[0][0])
+        np.testing.assert_array_equal(b, got[0][0])
