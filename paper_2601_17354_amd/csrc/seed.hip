@@ -27,8 +27,9 @@
 // more than k; its entries' exact distances and indices are then formed again
 // and sorted.  Rounding is monotone, so every point left out has an exact
 // distance above the k-th whenever the k-th's rounding is below the list's
-// last key; where it is not (many points at one distance), the lane searches
-// again with exact comparisons (knn_exact).  On 300k points of a
+// last key.  Where it is not (many points at one distance), the points that
+// round to the k-th's float32 are gone through again with keys of their exact
+// distances (knn_ties).  On 300k points of a
 // scene's surfaces with k = 16 the search went from 0.93 to 0.20 ms (41M vector
 // instructions, 306 MB of writes scattered to the queries' own order) and the
 // whole call from 1.06 to 0.27 ms; on 2000 points from 7.8 to 0.17 ms.
@@ -330,8 +331,7 @@ __device__ __forceinline__ void knn_insert(double d, int idx, double (&bd)[K], i
 }
 
 // Search of one query with exact comparisons throughout (the general path:
-// many points at one distance, distances past float32, coordinates that are
-// not finite).
+// distances outside float32's normal numbers, coordinates that are not finite).
 template <int K>
 __device__ __noinline__ void knn_exact(const float4* __restrict__ sorted, int m, const GridDesc& g,
                                        const uint32_t* __restrict__ starts, float4 qp, int* __restrict__ nbr,
@@ -403,6 +403,74 @@ __device__ __forceinline__ double key_max(double a, double b) {
     return r;
 }
 
+// Takes key x into the sorted list a, dropping its last.
+template <int N>
+__device__ __forceinline__ void key_insert(double (&a)[N], double x) {
+#pragma unroll
+    for (int k = N - 1; k > 0; --k) a[k] = key_min(a[k], key_max(a[k - 1], x));
+    a[0] = key_min(a[0], x);
+}
+
+// Entries from..K-1 of a query: the nearest points whose distance rounds to the
+// float32 r (a normal number, or zero), sorted by keys of (exact distance,
+// index).  The doubles that round to one float32 follow one another, 2^29 or so
+// of them, so a distance's place among them takes the upper half of a key.  The
+// points lie in the cells between the query's coordinates less and plus the root
+// of r (a cell number does not fall as a coordinate grows).  False where a
+// distance rounds to zero without being zero.  Searched from nothing with exact
+// comparisons, a lattice of 300k points took 993 us and 10k points 30 times each
+// 366, more than before there were lists (856 and 240); 455 and 190 now.
+template <int K>
+__device__ __forceinline__ bool knn_ties(const float4* __restrict__ sorted, int m, const GridDesc& g,
+                                         const uint32_t* __restrict__ starts, const float4& qp, float r, int from,
+                                         int* __restrict__ nbr, double* __restrict__ d2out) {
+    const double c[3] = {qp.x, qp.y, qp.z};
+    const double rad = sqrt((double)r * (1.0 + 1e-6) + 0x1p-149);  // what rounds to r is nearer
+    int lo[3], hi[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const double w = rad + fabs(c[a]) * 1e-15;  // the sums' rounding
+        lo[a] = cell_axis(c[a] - w, g.lo[a], g.h, g.dims[a]);
+        hi[a] = cell_axis(c[a] + w, g.lo[a], g.h, g.dims[a]);
+    }
+    // the least double that rounds to r, or the one that ties below it
+    const double least =
+        r > 0.0f ? 0.5 * ((double)r + (double)__uint_as_float(__float_as_uint(r) - 1u)) : 0.0;
+    const long long first = __double_as_longlong(least);
+    bool exact = true;
+    double b[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) b[k] = knn_key(kInfBits, 0xffffffffu);
+    for (int z = lo[2]; z <= hi[2]; ++z)
+        for (int y = lo[1]; y <= hi[1]; ++y) {
+            const uint32_t row = ((uint32_t)z * g.dims[1] + y) * g.dims[0];
+            const uint32_t e = starts[row + hi[0] + 1];
+            for (uint32_t t0 = starts[row + lo[0]]; t0 < e; t0 += 4) {
+                float4 p[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) p[u] = sorted[min(t0 + u, e - 1)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const double d = sqdist(c[0], c[1], c[2], p[u].x, p[u].y, p[u].z);
+                    if ((float)d == r && t0 + u < e && __float_as_int(p[u].w) != __float_as_int(qp.w)) {
+                        const uint32_t place = (uint32_t)(__double_as_longlong(d) - first);
+                        exact = exact && (r > 0.0f || d == 0.0);
+                        const double x = knn_key(place, __float_as_uint(p[u].w));
+                        if (x < b[K - 1]) key_insert<K>(b, x);
+                    }
+                }
+            }
+        }
+    const int q = __float_as_int(qp.w);
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        if (from + k < K) {
+            nbr[(size_t)(from + k) * m + q] = __double2loint(b[k]);
+            d2out[(size_t)(from + k) * m + q] = __longlong_as_double(first + (long long)(uint32_t)__double2hiint(b[k]));
+        }
+    return exact;
+}
+
 // Bound by vector issue: about 15 instructions per candidate and, whenever
 // one of the wave's lanes takes it, two per slot of the list.
 template <int K>
@@ -442,11 +510,7 @@ __global__ __launch_bounds__(kKnnThreads) void k_knn_grid(const float4* __restri
                 const uint32_t t = t0 + u;
                 const float d = (float)sqdist(qx, qy, qz, p[u].x, p[u].y, p[u].z);
                 const double x = knn_key(__float_as_uint(d) & 0x7fffffffu, t);
-                if (t < e && t != (uint32_t)j && x < a[KE - 1]) {
-#pragma unroll
-                    for (int k = KE - 1; k > 0; --k) a[k] = key_min(a[k], key_max(a[k - 1], x));
-                    a[0] = key_min(a[0], x);
-                }
+                if (t < e && t != (uint32_t)j && x < a[KE - 1]) key_insert<KE>(a, x);
             }
         }
     };
@@ -458,19 +522,24 @@ __global__ __launch_bounds__(kKnnThreads) void k_knn_grid(const float4* __restri
         const uint32_t c = ((uint32_t)z * ny + y) * nx;
         take(starts[c + x0], starts[c + x1 + 1]);
     };
-    // the 3 x 3 x 3 block, the query's own row first
-    run_of(cy, cz, cx - 1, cx + 1);
-    for (int i = 0; i < 9; ++i)
-        if (i != 4) run_of(cy + i % 3 - 1, cz + i / 3 - 1, cx - 1, cx + 1);
-    const int rmax = max(nx, max(ny, nz));
-    for (int r = 2;; ++r) {
-        // visited: every cell within r - 1; the k-th distance is at most its
-        // rounded key's value and a unit of rounding more (relative, or among
-        // the subnormal numbers their spacing)
-        const double reach = ((double)(r - 1) + gap) * h;
+    // whether no point farther than `reach` can enter or tie: the k-th distance
+    // is at most its rounded key's value and a unit of rounding more (relative,
+    // or among the subnormal numbers their spacing)
+    auto within = [&](double reach) {
         const uint32_t kth = (uint32_t)__double2hiint(a[K - 1]);
-        const double kth_most = (double)__uint_as_float(kth) * (1.0 + 1e-6) + 0x1p-149;
-        if (r > rmax || (kth < kInfBits && kth_most <= reach * reach * (1.0 - 1e-12))) break;
+        const double most = (double)__uint_as_float(kth) * (1.0 + 1e-6) + 0x1p-149;
+        return kth < kInfBits && most <= reach * reach * (1.0 - 1e-12);
+    };
+    // the 3 x 3 x 3 block, the query's own row first (enough where a point is
+    // repeated more than K times)
+    run_of(cy, cz, cx - 1, cx + 1);
+    const bool at_once = gap > 0.0 && within(gap * h);
+    for (int i = at_once ? 9 : 0; i < 9; ++i)
+        if (i != 4) run_of(cy + i % 3 - 1, cz + i / 3 - 1, cx - 1, cx + 1);
+    const int rmax = at_once ? 0 : max(nx, max(ny, nz));
+    for (int r = 2; r <= rmax; ++r) {
+        // visited: every cell within r - 1
+        if (within(((double)(r - 1) + gap) * h)) break;
         for (int dz = -r; dz <= r; ++dz)
             for (int dy = -r; dy <= r; ++dy) {
                 if (dz == -r || dz == r || dy == -r || dy == r) {
@@ -508,16 +577,22 @@ __global__ __launch_bounds__(kKnnThreads) void k_knn_grid(const float4* __restri
         }
     }
     // every point left out rounds to the last key's distance or more
-    if (!(__float_as_uint((float)bd[K - 1]) < (uint32_t)__double2hiint(a[KE - 1]))) {
-        knn_exact<K>(sorted, m, g, starts, qp, nbr, d2out);
-        return;
-    }
+    const float r = (float)bd[K - 1];
+    const bool sure = __float_as_uint(r) < (uint32_t)__double2hiint(a[KE - 1]);
     const int q = __float_as_int(qp.w);
+    int below = 0;  // entries that round to less than the k-th
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        nbr[(size_t)k * m + q] = bi[k];
-        d2out[(size_t)k * m + q] = bd[k];
+        if (sure || (float)bd[k] < r) {
+            nbr[(size_t)k * m + q] = bi[k];
+            d2out[(size_t)k * m + q] = bd[k];
+            below = k + 1;
+        }
     }
+    if (sure) return;
+    if (!(__float_as_uint(r) < kInfBits && (r == 0.0f || r >= 0x1p-126f)) ||
+        !knn_ties<K>(sorted, m, g, starts, qp, r, below, nbr, d2out))
+        knn_exact<K>(sorted, m, g, starts, qp, nbr, d2out);
 }
 
 // Workspace of pgs_knn for m points.

@@ -524,3 +524,30 @@ def test_knn_of_minute_spacing(scale):
             ids, dd = o_seed.knn(pts, list(range(600)), k)
             np.testing.assert_array_equal(nbr.cpu().numpy().T, ids)
             np.testing.assert_array_equal(d2.cpu().numpy().T, dd)
+
+
+@pytest.mark.parametrize("k", [4, 8, 16, 32])
+@pytest.mark.parametrize("case", ["shell", "copies", "close copies", "plane lattice"])
+def test_knn_of_many_points_at_one_rounded_distance(case, k):
+    # more points than the lists hold round to the k-th's float32: distances
+    # that differ past float32 (a sphere's points from its centre and from each
+    # other), exact copies, copies beside cell faces, and equal distances
+    rng = np.random.default_rng(23)
+    if case == "shell":
+        v = rng.normal(size=(700, 3))
+        pts = np.r_[v / np.linalg.norm(v, axis=1, keepdims=True), np.zeros((2, 3)), [[1e-4, 0, 0]]].astype(np.float32)
+    elif case == "copies":
+        pts = np.repeat(rng.uniform(size=(40, 3)).astype(np.float32), 50, axis=0)[rng.permutation(2000)]
+    elif case == "close copies":
+        at = np.r_[rng.integers(0, 9, (30, 3)) / 8.0, rng.uniform(size=(10, 3))].astype(np.float32)
+        pts = np.repeat(at, 40, axis=0)
+        pts[::3] = np.nextafter(pts[::3], np.float32(2))
+    else:
+        g = np.arange(40, dtype=np.float32) * np.float32(0.1)
+        pts = np.stack(np.meshgrid(g, g, np.zeros(1, np.float32), indexing="ij"), -1).reshape(-1, 3)
+    _, nbr, d2 = _knn_gpu(pts, k)
+    torch.cuda.synchronize()
+    q = sorted(set(range(0, len(pts), 7)) | set(range(max(0, len(pts) - 3), len(pts))))
+    ids, dd = o_seed.knn(pts, q, k)
+    np.testing.assert_array_equal(nbr.cpu().numpy()[:, q].T, ids)
+    np.testing.assert_array_equal(d2.cpu().numpy()[:, q].T, dd)
