@@ -551,3 +551,30 @@ def test_knn_of_many_points_at_one_rounded_distance(case, k):
     ids, dd = o_seed.knn(pts, q, k)
     np.testing.assert_array_equal(nbr.cpu().numpy()[:, q].T, ids)
     np.testing.assert_array_equal(d2.cpu().numpy()[:, q].T, dd)
+
+
+@pytest.mark.parametrize("k", [4, 16])
+@pytest.mark.parametrize("bad", ["nan", "inf", "both"])
+def test_knn_with_points_that_are_not_finite(bad, k):
+    # a distance that is not a number is never taken, an infinite one after all
+    # others by index; a query with too few keeps empty places
+    rng = np.random.default_rng(29)
+    pts = rng.normal(size=(120, 3)).astype(np.float32)
+    if bad != "inf":
+        pts[[7, 50]] = np.nan
+        pts[90, 1] = np.nan
+    if bad != "nan":
+        pts[11, 0], pts[60, 2], pts[61, 2] = np.inf, -np.inf, -np.inf
+    _, nbr, d2 = _knn_gpu(pts, k)
+    torch.cuda.synchronize()
+    P = pts.astype(np.float64)
+    for i in range(120):
+        with np.errstate(invalid="ignore"):
+            d = P - P[i]
+            d = (d[:, 0] * d[:, 0] + d[:, 1] * d[:, 1]) + d[:, 2] * d[:, 2]
+        idx = np.flatnonzero(~np.isnan(d) & (np.arange(120) != i))
+        idx = idx[np.lexsort((idx, d[idx]))][:k]
+        want = np.full(k, 0x7FFFFFFF), np.full(k, np.inf)
+        want[0][:len(idx)], want[1][:len(idx)] = idx, d[idx]
+        np.testing.assert_array_equal(nbr[:, i].cpu().numpy(), want[0])
+        np.testing.assert_array_equal(d2[:, i].cpu().numpy(), want[1])
