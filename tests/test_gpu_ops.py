@@ -578,3 +578,27 @@ def test_knn_with_points_that_are_not_finite(bad, k):
         want[0][:len(idx)], want[1][:len(idx)] = idx, d[idx]
         np.testing.assert_array_equal(nbr[:, i].cpu().numpy(), want[0])
         np.testing.assert_array_equal(d2[:, i].cpu().numpy(), want[1])
+
+
+@pytest.mark.parametrize("W,H", [(127, 5), (128, 4), (129, 9), (256, 8), (257, 13), (385, 601), (129, 2050), (641, 334)])
+def test_loss_at_the_edges_of_128_column_strips(W, H):
+    # a last strip of one column, of one column less, whole ones, and a lane's
+    # pair of columns cut by the image's edge; heights at the waves' rows (4 to
+    # 7 at these sizes), less and more than a whole wave
+    from paper_2601_17354_amd import binding as B
+    rng = np.random.default_rng(W * 3 + H)
+    x = rng.uniform(size=(3, H, W)).astype(np.float32)
+    y = np.clip(x + rng.normal(0, 0.2, x.shape), 0, 1).astype(np.float32)
+    guard = 1024
+    dl = torch.full((x.size + guard,), 7.0, device=DEV)
+    loss = torch.zeros(1, device=DEV)
+    ws = torch.empty(B.pgs_loss_workspace(W, H), dtype=torch.uint8, device=DEV)
+    B.pgs_loss_l1_dssim(torch.as_tensor(x, device=DEV), torch.as_tensor(y, device=DEV), W, H, 0.2, loss,
+                        dl[:x.size].view(3, H, W), ws)
+    torch.cuda.synchronize()
+    want, wg = o_loss.l1_dssim(x, y, 0.2)
+    assert abs(loss.item() - want) <= 1e-5 * abs(want)
+    out = dl.cpu().numpy()
+    for c in range(3):
+        assert_block_close(out[:x.size].reshape(3, H, W)[c], wg[c], 1e-4, what=f"dL/dx[{c}]")
+    assert (out[x.size:] == 7.0).all()
