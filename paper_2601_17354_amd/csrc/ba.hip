@@ -315,13 +315,8 @@ __global__ __launch_bounds__(kCamThreads) void k_ba_cameras(pgs_ba_problem pb, c
     }
 }
 
-// Free (moving) pose parameter k of nf: skips camera 0's six and camera 1's
-// centre coordinate along the gauge axis.
-__device__ __forceinline__ int free_param(int k, int gauge_axis) {
-    const int p = k + 6;                        // past camera 0
-    return p >= 9 + gauge_axis ? p + 1 : p;     // past camera 1's fixed centre coordinate
-}
-// Its inverse: the free parameter's number, or -1.
+// Number of pose parameter p among the free (moving) ones, or -1: camera 0's six
+// and camera 1's centre coordinate along the gauge axis are fixed.
 __device__ __forceinline__ int free_index(int p, int gauge_axis) {
     if (p < 6 || p == 9 + gauge_axis) return -1;
     return p - 6 - (p > 9 + gauge_axis ? 1 : 0);
