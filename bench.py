@@ -500,7 +500,12 @@ def mvs_runs(width=960, height=720, n_targets=8, iters=5):
     rel = np.concatenate(rel)
     npix, D = width * height, pr.n_planes
     cost_bytes = n_targets * (npix * D + 16 * npix)
-    sgm_bytes = n_targets * (16 * npix * D + 8 * npix)
+    # bytes a cell moves in the aggregation: whole-line sweeps read the costs
+    # four times and write and read one byte of row sum, with a checkpoint every
+    # 16 steps; few lines run three directions side by side with their path
+    # costs stored; depth and confidence per pixel
+    few = (height + 3) // 4 * n_targets <= (1024 if D == 64 else 640)
+    sgm_bytes = n_targets * ((10.0 if few else 6.25) * npix * D + 8 * npix)
     per_view = (t["cost"] + t["sgm"] + t["fuse"]) / n_targets + (t["census"] + t["range"] + t["reference"]) / 60
     res = {"workload": f"60 ring views {width}x{height} (ray-cast, textured), {D} planes, Census 7x7, SGM 4 paths "
                        f"P1={pr.p1} P2={pr.p2}, {n_targets} target views, 100k sparse points",

@@ -71,7 +71,8 @@ typedef enum pgs_status {
 #define PGS_PROJ_G 8
 #define PGS_PROJ_BLUE 9
 #define PGS_PROJ_EXTENT_X 10 /* half-extents of the pixels where alpha can reach */
-#define PGS_PROJ_EXTENT_Y 11 /* 1/255 (conservative; -1 = nowhere, inf = unknown) */
+#define PGS_PROJ_EXTENT_Y 11 /* 1/255 (conservative; -1 = nowhere, inf = unknown; */
+                             /* for callers, no kernel of the library reads them) */
 #define PGS_PROJ_FIELDS 12
 #define PGS_PROJ_STRIDE 16
 
@@ -524,7 +525,10 @@ pgs_status pgs_pca_seed(const float* points_dev, const float* colours_dev, int32
  * Learned seeding network.  Not part of PocketGS: a network that corrects
  * the disc-like seed of pgs_pca_seed (Sec. "Disc-Like Covariance Seeding")
  * from the point's neighbourhood.  Layers 64 -> 64 -> 64 -> 64 -> 8 with
- * exact-erf GELU after each hidden layer; every product multiplies bfloat16
+ * erf GELU after each hidden layer (pgs_mlp_forward through the library's
+ * erff; pgs_mlp_backward forms its activations again through a fit of erfc
+ * that is as close to the exact value, so a bfloat16 activation may differ
+ * from the forward's in its last place); every product multiplies bfloat16
  * operands (float32 values rounded to nearest, ties to even) and
  * accumulates in float32.  Weights: one float32 vector of
  * pgs_mlp_weight_count() = 13000 values, [W1 (64 x 64, row = output), b1,

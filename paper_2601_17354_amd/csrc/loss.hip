@@ -18,7 +18,8 @@
 // difference of terms a thousand times its size, so every sum is taken in the
 // order of its taps, with the roundings of the plain formula.
 //
-// Bound by vector issue (forward) and by memory (backward).  With one column
+// The forward spends 55% of its time issuing vector instructions and a third
+// waiting, the backward 32% and over half (its loads).  With one column
 // a lane, 22 (33) single LDS reads a pixel, addresses and bounds in vector
 // registers and 32 rows a wave whatever the image, 1920 x 1440 took 125 us with
 // the final sum, now 119; 1024 x 1024 77, now 60; 317 x 243 55, now 26.  (One

@@ -1045,7 +1045,7 @@ pgs_status check_params(const pgs_mvs_params* p, const char* who) {
 // the sums, run side by side too.  Before, one line per wave with 32-bit
 // planes, path costs stored as bytes and row sums in 16 bits: twelve bytes per
 // cell and about 50 vector instructions a pixel-step against 11; eight
-// 960x720 targets of 128 planes 2.12 -> 1.18 ms, one 0.70 -> 0.37 ms.
+// 960x720 targets of 128 planes 2.12 -> 1.19 ms, one 0.70 -> 0.37 ms.
 template <int D>
 constexpr long long kSgmWaves = D == 64 ? 1024 : 640;
 

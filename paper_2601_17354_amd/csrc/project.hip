@@ -162,7 +162,9 @@ __device__ __forceinline__ void view_geometry(const double (&mu)[3], const Shape
 // below 20 * 2^-24 / (1 - rho), rho = |B| / sqrt(AC)) and of exp (1e-3 added
 // to tau).  (-1, -1) when o is below the threshold (no pixel qualifies);
 // (inf, inf) when the conic is too close to degenerate (1 - rho < 1e-3) for
-// the bound, so that nothing is skipped.
+// the bound, so that nothing is skipped.  The extents are part of the record
+// for its readers outside; the compositing kernels test each wave's rows
+// against the conic itself, which keeps fewer splats.
 __device__ __forceinline__ double alpha_tau(float o) { return 2.0 * log(255.0 * fmax((double)o, 1.0 / 255.0)); }
 
 __device__ __forceinline__ void alpha_extent(float A, float B, float C, float o, double tau, float& hx, float& hy) {

@@ -50,8 +50,8 @@
 #include "common.hpp"
 
 // Splats a wave composites between two termination checks.  Four leave room for
-// eight waves a SIMD with their colours at hand: 300k Gaussians at 1920 x 1440
-// 201 us, with six 210, with eight 219.
+// eight waves a SIMD with their colours at hand (untraced, 300k Gaussians at
+// 1920 x 1440: six took 1.05 times as long, eight 1.09 times).
 #ifndef FWD_UNROLL
 #define FWD_UNROLL 4
 #endif
@@ -424,8 +424,9 @@ __device__ __forceinline__ void fwd_tile(const TileJob& j, int n_tiles_total, in
         // with the alphas and colours fetched between the steps' branches, lane
         // masks in vector registers and a 64 x 64 bit transpose a window for
         // the trace, 300k Gaussians at 1920 x 1440 took 227 us untraced, now
-        // 187, traced 510, now 477 (of which 1.5 GB of entries at the card's
-        // write rate would take 300).
+        // 187 (95% of its issue slots), traced 510, now 477 (80%: the entry
+        // pass issues as many vector instructions again, 102M to the 98M here,
+        // beside 1.5 GB of writes that take 260 alone).
         for (int c0 = 0; c0 < nb; c0 += 64) {
             if (live == 0ull) break;  // the whole wave has terminated
             const int cn = min(64, nb - c0);

@@ -31,7 +31,7 @@
 // round to the k-th's float32 are gone through again with keys of their exact
 // distances (knn_ties).  On 300k points of a
 // scene's surfaces with k = 16 the search went from 0.93 to 0.20 ms (41M vector
-// instructions, 306 MB of writes scattered to the queries' own order) and the
+// instructions, 314 MB of writes scattered to the queries' own order) and the
 // whole call from 1.06 to 0.27 ms; on 2000 points from 7.8 to 0.17 ms.
 //
 // pgs_pca_seed: per point, in float64: covariance of the 16 neighbours about
