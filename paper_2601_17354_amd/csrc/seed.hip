@@ -471,8 +471,10 @@ __device__ __forceinline__ bool knn_ties(const float4* __restrict__ sorted, int 
     return exact;
 }
 
-// Bound by vector issue: about 15 instructions per candidate and, whenever
-// one of the wave's lanes takes it, two per slot of the list.
+// About 15 vector instructions per candidate and, whenever one of the wave's
+// lanes takes it, two per slot of the list, most of them float64: at 300k points
+// a third of the waves' time waits for an issue slot, 43% for the candidates'
+// loads (three waves a SIMD, what the list's registers leave).
 template <int K>
 __global__ __launch_bounds__(kKnnThreads) void k_knn_grid(const float4* __restrict__ sorted, int m,
                                                           const GridDesc* __restrict__ desc,
