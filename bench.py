@@ -867,8 +867,8 @@ def bin_sort_roofline(recs, n):
     return {"kernel": "bin_sort", "bound": "hbm", "achieved": b8 / (t_ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": b8 / (t_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, "avg_ms": t_ms / k,
             "algorithmic_bytes": b8 / k, "algorithmic_bytes_design": bd / k,
-            "frac_design": bd / (t_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, "launches_per_step": 28,
-            "note": "latency-bound: 28 dependent launches, most of them a few microseconds long"}
+            "frac_design": bd / (t_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, "launches_per_step": 19,
+            "note": "latency-bound: 19 dependent launches, most of them a few microseconds long"}
 
 
 def atomic_runs(tr, reps=5):

@@ -368,9 +368,9 @@ __global__ __launch_bounds__(256) void k_ba_rows(int n_cams, int gauge_axis, dou
 // turning and moving a camera hardly differ.  One workgroup factoring a panel,
 // another launch updating the
 // trailing triangle and a triangular solve per row of the panel took 505 + 74
-// us at 60 cameras (nf = 353), 12 launches of 14.2 us and 39 + 11 us for the
-// back substitution and the first block now (products with inverses: 12.4 and
-// 31): each launch's fixed 4 us, its substitution and the 5 us of its 32 pivots
+// us at 60 cameras (nf = 353), 12 launches of 13.3 us and 39 + 10 us for the
+// back substitution and the first block now (products with inverses: 12.3 and
+// 30): each launch's fixed 4 us, its substitution and the 5 us of its 32 pivots
 // are what is left.
 constexpr int kPW = 32;
 constexpr int kPS = kPW + 1;
